@@ -137,10 +137,8 @@ struct PrefillArgs {
   const int32_t* block_table;   // [B, max_pages]
   int32_t page_shift, n_pages, max_pages;
   int32_t batch, n_new, n_q, n_kv, group, d_k, d_v, max_len;
-  int32_t tok_per_wg;       // query tokens per workgroup: (64 NQ) / G
+  int32_t tok_per_wg;       // query tokens per workgroup
   int32_t n_qblk;           // ceil(n_new / tok_per_wg)
-  int32_t lds_buf_bytes;    // one K + V tile buffer
-  int32_t pad_k, pad_v;     // LDS row padding in bytes (0 or 16)
   int64_t cap;
   float scale_log2e;
   // Key ranges (n_ksplit > 1, for launches whose query blocks alone would not fill the chip): a
@@ -159,10 +157,39 @@ struct PrefillArgs {
 struct PrefillPlan {
   int tok_per_wg, n_qblk, n_ksplit, tiles_per_split;
 };
-// Column blocks (of 16 query columns) per wavefront in the prefill kernel: four where the registers
-// hold their accumulators, three at d_k > 96 or d_v > 96.  The plan and the kernel's table of
-// instantiations both go by these.
-constexpr int kPrefillBlocks = 4, kPrefillBlocksWide = 3;
+// The prefill kernel's sizes: wavefronts of a workgroup, keys of a staged tile, blocks of 16 query
+// columns per wavefront (four where the registers hold their accumulators, three at d_k > 96 or
+// d_v > 96), and the pitches of a tile's rows in LDS (K: 16 bytes past a multiple of 64, V: an odd
+// multiple of 32 bytes, so that neither kind of read meets its own banks).  The plan, the kernel
+// and the launch all go by these.
+constexpr int kPrefillWaves = 4, kPrefillTile = 64;
+enum { kTilesDirect = 0, kTilesOddV = 1, kTilesCodes = 2 };   // bf16 rows of even width, odd V rows, one-byte codes
+constexpr int prefill_k_pitch(int k_steps) { return 64 * k_steps + 16; }
+constexpr int prefill_v_pitch(int channel_tiles) { return 32 * (channel_tiles | 1); }
+constexpr int prefill_blocks(int k_steps, int channel_tiles) { return k_steps > 3 || channel_tiles > 6 ? 3 : 4; }
+constexpr int prefill_tokens_per_wg(int k_steps, int channel_tiles, int group) {
+  return 16 * kPrefillWaves * prefill_blocks(k_steps, channel_tiles) / group;
+}
+// Which query block, slab (sequence and KV head) and key range workgroup `wg` takes.  Hardware
+// places workgroup L on XCD L mod 8, each with an L2 of its own, and all query blocks of a slab
+// read the same K and V rows: with a multiple of 8 slabs, an XCD takes one slab after the other.
+// Within a slab the heaviest query blocks (the last tokens, which see the most rows) come first.
+__host__ __device__ __forceinline__ void prefill_place(int wg, int n_qblk, int slabs, int n_ksplit, int* qb, int* slab, int* ks) {
+  const int per_slab = n_qblk * n_ksplit;
+  int r;
+  if ((slabs & 7) == 0) {
+    const int x = wg >> 3;
+    *slab = (x / per_slab) * 8 + (wg & 7);
+    r = x % per_slab;
+    *ks = r % n_ksplit;
+    *qb = n_qblk - 1 - r / n_ksplit;
+  } else {
+    *ks = wg % n_ksplit;
+    r = wg / n_ksplit;
+    *slab = r % slabs;
+    *qb = n_qblk - 1 - r / slabs;
+  }
+}
 PrefillPlan prefill_plan(int batch, int n_kv, int group, int d_k, int d_v, int n_new, int max_len);
 
 // fp64 -> E4M3 code (finite-only 8-bit float: 4 exponent bits, bias 7, 3 mantissa bits, no
