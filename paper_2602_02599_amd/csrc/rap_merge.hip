@@ -13,32 +13,56 @@
 // worked out here, by the workgroup of the query row: each thread multiplies one element of the
 // query row with the same element of the new K rows, the products are summed over the workgroup,
 // and the weighted new V rows enter the combination like one more range.
+//
+// Latency is all there is to this kernel (a few MB at most): the partials miss L2, they were written
+// through other XCDs, so one round trip for everything is the floor.  Eight slots per thread are
+// requested together, before the sequence length is known, and GRP groups of 128 threads take
+// eight slots each side by side, so that up to 8 GRP ranges cost one round trip; the groups meet in
+// LDS.  64 ranges (one sequence of 32768 rows, 32 query heads): 11.3 us with one group, 4.9 us with
+// eight.  Up to eight ranges one group is enough, and its smaller workgroup starts faster.
 #include "rap_device.h"
 
 namespace rap {
 
 constexpr int kMaxTok = 16;
+constexpr int kMergeSlots = 8;                     // slots a thread has in flight
 
-template <bool MULTI>
-__global__ __launch_bounds__(128) void merge_kernel(DecodeArgs a) {
+// MT: 0 for one query token, else an upper bound of n_tok (the loops over new tokens are unrolled to it).
+template <int MT, int GRP>
+__global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
+  constexpr bool MULTI = MT > 0;
   const long long hq = blockIdx.x;                 // query row: (b * n_tok + token) * n_q + query head
   const int b = static_cast<int>(hq / (static_cast<long long>(a.n_q) * a.n_tok));
-  const int c = threadIdx.x;
+  const int c = threadIdx.x & 127;
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
   const bool live = c < a.d_v;
   const float* ml = a.part_ml + hq * a.n_slots * 2;
   const float* accc = a.part_acc + hq * a.n_slots * a.d_v + (live ? c : 0);
-  const bool tok = a.n_slots > a.n_split;          // the slot behind the ranges is in use
+  // All slots of a query head are allocated, whatever they hold, so this group's first eight are
+  // requested before anything else is known.
+  float m[kMergeSlots], l[kMergeSlots], v[kMergeSlots];
+  auto request = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < kMergeSlots; ++u) {
+      const bool have = s0 + u < a.n_split;
+      m[u] = have ? ml[2 * (s0 + u)] : -INFINITY;
+      l[u] = have ? ml[2 * (s0 + u) + 1] : 0.f;
+      v[u] = have ? accc[static_cast<long long>(s0 + u) * a.d_v] : 0.f;
+    }
+  };
+  request(kMergeSlots * grp);
+  const bool tok = grp == 0 && a.n_slots > a.n_split;   // the slot behind the ranges is in use
   float m_tok = tok ? ml[2 * a.n_split] : -INFINITY;
   float l_tok = tok ? ml[2 * a.n_split + 1] : 0.f;
   float v_tok = tok ? accc[static_cast<long long>(a.n_split) * a.d_v] : 0.f;
   const int t_new = a.new_pos != nullptr ? a.new_pos[b] : -1;
+  int len = a.seq_lens[b];
+  len = len < 0 ? 0 : (len > a.max_len ? a.max_len : len);
   if constexpr (MULTI) {
-    __shared__ float s_dot[2][kMaxTok];
+    __shared__ float s_dot[2][MT > 0 ? MT : 1];
     const int T = a.n_tok, G = a.group;
     const int t = static_cast<int>((hq / a.n_q) % T);           // this query row's token
     const int h = static_cast<int>(hq % a.n_q) / G;             // and KV head
-    int len = a.seq_lens[b];
-    len = len < 0 ? 0 : (len > a.max_len ? a.max_len : len);
     const int p0 = len - T;                                     // position of new token 0, may be negative
     const bool q8 = a.k_scale != nullptr;
     // row of the cache (dense) or of the pool (paged) that holds position pos >= 0
@@ -50,17 +74,15 @@ __global__ __launch_bounds__(128) void merge_kernel(DecodeArgs a) {
     };
     const bool have_k = c < a.d_k;
     const float qv = have_k ? bf16_to_f32(a.q[hq * a.d_k + c]) : 0.f;
-    float prod[kMaxTok], vnew[kMaxTok];
-    // The loads of all n_tok slots are issued first and used afterwards, so that they travel
-    // together: slot j beyond this token's own row repeats that row, a position in front of the
-    // sequence reads row 0; what such a slot holds is dropped below by a select.
+    float prod[MT], vnew[MT];
+    // The loads of all slots are issued first and used afterwards, so that they travel together:
+    // slot j beyond this token's own row repeats that row, a position in front of the sequence
+    // reads row 0; what such a slot holds is dropped below by a select.
     const int ck = have_k ? c : 0, cv = live ? c : 0;
-    uint32_t kraw[kMaxTok], vraw[kMaxTok];
+    if (grp == 0) {
+      uint32_t kraw[MT], vraw[MT];
 #pragma unroll
-    for (int j = 0; j < kMaxTok; ++j) {
-      kraw[j] = 0;
-      vraw[j] = 0;
-      if (j < T) {
+      for (int j = 0; j < MT; ++j) {
         const int pos = p0 + (j < t ? j : t);
         const long long row = row_of(pos < 0 ? 0 : pos);
         if (q8) {
@@ -71,80 +93,63 @@ __global__ __launch_bounds__(128) void merge_kernel(DecodeArgs a) {
           vraw[j] = a.v_cache[row * a.d_v + cv];
         }
       }
-    }
 #pragma unroll
-    for (int j = 0; j < kMaxTok; ++j) {
-      const float kf = q8 ? e4m3_to_f32(static_cast<uint8_t>(kraw[j])) : bf16_to_f32(static_cast<uint16_t>(kraw[j]));
-      vnew[j] = q8 ? e4m3_to_f32(static_cast<uint8_t>(vraw[j])) : bf16_to_f32(static_cast<uint16_t>(vraw[j]));
-      prod[j] = have_k ? qv * kf : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < kMaxTok; ++j) {
-      if (j < T) {
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) prod[j] += __shfl_xor(prod[j], o);
+      for (int j = 0; j < MT; ++j) {
+        const float kf = q8 ? e4m3_to_f32(static_cast<uint8_t>(kraw[j])) : bf16_to_f32(static_cast<uint16_t>(kraw[j]));
+        vnew[j] = q8 ? e4m3_to_f32(static_cast<uint8_t>(vraw[j])) : bf16_to_f32(static_cast<uint16_t>(vraw[j]));
+        prod[j] = have_k ? qv * kf : 0.f;
       }
-    }
-    if ((c & 63) == 0) {
 #pragma unroll
-      for (int j = 0; j < kMaxTok; ++j) s_dot[c >> 6][j] = prod[j];
+      for (int o = 32; o >= 1; o >>= 1) {
+#pragma unroll
+        for (int j = 0; j < MT; ++j) prod[j] += __shfl_xor(prod[j], o);
+      }
+      if ((c & 63) == 0) {
+#pragma unroll
+        for (int j = 0; j < MT; ++j) s_dot[c >> 6][j] = prod[j];
+      }
     }
     __syncthreads();
-    const float sc = q8 ? a.scale_log2e * a.k_scale[h] : a.scale_log2e;
-    float x[kMaxTok];
-    m_tok = -INFINITY;
+    if (grp == 0) {
+      const float sc = q8 ? a.scale_log2e * a.k_scale[h] : a.scale_log2e;
+      float x[MT];
+      m_tok = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kMaxTok; ++j) {
-      x[j] = (j <= t && p0 + j >= 0) ? (s_dot[0][j] + s_dot[1][j]) * sc : -INFINITY;
-      m_tok = fmaxf(m_tok, x[j]);
-    }
-    l_tok = 0.f;
-    v_tok = 0.f;
-    if (m_tok > -INFINITY) {
-#pragma unroll
-      for (int j = 0; j < kMaxTok; ++j) {
-        const bool in = j <= t && p0 + j >= 0;
-        const float pj = in ? exp2f(x[j] - m_tok) : 0.f;
-        l_tok += pj;
-        v_tok = fmaf(pj, in ? vnew[j] : 0.f, v_tok);            // a left-out slot may hold NaN or inf
+      for (int j = 0; j < MT; ++j) {
+        x[j] = (j <= t && p0 + j >= 0) ? (s_dot[0][j] + s_dot[1][j]) * sc : -INFINITY;
+        m_tok = fmaxf(m_tok, x[j]);
       }
-      if (q8) v_tok *= a.v_scale[h];
+      l_tok = 0.f;
+      v_tok = 0.f;
+      if (m_tok > -INFINITY) {
+#pragma unroll
+        for (int j = 0; j < MT; ++j) {
+          const bool in = j <= t && p0 + j >= 0;
+          const float pj = in ? exp2f(x[j] - m_tok) : 0.f;
+          l_tok += pj;
+          v_tok = fmaf(pj, in ? vnew[j] : 0.f, v_tok);          // a left-out slot may hold NaN or inf
+        }
+        if (q8) v_tok *= a.v_scale[h];
+      }
     }
   }
-  // All slots of a query head are allocated, whatever they hold, so they are requested before the
-  // sequence length is known, eight at a time: up to eight ranges cost one memory round trip (these
-  // reads miss L2, the partials were written through other XCDs; wider groups were measured and
-  // do not help: with 32 ranges the kernel takes 7.4 us either way).  Slots beyond the ranges that
-  // hold rows are dropped by a select, not multiplied.
-  constexpr int kGroup = 8;
+  int n = a.n_split;                               // ranges that hold rows (prefill key ranges: every slot was written)
+  if (!a.all_slots) {
+    if (len > 0 && t_new == len - 1) len -= 1;     // the first stage stopped before the new token's row
+    if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;   // or before the new tokens' rows
+    n = (len + a.rows_per_split - 1) / a.rows_per_split;
+  }
   float mstar = m_tok, den = 0.f, num = 0.f;
   if (m_tok > -INFINITY) {
     den = l_tok;
     num = v_tok;
   }
-  int n = 0;
-  for (int s0 = 0; s0 < a.n_split; s0 += kGroup) {
-    float m[kGroup], l[kGroup], v[kGroup];
-#pragma unroll
-    for (int u = 0; u < kGroup; ++u) {
-      const bool have = s0 + u < a.n_split;
-      m[u] = have ? ml[2 * (s0 + u)] : -INFINITY;
-      l[u] = have ? ml[2 * (s0 + u) + 1] : 0.f;
-      v[u] = have ? accc[static_cast<long long>(s0 + u) * a.d_v] : 0.f;
-    }
-    if (s0 == 0 && a.all_slots) {
-      n = a.n_split;                               // prefill key ranges: every slot was written
-    } else if (s0 == 0) {
-      int len = a.seq_lens[b];
-      len = len < 0 ? 0 : (len > a.max_len ? a.max_len : len);
-      if (len > 0 && t_new == len - 1) len -= 1;   // the first stage stopped before the new token's row
-      if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;   // or before the new tokens' rows
-      n = (len + a.rows_per_split - 1) / a.rows_per_split;   // ranges that hold rows
-    }
-    if (s0 >= n) break;
+  // slots beyond the ranges that hold rows are dropped by a select, not multiplied
+  for (int s0 = kMergeSlots * grp; s0 < n; s0 += kMergeSlots * GRP) {
+    if (s0 != kMergeSlots * grp) request(s0);
     float gmax = -INFINITY;
 #pragma unroll
-    for (int u = 0; u < kGroup; ++u) {
+    for (int u = 0; u < kMergeSlots; ++u) {
       if (s0 + u >= n) {                           // unwritten slot: any bits, NaN included
         m[u] = -INFINITY;
         l[u] = 0.f;
@@ -159,22 +164,53 @@ __global__ __launch_bounds__(128) void merge_kernel(DecodeArgs a) {
       mstar = gmax;
     }
 #pragma unroll
-    for (int u = 0; u < kGroup; ++u) {
+    for (int u = 0; u < kMergeSlots; ++u) {
       const bool has = m[u] > -INFINITY;           // an empty range leaves only its reference and sum
       const float w = has ? exp2f(m[u] - mstar) : 0.f;
       den = fmaf(w, l[u], den);
       num = fmaf(w, has ? v[u] : 0.f, num);
     }
   }
+  if constexpr (GRP > 1) {
+    __shared__ float s_m[GRP], s_den[GRP], s_num[GRP][128];
+    if (c == 0) {
+      s_m[grp] = mstar;
+      s_den[grp] = den;
+    }
+    s_num[grp][c] = num;
+    __syncthreads();
+    if (grp != 0) return;
+#pragma unroll
+    for (int g = 1; g < GRP; ++g) mstar = fmaxf(mstar, s_m[g]);
+    den = 0.f;
+    num = 0.f;
+#pragma unroll
+    for (int g = 0; g < GRP; ++g) {
+      const float w = s_m[g] > -INFINITY ? exp2f(s_m[g] - mstar) : 0.f;
+      den = fmaf(w, s_den[g], den);
+      num = fmaf(w, s_num[g][c], num);
+    }
+  }
   if (live) a.out[hq * a.d_v + c] = den > 0.f ? num / den : 0.f;
 }
 
+namespace {
+
+template <int MT>
+void launch_groups(const DecodeArgs& a, hipStream_t stream) {
+  dim3 grid(static_cast<unsigned>(a.batch) * a.n_tok * a.n_q);
+  if (a.n_split <= kMergeSlots) hipLaunchKernelGGL((merge_kernel<MT, 1>), grid, dim3(128), 0, stream, a);
+  else if (a.n_split <= 2 * kMergeSlots) hipLaunchKernelGGL((merge_kernel<MT, 2>), grid, dim3(256), 0, stream, a);
+  else if (a.n_split <= 4 * kMergeSlots) hipLaunchKernelGGL((merge_kernel<MT, 4>), grid, dim3(512), 0, stream, a);
+  else hipLaunchKernelGGL((merge_kernel<MT, 8>), grid, dim3(1024), 0, stream, a);
+}
+
+}  // namespace
+
 hipError_t launch_merge(const DecodeArgs& a, hipStream_t stream) {
-  dim3 grid(static_cast<unsigned>(a.batch) * a.n_tok * a.n_q), block(128);
-  if (a.n_tok > 1 && !a.all_slots)
-    hipLaunchKernelGGL(merge_kernel<true>, grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL(merge_kernel<false>, grid, block, 0, stream, a);
+  if (a.n_tok <= 1 || a.all_slots) launch_groups<0>(a, stream);
+  else if (a.n_tok <= 4) launch_groups<4>(a, stream);
+  else launch_groups<kMaxTok>(a, stream);
   return hipGetLastError();
 }
 
