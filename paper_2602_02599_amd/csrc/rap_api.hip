@@ -76,44 +76,95 @@ int device_cus() {
   return n;
 }
 
-// Row range per workgroup.  A workgroup whose range starts at or beyond its sequence's length
-// exits at once, so ragged batches cost only empty launches.  Measured on MI355X: a workgroup
-// should stream for a long time (its fixed cost is a few microseconds), and when the whole job
-// fits in one round of resident workgroups their number should be a multiple of the compute
-// units.  So: about two workgroups per compute unit when the (b, h) count allows it, ranges never
-// shorter than 512 rows nor longer than 4096 (longer ranges only lengthen the tail of a ragged
-// batch) - except when that ceiling would leave a second, partly filled round of workgroups
-// (more than the chip holds at once, fewer than twice that): then ranges of up to 8192 rows bring
-// the job back into a single round of two workgroups per compute unit (cfg4 shape, 4 x 8 slabs of
-// 131072 rows: 1024 workgroups of 4096 rows over 768 places took 195 us, 512 of 8192 rows 189 us).
-rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuning_t* t, Plan* p) {
-  int rps = t ? t->rows_per_split : 0;
+size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// Bytes of the partials of n_split ranges (and the extra slot): accumulators, then (reference, sum).
+size_t partial_bytes(const rap_shape_t* s, int n_split, int n_tok) {
+  const size_t slots = static_cast<size_t>(s->batch) * n_tok * s->n_q_heads * (n_split + 1);
+  return align_up(slots * s->d_v * sizeof(float), 256) + align_up(slots * 2 * sizeof(float), 256) + 256;
+}
+
+int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap::kSplitQuantum * rap::kSplitQuantum; }
+
+// Row range per workgroup, a function of the shape and max_seq_len alone.  A workgroup whose range
+// starts at or beyond its sequence's length exits at once.  Measured on MI355X (bf16, d = 90, 8 KV
+// heads unless said otherwise, attention call in a graph; "ragged": lengths spread evenly from
+// max / 16 to max, which the host cannot see):
+//  * A launch takes 6.9 us with one 128-row step per workgroup and 1.25 us more for each further
+//    step; cutting into ranges adds a combining launch, 2.7 us.  So while one range per compute unit
+//    is at most 512 rows, that is the range, if it spares three steps or more (1 x 2048 rows: 14.0 us
+//    in ranges of 512, 10.5 in 128; 1 x 8192: 15.0 in 512, 13.5 in 256; 16 x 512: 13.2 in 256, 12.0
+//    whole); and with a slab for every compute unit up to 1024 rows stay whole (32 x 1024: 23.4 us
+//    in two ranges, 22.1 in one).
+//  * Beyond that the chip wants at least two workgroups per compute unit, of 512 rows or more.
+//    Where the slabs do not divide that number, more and shorter ranges that do come out even are
+//    better: 24 x 8192 (192 slabs) 102 us with 2 ranges per slab, 95 with 4; 40 x 4096 (320 slabs) 94
+//    us with one, 82 with 4.
+//  * Long ranges save a little on equal lengths and cost a lot on ragged ones, whose workgroups are
+//    then few and unequal: an eighth of max_seq_len, no less than 2048 and no more than 4096 rows.
+//    64 x 16384: 451 / 456 / 464 us in 8192 / 4096 / 2048 rows, ragged 327 / 274 / 265; 32 x 16384
+//    230 / 231 / 232, ragged 159 / 145 / 141; fp8 32 x 16384 137 / 147 / 137, ragged 117 / 89 / 87;
+//    64 x 32768 892 / 902 / 931, ragged 539 / 520 / 515.  Up to 16 sequences keep the plain rule's
+//    ranges of up to 8192 rows where those bring the job into a single round (4 x 131072, d = 64: 167
+//    us in 8192 rows, 171 in 4096).
+//  * The plan never takes more partials than the static scratch array holds where the plain rule
+//    (two workgroups per compute unit, ranges of 512 to 4096 rows, up to 8192 where that avoids a
+//    partly filled second round of workgroups) would not, so that what a caller with that much
+//    scratch may ask for does not depend on any of the above.  A caller who hands in less than the
+//    plan wants, but enough for the plain rule, gets the plain rule (`plain`).
+rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuning_t* t, Plan* p, bool plain = false) {
+  const int rps = t ? t->rows_per_split : 0;
   if (rps < 0 || (rps % rap::kSplitQuantum) != 0) return RAP_ERR_SHAPE;
   const int kernel = t ? t->kernel : 0;
   if (kernel < 0 || kernel > 2) return RAP_ERR_SHAPE;
-  if (rps == 0) {
-    const int cus = device_cus();
-    const int64_t slabs = static_cast<int64_t>(s->batch) * s->n_kv_heads;
-    int64_t per_slab = slabs > 0 ? (2LL * cus) / slabs : 1;            // ranges per (b, h)
-    if (per_slab < 1) per_slab = 1;
-    int64_t r = (max_seq_len + per_slab - 1) / per_slab;
-    r = (r + rap::kSplitQuantum - 1) / rap::kSplitQuantum * rap::kSplitQuantum;
-    const int64_t single_round = r;
-    if (r < 512) r = 512;
-    if (r > 4096) r = 4096;
-    // workgroups the chip holds at once: three per compute unit up to d_k = 96, else two
-    const int64_t places = static_cast<int64_t>(cus) * (2 * s->n_pairs <= 96 ? 3 : 2);
-    const int64_t n_wg = slabs * ((max_seq_len + r - 1) / r);
-    if (n_wg > places && n_wg < 2 * places && single_round <= 8192) r = single_round;
-    rps = static_cast<int>(r);
-  }
-  p->rows_per_split = rps;
-  p->n_split = static_cast<int>((max_seq_len + rps - 1) / rps);
   p->kernel = kernel == 0 ? 2 : kernel;
+  auto ranges_of = [&](int64_t rows) { return static_cast<int>((max_seq_len + rows - 1) / rows); };
+  if (rps != 0) {
+    p->rows_per_split = rps;
+    p->n_split = ranges_of(rps);
+    return RAP_OK;
+  }
+  const int64_t cus = device_cus();
+  const int64_t slabs = s->batch > 0 ? static_cast<int64_t>(s->batch) * s->n_kv_heads : 1;
+  const int64_t k0 = 2 * cus / slabs > 1 ? 2 * cus / slabs : 1;                // ranges per slab, plain rule
+  const int64_t halves = round_to_quantum((max_seq_len + k0 - 1) / k0);
+  int64_t r = halves < 512 ? 512 : (halves > 4096 ? 4096 : halves);
+  // workgroups the chip holds at once: three per compute unit up to d_k = 96, else two
+  const int64_t places = cus * (2 * s->n_pairs <= 96 ? 3 : 2);
+  const int64_t n_wg = slabs * ((max_seq_len + r - 1) / r);
+  const bool single_round = n_wg > places && n_wg < 2 * places && halves <= 8192;
+  if (single_round) r = halves;
+  p->rows_per_split = static_cast<int>(r);
+  p->n_split = ranges_of(r);
+  if (plain) return RAP_OK;
+
+  const int64_t per_cu = slabs >= 4 * cus ? max_seq_len : round_to_quantum((max_seq_len * slabs + cus - 1) / cus);
+  if (per_cu <= 512) {
+    r = max_seq_len - per_cu >= 3 * rap::kSplitQuantum ? per_cu : round_to_quantum(max_seq_len);
+  } else if (slabs >= cus && max_seq_len <= 1024) {
+    r = round_to_quantum(max_seq_len);
+  } else {
+    int64_t k = k0;
+    double best = 0.0;
+    for (int64_t c = k0; c <= 4 * k0 && (c == k0 || max_seq_len >= 1024 * c); ++c) {
+      const int64_t n = slabs * c, rounds = (n + cus - 1) / cus;
+      const double even = static_cast<double>(n) / static_cast<double>(rounds * cus) - 0.03 * static_cast<double>(c - k0) / static_cast<double>(k0);
+      if (even > best + 0.02) {
+        best = even;
+        k = c;
+      }
+    }
+    const int64_t eighth = round_to_quantum(max_seq_len / 8);
+    const int64_t most = eighth < 2048 ? 2048 : (eighth > 4096 ? 4096 : eighth);
+    r = round_to_quantum((max_seq_len + k - 1) / k);
+    r = r < 512 ? 512 : (r > most ? most : r);
+    if (single_round && s->batch <= 16) r = halves;
+  }
+  if (ranges_of(r) > p->n_split && partial_bytes(s, ranges_of(r), 1) > RAP_STATIC_SCRATCH_BYTES) return RAP_OK;   // plain
+  p->rows_per_split = static_cast<int>(r);
+  p->n_split = ranges_of(r);
   return RAP_OK;
 }
-
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Workspace = accumulators [B, H_q, n_split + 1, d_v], then (reference, sum) pairs
 // [B, H_q, n_split + 1, 2], fp32, each block rounded up to 256 bytes; the extra slot is the new
@@ -122,12 +173,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 size_t part_acc_bytes(const rap_shape_t* s, const Plan& p, int n_tok = 1) {
   return align_up(static_cast<size_t>(s->batch) * n_tok * s->n_q_heads * (p.n_split + 1) * s->d_v * sizeof(float), 256);
 }
-size_t part_ml_bytes(const rap_shape_t* s, const Plan& p, int n_tok = 1) {
-  return align_up(static_cast<size_t>(s->batch) * n_tok * s->n_q_heads * (p.n_split + 1) * 2 * sizeof(float), 256);
-}
-size_t workspace_need(const rap_shape_t* s, const Plan& p, int n_tok = 1) {
-  return part_acc_bytes(s, p, n_tok) + part_ml_bytes(s, p, n_tok) + 256;
-}
+size_t workspace_need(const rap_shape_t* s, const Plan& p, int n_tok = 1) { return partial_bytes(s, p.n_split, n_tok); }
 
 // page_rows a power of two in [32, 65536], table present, logical capacity consistent
 rap_status_t check_paging(const rap_shape_t* s, const rap_paging_t* pg, int* shift) {
@@ -278,9 +324,17 @@ rap_status_t decode_impl(const DecodeRequest& r) {
   if (multi && (p.kernel != 2 || step || r.q_pos ||
                 static_cast<int64_t>(r.n_tok) * (shape->n_q_heads / shape->n_kv_heads) > 16))
     return RAP_ERR_UNSUPPORTED;
+  // (a workspace too small for the plan, but large enough for the plain rule's, gets the latter)
+  auto holds = [&](const Plan& q) {
+    return !(q.n_split > 1 || fused_step || multi) || (r.workspace && r.workspace_bytes >= workspace_need(shape, q, r.n_tok));
+  };
+  if (!holds(p)) {
+    st = make_plan(shape, r.max_seq_len, r.tuning, &p, true);
+    if (st != RAP_OK) return st;
+    if (!holds(p)) return RAP_ERR_WORKSPACE;
+  }
   const bool combine = p.n_split > 1 || fused_step || multi;
   if (combine) {
-    if (!r.workspace || r.workspace_bytes < workspace_need(shape, p, r.n_tok)) return RAP_ERR_WORKSPACE;
     if (misaligned(r.workspace, 256)) return RAP_ERR_WORKSPACE;
   }
   if (p.n_split > 65535 || (static_cast<int64_t>(p.n_split) + 1) * shape->n_kv_heads * shape->batch > kInt32Max)

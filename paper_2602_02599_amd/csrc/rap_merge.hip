@@ -18,7 +18,7 @@
 // through other XCDs, so one round trip for everything is the floor.  Eight slots per thread are
 // requested together, before the sequence length is known, and GRP groups of 128 threads take
 // eight slots each side by side, so that up to 8 GRP ranges cost one round trip; the groups meet in
-// LDS.  64 ranges (one sequence of 32768 rows, 32 query heads): 11.3 us with one group, 4.9 us with
+// LDS.  64 ranges (one sequence of 32768 rows, 32 query heads): 11.3 us with one group, 3.9 us with
 // eight.  Up to eight ranges one group is enough, and its smaller workgroup starts faster.
 #include "rap_device.h"
 
