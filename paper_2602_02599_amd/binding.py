@@ -57,24 +57,40 @@ STATUS = {0: "RAP_OK", 1: "RAP_ERR_NULL", 2: "RAP_ERR_SHAPE", 3: "RAP_ERR_UNSUPP
           5: "RAP_ERR_WORKSPACE", 6: "RAP_ERR_HIP", 7: "RAP_ERR_STATIC_LIMIT"}
 
 
-def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor") -> C.c_void_p:
+# A small decode step is over on the GPU before a slow binding has handed the next one in, so the
+# marshalling of a call is kept to what it needs: one test per tensor, plain integers for addresses
+# (the prototypes convert them), and the raw handle of the current stream instead of a Stream object
+# (append and attention of one sequence of 2048 rows: 22 us per step bound by the host, of which the
+# tensors' checks and the stream took more than half).
+
+def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor") -> Optional[int]:
     if t is None:
-        return C.c_void_p(0)
+        return None
+    if t.is_cuda and (dtype is None or t.dtype is dtype) and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError("%s must live on the GPU" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if dtype is not None and t.dtype != dtype:
-        raise ValueError("%s must be %s, got %s" % (name, dtype, t.dtype))
-    return C.c_void_p(t.data_ptr())
+    raise ValueError("%s must be %s, got %s" % (name, dtype, t.dtype))
 
 
-def _stream(stream) -> C.c_void_p:
+def _nbytes(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.numel() * t.element_size()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_cur_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _cur_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_cur_device())
         if not torch.cuda.is_available():     # host-only argument checks: nothing will be launched
-            return C.c_void_p(0)
+            return 0
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 class Rap:
@@ -221,7 +237,7 @@ class Rap:
                                       _ptr(v_cache, torch.bfloat16, "v_cache"), _ptr(seq_lens, torch.int32, "seq_lens"),
                                       max_seq_len, _ptr(out, torch.float32, "out"), scale,
                                       _ptr(workspace, None, "workspace"),
-                                      0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                      _nbytes(workspace),
                                       C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -245,7 +261,7 @@ class Rap:
                                            _ptr(k_cache, torch.bfloat16, "k_cache"), _ptr(v_cache, torch.bfloat16, "v_cache"),
                                            _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len,
                                            _ptr(out, torch.float32, "out"), scale, _ptr(workspace, None, "workspace"),
-                                           0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                           _nbytes(workspace),
                                            C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -260,7 +276,7 @@ class Rap:
                                       _ptr(k_cache, torch.bfloat16, "k_cache"), _ptr(v_cache, torch.bfloat16, "v_cache"),
                                       _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len, _ptr(out, torch.float32, "out"),
                                       scale, _ptr(workspace, None, "workspace"),
-                                      0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                      _nbytes(workspace),
                                       C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -313,7 +329,7 @@ class Rap:
                                             _ptr(k_pool, torch.bfloat16, "k_pool"), _ptr(v_pool, torch.bfloat16, "v_pool"),
                                             _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len, _ptr(out, torch.float32, "out"),
                                             scale, _ptr(workspace, None, "workspace"),
-                                            0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                            _nbytes(workspace),
                                             C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -340,7 +356,7 @@ class Rap:
                                          _ptr(k_scale, torch.float32, "k_scale"), _ptr(v_scale, torch.float32, "v_scale"),
                                          _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len, _ptr(out, torch.float32, "out"),
                                          scale, _ptr(workspace, None, "workspace"),
-                                         0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                         _nbytes(workspace),
                                          C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -365,7 +381,7 @@ class Rap:
                                           _ptr(v_codes, torch.uint8, "v_codes"), _ptr(v_scales, torch.uint8, "v_scales"),
                                           _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len, _ptr(out, torch.float32, "out"),
                                           scale, _ptr(workspace, None, "workspace"),
-                                          0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                          _nbytes(workspace),
                                           C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -392,7 +408,7 @@ class Rap:
                                                _ptr(k_scale, torch.float32, "k_scale"), _ptr(v_scale, torch.float32, "v_scale"),
                                                _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len,
                                                _ptr(out, torch.float32, "out"), scale, _ptr(workspace, None, "workspace"),
-                                               0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                               _nbytes(workspace),
                                                C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -410,7 +426,7 @@ class Rap:
                                          _ptr(keep_pair_idx, torch.int32, "keep_pair_idx"), _ptr(q, torch.bfloat16, "q"),
                                          1 if q_is_rotated else 0, _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len,
                                          _ptr(out, torch.float32, "out"), scale, _ptr(workspace, None, "workspace"),
-                                         0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                         _nbytes(workspace),
                                          C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
@@ -441,7 +457,7 @@ class Rap:
         st = self.lib.rap_prefill_attn_split(C.byref(shape), C.byref(cache), n_new, _ptr(q, torch.bfloat16, "q"),
                                              _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len,
                                              _ptr(out, torch.float32, "out"), scale, _ptr(workspace, None, "workspace"),
-                                             0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                             _nbytes(workspace),
                                              _stream(stream))
         if check:
             self._check(st)
@@ -457,7 +473,7 @@ class Rap:
         st = self.lib.rap_decode_attn_multi(C.byref(shape), C.byref(cache), n_tok, _ptr(q, torch.bfloat16, "q"),
                                             _ptr(seq_lens, torch.int32, "seq_lens"), max_seq_len,
                                             _ptr(out, torch.float32, "out"), scale, _ptr(workspace, None, "workspace"),
-                                            0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                            _nbytes(workspace),
                                             C.byref(tuning) if tuning is not None else None, _stream(stream))
         if check:
             self._check(st)
