@@ -138,8 +138,9 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
   p->n_split = ranges_of(r);
   if (plain) return RAP_OK;
 
-  const int64_t per_cu = slabs >= 4 * cus ? max_seq_len : round_to_quantum((max_seq_len * slabs + cus - 1) / cus);
-  if (per_cu <= 512) {
+  const int64_t k1 = cus / slabs > 1 ? cus / slabs : 1;                        // ranges per slab with one workgroup per compute unit
+  const int64_t per_cu = round_to_quantum((max_seq_len + k1 - 1) / k1);
+  if (per_cu <= 512 && slabs <= cus) {
     r = max_seq_len - per_cu >= 3 * rap::kSplitQuantum ? per_cu : round_to_quantum(max_seq_len);
   } else if (slabs >= cus && max_seq_len <= 1024) {
     r = round_to_quantum(max_seq_len);
