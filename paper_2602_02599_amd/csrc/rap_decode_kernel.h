@@ -33,6 +33,8 @@
 #ifndef RAP_DECODE_KERNEL_H_
 #define RAP_DECODE_KERNEL_H_
 
+#include <utility>
+
 #include "rap_device.h"
 
 namespace rap {
@@ -199,6 +201,16 @@ __device__ __forceinline__ void token_finish(const DecodeArgs& a, int b, int h, 
   }
 }
 
+// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
+template <int... Is, class F>
+__device__ __forceinline__ void static_for_pairs_seq(std::integer_sequence<int, Is...>, F&& f) {
+  (f(std::integral_constant<int, Is>()), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for_pairs(F&& f) {
+  static_for_pairs_seq(std::make_integer_sequence<int, N>(), f);
+}
+
 constexpr int kMaxCols = 16;   // columns of the matrix instruction: query rows of one (b, h) with several tokens
 
 // KCH = ceil(d_k / 32) score k-steps, NT = 16-channel output tiles.  VPAIR (even d_v): a lane
@@ -216,24 +228,34 @@ constexpr int kMaxCols = 16;   // columns of the matrix instruction: query rows 
 // lane takes FOUR adjacent V channels of a row with two aligned dwords (NT is 4 or 8, tile nt
 // holds channels 64 (nt / 4) + 4 l16 + (nt & 3)) and sorts the bytes of eight rows into the four
 // operands with byte permutes.
-// MX4: the caches hold 4-bit codes (microscaling FP4: E2M1 elements, one E8M0 scale byte per block
-// of 32 elements; a row is KCH, respectively NT / 2, blocks of 16 code bytes, its scale bytes sit in
-// a second array, four per row).  A tile of 32 rows is a flat run of 16-byte blocks: a lane
-// fetches whole blocks with the scale byte of each, widens a block to 32 bf16 (exactly:
-// v_cvt_scalef32_pk_bf16_fp4 multiplies the two codes of a byte by the scale it is given; compared
-// on the device with the format's table for every byte value and scales from 2^-126 to 2^127) on
-// the way into LDS, and from there on the tile is a bf16 tile of 32 KCH x 16 NT elements (rows and
-// blocks placed so that neither the stores nor the fragment reads collide on LDS banks, see
-// mx4_row_pitch): scores, softmax and P.V are the bf16 path's, instruction for instruction.
-template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, bool MX4 = false>
-__global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(DecodeArgs a) {
-  // 1 KB wave-loads covering a K tile (d_k <= 32 KCH); MX4: 16-byte blocks of the tile per lane
-  constexpr int NLD_K = MX4 ? (kTileRows * KCH + 63) / 64 : k_tile_loads(KCH, Q8);
-  constexpr int NLD_V = MX4 ? (kTileRows * (NT / 2) + 63) / 64 : v_tile_loads(NT, Q8);   // same for a V tile (d_v <= 16 NT)
-  static_assert(!MX4 || (VPAIR && !PAGED && !Q8 && !AL && NT % 2 == 0), "4-bit caches: dense, blocks of 32 channels");
+// MX4B > 0: the caches hold 4-bit codes (microscaling FP4: E2M1 elements, one E8M0 scale byte per
+// block of 32 elements; a row is KCH, respectively MX4B, blocks of 16 code bytes, its scale bytes sit
+// in a second array, four per row).  Codes are widened to bf16 (exactly: v_cvt_scalef32_pk_bf16_fp4
+// multiplies the two codes of a byte by the scale it is given; compared on the device with the
+// format's table for every byte value and scales from 2^-126 to 2^127) in the registers of the lane
+// that feeds them to the matrix instruction, never in LDS: widened tiles in LDS made this variant
+// LDS-bound (address unit 82 % busy, 3.7 TB/s).
+//  * K does not touch LDS at all.  Lane (l16, lg) loads block lg of row l16 of each half tile, 16
+//    bytes, and the row's scale bytes; four lane-group swaps turn that into word lg of every block,
+//    which is the fragment of step kk = block in code form.
+//  * V lies in LDS as it lies in memory, a quarter of a bf16 tile.  A lane takes NT adjacent channels
+//    of each of its eight rows with one read (NT is 8, or 4 where a row has at most two blocks: tile
+//    nt holds channels NT l16 + nt) and one read of the scale byte of their block.
+// Scores and P.V are the bf16 path's, contraction slot for contraction slot: the output is that of
+// the bf16 call on the dequantised cache, bit for bit.  16 x 32768 rows at d = 90 (428 MB): kernel 127
+// -> 93 us (3.4 -> 4.6 TB/s); 64 wide 87 -> 68, 128 wide 130 -> 102 us.  What bounds it now is the
+// vector ALU, 255 instructions per 32 rows and 60 % busy; row masks and clamped V rows are off the
+// common path for that reason (without that 103 us).
+template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, int MX4B = 0>
+__global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B > 0 || KCH <= 3) ? 3 : 2)) void decode_mfma_kernel(DecodeArgs a) {
+  constexpr bool MX4 = MX4B > 0;
+  // 1 KB wave-loads covering a K tile (d_k <= 32 KCH); MX4: one block per lane and half tile
+  constexpr int NLD_K = MX4 ? 2 : k_tile_loads(KCH, Q8);
+  constexpr int NLD_V = MX4 ? (kTileRows * MX4B + 63) / 64 : v_tile_loads(NT, Q8);   // same for a V tile (d_v <= 16 NT)
+  static_assert(!MX4 || (!VPAIR && !PAGED && !Q8 && !AL && NT == mx4_lane_channels(MX4B)), "4-bit caches: dense");
   constexpr int TRIM_K = k_tile_trimmed(Q8), TRIM_V = v_tile_trimmed(Q8);   // trailing loads trimmed by lane
   constexpr int EB = Q8 ? 1 : 2;                   // bytes per cache element
-  constexpr int VLANE = Q8 ? 4 : (VPAIR ? 4 : 2);  // bytes of a V row one lane slot stands for
+  constexpr int VLANE = MX4 ? NT / 2 : Q8 ? 4 : (VPAIR ? 4 : 2);  // bytes of a V row one lane slot stands for
   static_assert(!Q8 || (!VPAIR && (NT == 4 || NT == 8)), "one-byte caches: blocks of 64 channels");
   static_assert(Q8 || !AL, "AL (rows of one-byte codes that keep fragments aligned) belongs to Q8");
   extern __shared__ __align__(16) unsigned char smem[];
@@ -308,12 +330,10 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
   const int G = a.group;
   const int cols = G * a.n_tok;                    // query rows of this (b, h): columns of the matrix instruction
   const int dk = a.d_k, dv = a.d_v;
-  const int pitch_k = MX4 ? 16 * KCH : EB * dk, pitch_v = MX4 ? 8 * NT : EB * dv;   // bytes of a cache row
-  const int lpk = MX4 ? mx4_row_pitch(KCH) : pitch_k, lpv = MX4 ? mx4_row_pitch(NT / 2) : pitch_v;   // bytes of a row in LDS
-  constexpr int SK = MX4 ? mx4_block_stride(KCH) : 64, SV = MX4 ? mx4_block_stride(NT / 2) : 64;    // bytes from one 32-element block of a row to the next
+  const int pitch_k = MX4 ? 16 * KCH : EB * dk, pitch_v = MX4 ? 16 * MX4B : EB * dv;   // bytes of a row, in the cache and in LDS
   // LDS slice of this wavefront: K area and V area, each a whole number of 1 KB wave-stores
   unsigned char* kt = smem + wave * a.lds_wave_bytes;
-  unsigned char* vt = kt + (MX4 ? kTileRows * lpk : 1024 * NLD_K);
+  unsigned char* vt = kt + (MX4 ? 4 * kTileRows : 1024 * NLD_K);   // MX4: the V rows' scale bytes, then their codes
 
   const long long slab = static_cast<long long>(b) * a.n_kv + h;
   const unsigned char* kslab = reinterpret_cast<const unsigned char*>(a.k_cache) + (PAGED ? 0 : slab * a.cap * pitch_k);
@@ -341,31 +361,10 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
   for (int j = 0; j < NLD_K; ++j) kst[j] = make_uint4(0, 0, 0, 0);
 #pragma unroll
   for (int j = 0; j < NLD_V; ++j) vst[j] = make_uint4(0, 0, 0, 0);
-  // MX4: the scale byte that goes with each staged block, where the block lands in LDS, and the
-  // slabs of the scale bytes.  Block c = lane + 64 j of a tile is block c % KCH of row c / KCH.
-  uint32_t kss[MX4 ? NLD_K : 1], vss[MX4 ? NLD_V : 1];
-  int k_lds[MX4 ? NLD_K : 1], v_lds[MX4 ? NLD_V : 1];
-  bool k_rot[MX4 ? NLD_K : 1], v_rot[MX4 ? NLD_V : 1];     // this block stores its pieces in the order 2, 3, 0, 1
-  const unsigned char* ksslab = nullptr;
-  const unsigned char* vsslab = nullptr;
-  if constexpr (MX4) {
-    ksslab = a.k_scales4 + slab * a.cap * 4;
-    vsslab = a.v_scales4 + slab * a.cap * 4;
-#pragma unroll
-    for (int j = 0; j < NLD_K; ++j) {
-      const int c = lane + 64 * j, row = c / KCH;
-      kss[j] = 127;
-      k_lds[j] = row * lpk + (c - row * KCH) * SK;
-      k_rot[j] = mx4_rotate_upper_blocks(KCH) && ((c - row * KCH) & 2) != 0;
-    }
-#pragma unroll
-    for (int j = 0; j < NLD_V; ++j) {
-      const int c = lane + 64 * j, row = c / (NT / 2);
-      vss[j] = 127;
-      v_lds[j] = row * lpv + (c - row * (NT / 2)) * SV;
-      v_rot[j] = mx4_rotate_upper_blocks(NT / 2) && ((c - row * (NT / 2)) & 2) != 0;
-    }
-  }
+  // MX4: the scale bytes of this lane's K rows (l16 of either half) and, lanes below 32, of V row `lane`
+  uint32_t kss[2] = {0, 0}, vss = 0;
+  const unsigned char* ksslab = MX4 ? a.k_scales4 + slab * a.cap * 4 : nullptr;
+  const unsigned char* vsslab = MX4 ? a.v_scales4 + slab * a.cap * 4 : nullptr;
 
   // A full tile is fetched with whole-KB loads except the last one or two of each run, which are
   // trimmed to the tile's own bytes (tile_load_issued): nothing is fetched twice, nothing beyond
@@ -379,25 +378,18 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
     const unsigned char* kg = kslab + trow * pitch_k + 16 * lane;
     const unsigned char* vg = vslab + trow * pitch_v + 16 * lane;
     if constexpr (MX4) {
-      // whole blocks of the rows below len8 (<= cache_cap), each with its scale byte: block c of the
-      // tile is 16 c bytes into it, its scale byte 4 (c / KCH) + c % KCH bytes into the tile's scales
+      // whole blocks of the rows below len8 (<= cache_cap), and their scale bytes
       const int rows = min(kTileRows, len8 - base);
 #pragma unroll
-      for (int j = 0; j < NLD_K; ++j) {
-        const int c = lane + 64 * j, row = c / KCH;
-        if (c < rows * KCH) {
-          kst[j] = ld_stream(kg + 1024 * j);
-          kss[j] = ksslab[(trow + row) * 4 + (c - row * KCH)];
+      for (int rt = 0; rt < 2; ++rt)
+        if (16 * rt + l16 < rows) {
+          if (lg < KCH) kst[rt] = ld_stream(kslab + (trow + 16 * rt + l16) * pitch_k + 16 * lg);
+          kss[rt] = *reinterpret_cast<const uint32_t*>(ksslab + (trow + 16 * rt + l16) * 4);
         }
-      }
 #pragma unroll
-      for (int j = 0; j < NLD_V; ++j) {
-        const int c = lane + 64 * j, row = c / (NT / 2);
-        if (c < rows * (NT / 2)) {
-          vst[j] = ld_stream(vg + 1024 * j);
-          vss[j] = vsslab[(trow + row) * 4 + (c - row * (NT / 2))];
-        }
-      }
+      for (int j = 0; j < NLD_V; ++j)
+        if (lane + 64 * j < rows * MX4B) vst[j] = ld_stream(vg + 1024 * j);
+      if (lane < rows) vss = *reinterpret_cast<const uint32_t*>(vsslab + (trow + lane) * 4);
       return;
     }
     if (base + kTileRows <= len8) {
@@ -469,39 +461,43 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
   // LDS byte offsets of this lane's operands inside a tile
   int koff[2];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) koff[rt] = (16 * rt + l16) * lpk + 8 * EB * lg;
+  for (int rt = 0; rt < 2; ++rt) koff[rt] = (16 * rt + l16) * pitch_k + 8 * EB * lg;
   int vo_laid[8];   // V rows of the lane's eight contraction slots as laid out: j = 4 rt + r is row 16 rt + 4 lg + r
 #pragma unroll
-  for (int j = 0; j < 8; ++j) vo_laid[j] = (16 * (j >> 2) + 4 * lg + (j & 3)) * lpv + VLANE * l16;
-  // MX4: a staged block of 32 codes becomes 32 bf16 (64 bytes) of its row in LDS
-  // (rot: the block's 16-byte pieces are stored in the order 2, 3, 0, 1, each at its own place)
-  auto park_mx4 = [&](unsigned char* area, int off, const uint4& blk, uint32_t scale_byte, bool rot, bool may_rot) {
-    const float sc = bits_f32((scale_byte & 0xffu) << 23);       // 2^(e - 127), e >= 1
-    const uint32_t w[4] = {blk.x, blk.y, blk.z, blk.w};
-    const int off_lo = may_rot && rot ? off + 32 : off, off_hi = may_rot && rot ? off - 32 : off;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t src = may_rot && rot ? w[i ^ 2] : w[i];
-      uint4 o;
-      o.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(src, sc, 0));
-      o.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(src, sc, 1));
-      o.z = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(src, sc, 2));
-      o.w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(src, sc, 3));
-      *reinterpret_cast<uint4*>(area + (i < 2 ? off_lo : off_hi) + 16 * i) = o;
-    }
+  for (int j = 0; j < 8; ++j) vo_laid[j] = (16 * (j >> 2) + 4 * lg + (j & 3)) * pitch_v + VLANE * l16;
+  // MX4: eight codes -> eight bf16; scale byte `blk` of a row's four as the scale they are multiplied by
+  auto widen_mx4 = [&](uint32_t codes, float sc) -> uint4 {
+    return make_uint4(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 0)),
+                      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 1)),
+                      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 2)),
+                      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc, 3)));
   };
-
+  auto mx4_scale = [&](uint32_t bytes, int blk) -> float { return bits_f32(((bytes >> (8 * blk)) & 0xffu) << 23); };   // 2^(e - 127), e >= 1
 
   for (int base = first; base < r1; base += 4 * kTileRows) {
     // ---- park the staged tile in LDS, start fetching the next one
     wave_lds_sync();
+    uint32_t kw[2][4];            // MX4: word lg of block kk of the lane's two K rows
+    float ksc[2][KCH];            // and the block's scale
     if constexpr (MX4) {
 #pragma unroll
-      for (int j = 0; j < NLD_K; ++j)
-        if (lane + 64 * j < kTileRows * KCH) park_mx4(kt, k_lds[j], kst[j], kss[j], k_rot[j], mx4_rotate_upper_blocks(KCH));
-#pragma unroll
       for (int j = 0; j < NLD_V; ++j)
-        if (lane + 64 * j < kTileRows * (NT / 2)) park_mx4(vt, v_lds[j], vst[j], vss[j], v_rot[j], mx4_rotate_upper_blocks(NT / 2));
+        if (lane + 64 * j < kTileRows * MX4B) *reinterpret_cast<uint4*>(vt + 1024 * j + 16 * lane) = vst[j];
+      if (lane < kTileRows) *reinterpret_cast<uint32_t*>(kt + 4 * lane) = vss;
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        // lane group g holds words 0 .. 3 of block g; it wants word g of blocks 0 .. 3
+        const auto a0 = __builtin_amdgcn_permlane32_swap(kst[rt].x, kst[rt].z, false, false);
+        const auto a1 = __builtin_amdgcn_permlane32_swap(kst[rt].y, kst[rt].w, false, false);
+        const auto b0 = __builtin_amdgcn_permlane16_swap(a0[0], a1[0], false, false);
+        const auto b1 = __builtin_amdgcn_permlane16_swap(a0[1], a1[1], false, false);
+        kw[rt][0] = b0[0];
+        kw[rt][1] = b0[1];
+        kw[rt][2] = b1[0];
+        kw[rt][3] = b1[1];
+#pragma unroll
+        for (int kk = 0; kk < KCH; ++kk) ksc[rt][kk] = mx4_scale(kss[rt], kk);
+      }
     } else {
 #pragma unroll
       for (int j = 0; j < NLD_K; ++j) *reinterpret_cast<uint4*>(kt + 1024 * j + 16 * lane) = kst[j];
@@ -536,8 +532,12 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
           }
           w = widen_e4m3x8(c0, c1);
         } else {
-          const uint32_t* p = reinterpret_cast<const uint32_t*>(kt + koff[rt] + SK * kk);
-          w = make_uint4(p[0], p[1], p[2], p[3]);
+          if constexpr (MX4) {
+            w = widen_mx4(kw[rt][kk], ksc[rt][kk]);
+          } else {
+            const uint32_t* p = reinterpret_cast<const uint32_t*>(kt + koff[rt] + 64 * kk);
+            w = make_uint4(p[0], p[1], p[2], p[3]);
+          }
           if (kk == KCH - 1) {
             w.x &= kmask[0];
             w.y &= kmask[1];
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
     // are branches around a few instructions, not copies of the arithmetic.
     const int nv = min(kTileRows, r1 - base);       // valid rows in this tile, >= 1
     const int skip_rel = t_skip - base;             // the one row to leave out, if it is in this tile
-    const bool plain = nv == kTileRows && static_cast<unsigned>(skip_rel) >= static_cast<unsigned>(kTileRows);
+    const bool plain = nv == kTileRows && (MX4 || static_cast<unsigned>(skip_rel) >= static_cast<unsigned>(kTileRows));
     float x[2][4];
     float tmax = -INFINITY;
 #pragma unroll
@@ -563,14 +563,14 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float s = sc[rt][r] * scale_log2e;
-        x[rt][r] = (Q8 || ((16 * rt + 4 * lg + r) < nv && (16 * rt + 4 * lg + r) != skip_rel)) ? s : -INFINITY;
+        x[rt][r] = (Q8 || MX4 || ((16 * rt + 4 * lg + r) < nv && (16 * rt + 4 * lg + r) != skip_rel)) ? s : -INFINITY;
       }
-    if (Q8 && !plain) {
+    if ((Q8 || MX4) && !plain) {
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          x[rt][r] = ((16 * rt + 4 * lg + r) < nv && (16 * rt + 4 * lg + r) != skip_rel) ? x[rt][r] : -INFINITY;
+          x[rt][r] = ((16 * rt + 4 * lg + r) < nv && (MX4 || (16 * rt + 4 * lg + r) != skip_rel)) ? x[rt][r] : -INFINITY;
     }
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
@@ -632,20 +632,60 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
         for (int j = 0; j < 8; ++j) {
           int row = min(16 * (j >> 2) + 4 * lg + (j & 3), nv - 1);
           row = row == skip_rel ? (skip_rel == 0 ? min(1, nv - 1) : skip_rel - 1) : row;
-          vo_laid[j] = row * lpv + VLANE * l16;
+          vo_laid[j] = row * pitch_v + VLANE * l16;
         }
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) vo[j] = vo_laid[j];
-    } else {
+    } else if constexpr (!MX4) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         int row = min(16 * (j >> 2) + 4 * lg + (j & 3), nv - 1);
         row = row == skip_rel ? (skip_rel == 0 ? min(1, nv - 1) : skip_rel - 1) : row;
-        vo[j] = plain ? vo_laid[j] : row * lpv + VLANE * l16;
+        vo[j] = plain ? vo_laid[j] : row * pitch_v + VLANE * l16;
       }
     }
-    if constexpr (Q8) {
+    if constexpr (MX4) {
+      // the lane's NT channels of row j, lowest channel in the low nibble, and the scale byte of their
+      // block.  In a whole tile all sixteen reads are constant offsets from two addresses; a row at or
+      // beyond the valid ones reads the last valid row.
+      uint32_t w[8], e[8];
+      auto read_v = [&](int row, int off, int j) {
+        const unsigned char* wp = vt + row * pitch_v + off * (16 * MX4B) + VLANE * l16;
+        w[j] = NT == 8 ? *reinterpret_cast<const uint32_t*>(wp) : *reinterpret_cast<const uint16_t*>(wp);
+        e[j] = kt[4 * (row + off) + l16 / (32 / NT)];
+      };
+      if (plain) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) read_v(4 * lg, 16 * (j >> 2) + (j & 3), j);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) read_v(min(16 * (j >> 2) + 4 * lg + (j & 3), nv - 1), 0, j);
+      }
+      float vsc[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) vsc[j] = bits_f32(e[j] << 23);
+      static_for_pairs<NT / 2>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        uint32_t x[8];                 // channels 2 p (low half) and 2 p + 1 of row j
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[j], vsc[j], p));
+        uint4 be, bo;
+        be.x = __builtin_amdgcn_perm(x[1], x[0], 0x05040100u);
+        be.y = __builtin_amdgcn_perm(x[3], x[2], 0x05040100u);
+        be.z = __builtin_amdgcn_perm(x[5], x[4], 0x05040100u);
+        be.w = __builtin_amdgcn_perm(x[7], x[6], 0x05040100u);
+        bo.x = __builtin_amdgcn_perm(x[1], x[0], 0x07060302u);
+        bo.y = __builtin_amdgcn_perm(x[3], x[2], 0x07060302u);
+        bo.z = __builtin_amdgcn_perm(x[5], x[4], 0x07060302u);
+        bo.w = __builtin_amdgcn_perm(x[7], x[6], 0x07060302u);
+        const bf16x8 vbe = __builtin_bit_cast(bf16x8, be), vbo = __builtin_bit_cast(bf16x8, bo);
+        acc[2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_hi, vbe, acc[2 * p], 0, 0, 0);
+        acc[2 * p + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_hi, vbo, acc[2 * p + 1], 0, 0, 0);
+        acc[2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_lo, vbe, acc[2 * p], 0, 0, 0);
+        acc[2 * p + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_lo, vbo, acc[2 * p + 1], 0, 0, 0);
+      });
+    } else if constexpr (Q8) {
 #pragma unroll
       for (int nq = 0; nq < NT / 4; ++nq) {
         uint32_t w[8];                 // four adjacent channels of row j, lowest channel in the low byte
@@ -678,7 +718,7 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
         uint4 be, bo;   // even / odd channel of the pair, rows packed two by two
         uint32_t w[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) w[j] = *reinterpret_cast<const uint32_t*>(vt + vo[j] + SV * np);
+        for (int j = 0; j < 8; ++j) w[j] = *reinterpret_cast<const uint32_t*>(vt + vo[j] + 64 * np);
         be.x = __builtin_amdgcn_perm(w[1], w[0], 0x05040100u);
         be.y = __builtin_amdgcn_perm(w[3], w[2], 0x05040100u);
         be.z = __builtin_amdgcn_perm(w[5], w[4], 0x05040100u);
@@ -707,7 +747,7 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
     }
     if (Q8 && !plain) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) vo_laid[j] = (16 * (j >> 2) + 4 * lg + (j & 3)) * lpv + VLANE * l16;
+      for (int j = 0; j < 8; ++j) vo_laid[j] = (16 * (j >> 2) + 4 * lg + (j & 3)) * pitch_v + VLANE * l16;
     }
   }
 
@@ -726,7 +766,7 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
     if (g < (cols > kMaxGroup ? kMaxCols : kMaxGroup)) {   // the hand-over area holds 8 columns, or all 16 when more are in use
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
-        wm[32 + g * (16 * NT) + (Q8 ? 64 * (nt >> 2) + 4 * l16 + (nt & 3) : VPAIR ? 32 * (nt >> 1) + 2 * l16 + (nt & 1) : 16 * nt + l16)] = acc[nt][reg];
+        wm[32 + g * (16 * NT) + (MX4 ? NT * l16 + nt : Q8 ? 64 * (nt >> 2) + 4 * l16 + (nt & 3) : VPAIR ? 32 * (nt >> 1) + 2 * l16 + (nt & 1) : 16 * nt + l16)] = acc[nt][reg];
     }
   }
   __syncthreads();
@@ -763,17 +803,17 @@ __global__ __launch_bounds__(256, (KCH <= 3 ? 3 : 2)) void decode_mfma_kernel(De
   }
 }
 
-template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL = false, bool MX4 = false>
+template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL = false, int MX4B = 0>
 hipError_t launch_inst2(const DecodeArgs& a, hipStream_t stream) {
   // scanning workgroups, then (decode step: n_slots = n_split + 1) one per (b, h) for the new token
   dim3 grid(static_cast<unsigned>(a.n_slots) * a.n_kv * a.batch), block(256);
   const size_t lds = 4 * static_cast<size_t>(a.lds_wave_bytes);
   if (lds > 64 * 1024) {
     // more than the default dynamic-LDS limit: raise it once per kernel (gfx950 has 160 KB per CU)
-    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(&decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4>), static_cast<int>(lds));
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(&decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B>), static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4>), grid, block, lds, stream, a);
+  hipLaunchKernelGGL((decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B>), grid, block, lds, stream, a);
   return hipGetLastError();
 }
 

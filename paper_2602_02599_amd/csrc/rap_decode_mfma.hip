@@ -44,10 +44,10 @@ hipError_t launch_k(const DecodeArgs& a, hipStream_t stream) {
 
 // LDS bytes one wavefront needs: its K tile, its V tile and slack for the fragment reads that run
 // past the last row, or the hand-over area of the final fold, whichever is larger.
-// (4-bit caches: the tile is widened on its way into LDS, to rows of 32 bf16 per block plus 16 bytes.)
+// (4-bit caches: the V tile's scale bytes and codes; a lane beyond the row's channels reads past it.)
 int mfma_lds_wave_bytes(int d_k, int d_v, bool q8, int cols, bool mx4) {
-  const int nt = mx4 ? 2 * mx_blocks(d_v) : decode_v_tiles(d_v, q8);
-  const int tiles = mx4 ? 32 * (mx4_row_pitch(mx_blocks(d_k)) + mx4_row_pitch(nt / 2)) + 128
+  const int nt = mx4 ? mx4_lane_channels(mx_blocks(d_v)) : decode_v_tiles(d_v, q8);
+  const int tiles = mx4 ? 32 * (4 + 16 * mx_blocks(d_v)) + 128
                         : 1024 * (k_tile_loads((d_k + 31) / 32, q8) + v_tile_loads(nt, q8)) + 128;
   const int fold = (32 + (cols > kMaxGroup ? kMaxCols : kMaxGroup) * 16 * nt) * 4;
   const int need = tiles > fold ? tiles : fold;

@@ -9,10 +9,10 @@ namespace {
 template <int KCH>
 hipError_t launch_v(const DecodeArgs& a, hipStream_t stream) {
   switch (mx_blocks(a.d_v)) {
-    case 1: return launch_inst2<KCH, 2, true, false, false, false, true>(a, stream);
-    case 2: return launch_inst2<KCH, 4, true, false, false, false, true>(a, stream);
-    case 3: return launch_inst2<KCH, 6, true, false, false, false, true>(a, stream);
-    case 4: return launch_inst2<KCH, 8, true, false, false, false, true>(a, stream);
+    case 1: return launch_inst2<KCH, 4, false, false, false, false, 1>(a, stream);
+    case 2: return launch_inst2<KCH, 4, false, false, false, false, 2>(a, stream);
+    case 3: return launch_inst2<KCH, 8, false, false, false, false, 3>(a, stream);
+    case 4: return launch_inst2<KCH, 8, false, false, false, false, 4>(a, stream);
     default: return hipErrorInvalidValue;
   }
 }
