@@ -97,9 +97,10 @@ int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap:
 //    whole); and with a slab for every compute unit up to 1024 rows stay whole (32 x 1024: 23.4 us
 //    in two ranges, 22.1 in one).
 //  * Beyond that the chip wants at least two workgroups per compute unit, of 512 rows or more.
-//    Where the slabs do not divide that number, more and shorter ranges that do come out even are
-//    better: 24 x 8192 (192 slabs) 102 us with 2 ranges per slab, 95 with 4; 40 x 4096 (320 slabs) 94
-//    us with one, 82 with 4.
+//    Where the slabs leave more than a fifth of that number over, more and shorter ranges that come
+//    out even are better: 24 x 8192 (192 slabs) 102 us with 2 ranges per slab, 95 with 4; 40 x 4096
+//    (320 slabs) 94 us with one, 82 with 4.  With less left over they are not: 18 x 8192 (144 slabs)
+//    72 us with 3 ranges, 75 with 7; 14 x 9738 at 16 query rows per slab 74 us with 4, 78 with 9.
 //  * Long ranges save a little on equal lengths and cost a lot on ragged ones, whose workgroups are
 //    then few and unequal: an eighth of max_seq_len, no less than 2048 and no more than 4096 rows.
 //    64 x 16384: 451 / 456 / 464 us in 8192 / 4096 / 2048 rows, ragged 327 / 274 / 265; 32 x 16384
@@ -145,20 +146,20 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
   } else if (slabs >= cus && max_seq_len <= 1024) {
     r = round_to_quantum(max_seq_len);
   } else {
-    int64_t k = k0;
-    double best = 0.0;
-    for (int64_t c = k0; c <= 4 * k0 && (c == k0 || max_seq_len >= 1024 * c); ++c) {
+    // how evenly c ranges per slab fill the compute units, less a little for every further range
+    auto evenness = [&](int64_t c) {
       const int64_t n = slabs * c, rounds = (n + cus - 1) / cus;
-      const double even = static_cast<double>(n) / static_cast<double>(rounds * cus) - 0.03 * static_cast<double>(c - k0) / static_cast<double>(k0);
-      if (even > best + 0.02) {
-        best = even;
-        k = c;
-      }
+      return static_cast<double>(n) / static_cast<double>(rounds * cus) - 0.03 * static_cast<double>(c - k0) / static_cast<double>(k0);
+    };
+    int64_t k = k0;
+    if (evenness(k0) < 0.78) {
+      for (int64_t c = k0 + 1; c <= 4 * k0 && max_seq_len >= 1024 * c; ++c)
+        if (evenness(c) > evenness(k) + 0.02) k = c;
     }
     const int64_t eighth = round_to_quantum(max_seq_len / 8);
     const int64_t most = eighth < 2048 ? 2048 : (eighth > 4096 ? 4096 : eighth);
     r = round_to_quantum((max_seq_len + k - 1) / k);
-    r = r < 512 ? 512 : (r > most ? most : r);
+    r = r < 512 ? 512 : (r > most + most / 2 ? most : r);      // not for the sake of a little: 112 slabs of 9738 rows 73 us in 2560, 81 in 2048
     if (single_round && s->batch <= 16) r = halves;
   }
   if (ranges_of(r) > p->n_split && partial_bytes(s, ranges_of(r), 1) > RAP_STATIC_SCRATCH_BYTES) return RAP_OK;   // plain
