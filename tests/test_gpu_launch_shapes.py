@@ -1,0 +1,159 @@
+"""Kernels and dispatch rules at the sizes where they can go wrong: every instantiation width of the
+prefill kernel with the cache ending inside its last row, range counts at the edges of the combining
+kernel's groups, block counts of 4-bit rows, the ranges the split plan picks, and workspaces of the
+size the plain range rule asks for.  Against the float64 oracle; bars as in tests/helpers.py."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import rap_oracle as O
+import rap_inputs as I
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _say(msg):
+    print("[launch shapes] " + msg, flush=True)
+
+
+def _caches(rap, rng, B, Hkv, cap, P, dv, lens, fp8, page_rows):
+    k = rng.standard_normal((B, Hkv, cap, 2 * P))
+    v = rng.standard_normal((B, Hkv, cap, dv))
+    ks = (rng.uniform(4.0, 6.0, Hkv) / 448.0).astype(np.float32) if fp8 else None
+    vs = (rng.uniform(4.0, 6.0, Hkv) / 448.0).astype(np.float32) if fp8 else None
+    return H.encode_cache(rap, rng, k, v, lens, fp8, page_rows, ks, vs) + (ks, vs)
+
+
+# d_k in every quarter (one to four steps of 32), d_v in every sixteenth and odd ones; pages of 64
+# rows, and dense caches that end with the last row of the last sequence, so that the 16-byte pieces
+# of that row must not be read whole
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("P,dv,Hq,Hkv,n_new,page_rows", [
+    (1, 1, 2, 2, 65, 0), (9, 16, 8, 8, 33, 0), (16, 17, 4, 4, 70, 64), (17, 32, 16, 8, 64, 0), (24, 45, 3, 1, 129, 0),
+    (32, 48, 8, 8, 47, 64), (33, 64, 10, 2, 52, 0), (35, 66, 4, 4, 96, 0), (45, 79, 8, 2, 31, 64), (48, 80, 4, 2, 64, 0),
+    (45, 96, 16, 1, 40, 0), (49, 97, 4, 4, 61, 0), (51, 102, 8, 8, 35, 64), (58, 112, 6, 2, 63, 0), (61, 113, 4, 4, 90, 0),
+    (64, 127, 8, 8, 20, 64), (64, 128, 8, 4, 65, 0)])
+def test_prefill_widths(rap, fp8, P, dv, Hq, Hkv, n_new, page_rows):
+    """Whole and cut into key ranges, over a cache that holds exactly the rows of the longest sequence."""
+    _say("prefill P=%d dv=%d heads %d/%d n_new=%d fp8=%s pages=%d" % (P, dv, Hq, Hkv, n_new, fp8, page_rows))
+    cap = 576
+    lens = np.asarray([cap - 41, cap], dtype=np.int64)         # the last sequence fills its slab, the last of the cache
+    rng = np.random.Generator(np.random.PCG64(7000 + P + dv))
+    kd, vd, kdev, vdev, ksd, vsd, pg, ks, vs = _caches(rap, rng, 2, Hkv, cap, P, dv, lens, fp8, page_rows)
+    qb = O.f64_to_bf16_bits_rne(rng.standard_normal((2, n_new, Hq, 2 * P)))
+    q, sl = I.from_bits(qb, DEV), torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    scale = 1.0 / math.sqrt(2 * P)
+    shp = rap.shape(2, Hq, Hkv, 128, P, dv, cap, 5e5)
+    guard, out = H.guarded_out((2, n_new, Hq, dv), DEV)
+    rap.rap_prefill_attn_ex(shp, kdev, vdev, ksd, vsd, pg, n_new, q, sl, cap, out, scale)
+    torch.cuda.synchronize()
+    guard.check("out of rap_prefill_attn_ex")
+    ref = O.prefill_attn_q8_ref(qb, kd, vd, ks, vs, lens, scale) if fp8 else O.prefill_attn_ref(qb, kd, vd, lens, scale)
+    H.assert_attn_close(out.cpu().numpy(), ref, "prefill")
+    need = rap.rap_prefill_attn_split_workspace_bytes(shp, n_new, cap)
+    if need:
+        gw = H.Guarded(need, DEV)
+        cut = torch.full_like(out, float("nan"))
+        rap.rap_prefill_attn_split(shp, kdev, vdev, ksd, vsd, pg, n_new, q, sl, cap, cut, scale, gw.bytes)
+        torch.cuda.synchronize()
+        gw.check("workspace of rap_prefill_attn_split")
+        H.assert_attn_close(cut.cpu().numpy(), ref, "prefill in key ranges")
+
+
+# eight slots per thread and round; one, two, four or eight groups of threads
+@pytest.mark.parametrize("n_tok", [1, 2, 5])
+@pytest.mark.parametrize("n_split", [7, 8, 9, 16, 17, 32, 33, 64, 65, 130])
+def test_range_counts(rap, n_split, n_tok):
+    """Ranges of 128 rows up to more than the combining kernel's groups read at once: full sequences,
+    one that leaves the last ranges empty, an empty one (NaN in every slot of the workspace)."""
+    P, dv, Hq, Hkv = 10, 21, 3, 1
+    cap = 128 * n_split
+    lens = np.asarray([cap, cap - 128 * (n_split // 3) - 5, 0, cap - 1], dtype=np.int64)
+    _say("ranges %d tokens %d" % (n_split, n_tok))
+    rng = np.random.Generator(np.random.PCG64(900 + n_split))
+    kd, vd, kdev, vdev, _, _, _, _, _ = _caches(rap, rng, 4, Hkv, cap, P, dv, lens, False, 0)
+    qb = O.f64_to_bf16_bits_rne(rng.standard_normal((4, n_tok, Hq, 2 * P)))
+    q, sl = I.from_bits(qb, DEV), torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    shp, scale = rap.shape(4, Hq, Hkv, 128, P, dv, cap, 5e5), 0.25
+    tun = rap.tuning(rows_per_split=128)
+    gw, ws = H.guarded_workspace(rap, shp, cap, tun, n_tok=n_tok)
+    go, out = H.guarded_out((4, n_tok, Hq, dv), DEV)
+    rap.rap_decode_attn_multi(shp, kdev, vdev, None, None, None, n_tok, q, sl, cap, out, scale, ws, tun)
+    torch.cuda.synchronize()
+    gw.check("workspace")
+    go.check("out")
+    H.assert_attn_close(out.cpu().numpy(), O.prefill_attn_ref(qb, kd, vd, lens, scale), "%d ranges" % n_split)
+
+
+@pytest.mark.parametrize("P,dv", [(16, 65), (5, 128), (17, 32), (30, 96), (32, 97), (40, 31), (48, 64), (45, 128), (49, 1), (64, 33), (56, 95)])
+def test_mx4_block_counts(rap, P, dv):
+    """4-bit rows with every pairing of one to four K and V blocks, sequence lengths at the edges of the
+    32-row tile: bit for bit the bf16 call on the dequantised cache, and the oracle."""
+    _say("mx4 P=%d dv=%d" % (P, dv))
+    lens = np.asarray([1, 31, 32, 33, 128, 161], dtype=np.int64)
+    B, Hkv, Hq, cap = len(lens), 2, 6, 168
+    rng = np.random.Generator(np.random.PCG64(5 + P + dv))
+    kc, ks = O.mx4_quantize_rows(rng.standard_normal((B, Hkv, cap, 2 * P)))
+    vc, vs = O.mx4_quantize_rows(rng.standard_normal((B, Hkv, cap, dv)))
+    for b in range(B):
+        for x in (kc, ks, vc, vs):
+            x[b, :, int(lens[b]):] = 0xFF
+    qb = O.f64_to_bf16_bits_rne(rng.standard_normal((B, Hq, 2 * P)))
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).to(DEV) for x in (kc, ks, vc, vs)]
+    q, sl = I.from_bits(qb, DEV), torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    shp, scale = rap.shape(B, Hq, Hkv, 128, P, dv, cap, 5e5), 1.0 / math.sqrt(2 * P)
+    ref = O.attn_mx4_ref(qb, kc, ks, vc, vs, lens, scale, 2 * P, dv)
+    kb = I.from_bits(O.f64_to_bf16_bits_rne(np.nan_to_num(O.mx4_dequantize_rows(kc, ks, 2 * P))), DEV)
+    vb = I.from_bits(O.f64_to_bf16_bits_rne(np.nan_to_num(O.mx4_dequantize_rows(vc, vs, dv))), DEV)
+    for rps in (0, 128):
+        tun = rap.tuning(rows_per_split=rps)
+        gw, ws = H.guarded_workspace(rap, shp, cap, tun)
+        go, out = H.guarded_out((B, Hq, dv), DEV)
+        rap.rap_decode_attn_mx4(shp, q, *dev, sl, cap, out, scale, ws, tun)
+        torch.cuda.synchronize()
+        gw.check("workspace")
+        go.check("out")
+        H.assert_attn_close(out.cpu().numpy(), ref, "mx4")
+        b16 = torch.empty_like(out)
+        rap.rap_decode_attn(shp, q, kb, vb, sl, cap, b16, scale, ws, tun)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int32), b16.view(torch.int32)), "differs from the bf16 call on the dequantised cache"
+
+
+def _slots_bytes(B, Hq, dv, n_split):
+    """Workspace of n_split ranges as rap_decode_attn lays it out: accumulators, (reference, sum) pairs."""
+    up = lambda x: (x + 255) // 256 * 256
+    return up(B * Hq * (n_split + 1) * dv * 4) + up(B * Hq * (n_split + 1) * 8) + 256
+
+
+@pytest.mark.parametrize("B,ctx,plain", [(1, 512, 1), (1, 2048, 4), (2, 384, 1), (3, 5000, 10), (1, 130, 1), (24, 1100, 2)])
+def test_plan_and_smaller_workspace(rap, B, ctx, plain):
+    """The ranges of the automatic plan at few sequences and ragged lengths, and the same call with a
+    workspace that only holds the plain rule's ranges (none where that is a single range)."""
+    P, dv, Hq, Hkv = 20, 40, 8, 8
+    cap = (ctx + 7) // 8 * 8
+    _say("plan B=%d ctx=%d" % (B, ctx))
+    rng = np.random.Generator(np.random.PCG64(40 + ctx))
+    lens = rng.integers(1, ctx + 1, B).astype(np.int64)
+    lens[0] = ctx
+    kd, vd, kdev, vdev, _, _, _, _, _ = _caches(rap, rng, B, Hkv, cap, P, dv, lens, False, 0)
+    qb = O.f64_to_bf16_bits_rne(rng.standard_normal((B, Hq, 2 * P)))
+    q, sl = I.from_bits(qb, DEV), torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    shp, scale = rap.shape(B, Hq, Hkv, 128, P, dv, cap, 5e5), 0.2
+    ref = O.attn_ref(qb, kd, vd, lens, scale)
+    gw, ws = H.guarded_workspace(rap, shp, ctx)
+    small = H.Guarded(_slots_bytes(B, Hq, dv, plain), DEV) if plain > 1 else None
+    for which, g, w in (("planned", gw, ws), ("plain", small, small.bytes if small else None)):
+        go, out = H.guarded_out((B, Hq, dv), DEV)
+        rap.rap_decode_attn(shp, q, kdev, vdev, sl, ctx, out, scale, w)
+        torch.cuda.synchronize()
+        go.check("out")
+        if g is not None:
+            g.check("workspace")
+        H.assert_attn_close(out.cpu().numpy(), ref, which)
+    if plain > 1:                                              # one byte less is refused
+        assert rap.rap_decode_attn(shp, q, kdev, vdev, sl, ctx, out, scale, small.bytes[:-1], check=False) == 5
