@@ -199,9 +199,11 @@ namespace {
 template <int MT>
 void launch_groups(const DecodeArgs& a, hipStream_t stream) {
   dim3 grid(static_cast<unsigned>(a.batch) * a.n_tok * a.n_q);
-  if (a.n_split <= kMergeSlots) hipLaunchKernelGGL((merge_kernel<MT, 1>), grid, dim3(128), 0, stream, a);
-  else if (a.n_split <= 2 * kMergeSlots) hipLaunchKernelGGL((merge_kernel<MT, 2>), grid, dim3(256), 0, stream, a);
-  else if (a.n_split <= 4 * kMergeSlots) hipLaunchKernelGGL((merge_kernel<MT, 4>), grid, dim3(512), 0, stream, a);
+  // a launch holds fewer than 2^32 threads: from 4 M query rows on, fewer groups walk the ranges in turn
+  auto fits = [&](unsigned threads) { return static_cast<unsigned long long>(grid.x) * threads < (1ull << 32); };
+  if (a.n_split <= kMergeSlots || !fits(256)) hipLaunchKernelGGL((merge_kernel<MT, 1>), grid, dim3(128), 0, stream, a);
+  else if (a.n_split <= 2 * kMergeSlots || !fits(512)) hipLaunchKernelGGL((merge_kernel<MT, 2>), grid, dim3(256), 0, stream, a);
+  else if (a.n_split <= 4 * kMergeSlots || !fits(1024)) hipLaunchKernelGGL((merge_kernel<MT, 4>), grid, dim3(512), 0, stream, a);
   else hipLaunchKernelGGL((merge_kernel<MT, 8>), grid, dim3(1024), 0, stream, a);
 }
 
