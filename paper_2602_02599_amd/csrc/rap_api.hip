@@ -6,6 +6,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "../../include/rap.h"
 #include "rap_device.h"
 
@@ -111,8 +113,8 @@ int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap:
 //  * The plan never takes more partials than the static scratch array holds where the plain rule
 //    (two workgroups per compute unit, ranges of 512 to 4096 rows, up to 8192 where that avoids a
 //    partly filled second round of workgroups) would not, so that what a caller with that much
-//    scratch may ask for does not depend on any of the above.  A caller who hands in less than the
-//    plan wants, but enough for the plain rule, gets the plain rule (`plain`).
+//    scratch may ask for does not depend on any of the above.  Every call has to bring a workspace
+//    for the plain rule (`plain`) and gets its ranges if the plan's do not fit in it.
 rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuning_t* t, Plan* p, bool plain = false) {
   const int rps = t ? t->rows_per_split : 0;
   if (rps < 0 || (rps % rap::kSplitQuantum) != 0) return RAP_ERR_SHAPE;
@@ -326,19 +328,18 @@ rap_status_t decode_impl(const DecodeRequest& r) {
   if (multi && (p.kernel != 2 || step || r.q_pos ||
                 static_cast<int64_t>(r.n_tok) * (shape->n_q_heads / shape->n_kv_heads) > 16))
     return RAP_ERR_UNSUPPORTED;
-  // (a workspace too small for the plan, but large enough for the plain rule's, gets the latter)
+  // What a call must hand in is what the plain rule needs, so that whether it is accepted does not
+  // hang on the plan; a workspace that holds no more than that gets the plain rule's ranges.
+  Plan base;
+  st = make_plan(shape, r.max_seq_len, r.tuning, &base, true);
+  if (st != RAP_OK) return st;
+  auto combines = [&](const Plan& q) { return q.n_split > 1 || fused_step || multi; };
   auto holds = [&](const Plan& q) {
-    return !(q.n_split > 1 || fused_step || multi) || (r.workspace && r.workspace_bytes >= workspace_need(shape, q, r.n_tok));
+    return r.workspace && !misaligned(r.workspace, 256) && r.workspace_bytes >= workspace_need(shape, q, r.n_tok);
   };
-  if (!holds(p)) {
-    st = make_plan(shape, r.max_seq_len, r.tuning, &p, true);
-    if (st != RAP_OK) return st;
-    if (!holds(p)) return RAP_ERR_WORKSPACE;
-  }
-  const bool combine = p.n_split > 1 || fused_step || multi;
-  if (combine) {
-    if (misaligned(r.workspace, 256)) return RAP_ERR_WORKSPACE;
-  }
+  if (combines(base) && !holds(base)) return RAP_ERR_WORKSPACE;
+  if (combines(p) && !holds(p)) p = base;
+  const bool combine = combines(p);
   if (p.n_split > 65535 || (static_cast<int64_t>(p.n_split) + 1) * shape->n_kv_heads * shape->batch > kInt32Max)
     return RAP_ERR_UNSUPPORTED;
   // combinations no kernel is built for
@@ -701,7 +702,11 @@ size_t rap_decode_attn_workspace_bytes(const rap_shape_t* shape, int64_t max_seq
   if (check_shape(shape) != RAP_OK || max_seq_len < 1 || max_seq_len > shape->cache_cap) return 0;
   Plan p;
   if (make_plan(shape, max_seq_len, tuning, &p) != RAP_OK) return 0;
-  return workspace_need(shape, p);
+  // no less than the plain rule's, which every call has to bring: an array sized for the largest
+  // batch then also serves smaller ones whose plan has more ranges (32 x 1024 rows: whole; 31: two)
+  Plan base;
+  make_plan(shape, max_seq_len, tuning, &base, true);
+  return std::max(workspace_need(shape, p), workspace_need(shape, base));
 }
 
 rap_status_t rap_decode_attn(const rap_shape_t* shape, const void* q, const void* k_cache, const void* v_cache,
