@@ -530,8 +530,10 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
         mul = 1.f;
         dst = a.part_acc + slot * dv;
       } else {
-        live = shift + i >= 0 && l > 0.f;
-        mul = live ? 1.f / l : 0.f;
+        // a token in front of its sequence is zeros; for one that exists a sum that is not a number
+        // has made the accumulators so too, and they are multiplied, not replaced, so that it shows
+        live = shift + i >= 0;
+        mul = l > 0.f ? 1.f / l : 0.f;
         dst = a.out + row * dv;
       }
       if constexpr (Q8) mul *= a.v_scale[h];       // codes -> values

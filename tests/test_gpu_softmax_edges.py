@@ -352,3 +352,68 @@ def test_prefill_families(rap, pattern, name, fp8, page_rows, P, dv, Hkv, G, n_n
     if gw is not None:
         gw.check(name)
     _report(name, out.cpu().numpy(), ref)
+
+
+# widths with a spare channel for the row sums (odd V rows, codes, even rows) and without one
+POISON_CASES = [("bf16 d90/90", False, 0, 45, 90, 4), ("bf16 d64/64", False, 64, 32, 64, 4), ("bf16 d116/115", False, 0, 58, 115, 2),
+                ("bf16 d90/96", False, 0, 45, 96, 3), ("fp8 d90/90", True, 0, 45, 90, 4), ("fp8 paged d64/128", True, 64, 32, 128, 2)]
+
+
+@pytest.mark.parametrize("poison", ["query", "key", "overflow"])
+@pytest.mark.parametrize("name,fp8,page_rows,P,dv,G", POISON_CASES, ids=[c[0] for c in POISON_CASES])
+def test_prefill_shows_what_is_not_a_number(rap, poison, name, fp8, page_rows, P, dv, G):
+    """A NaN in one query row, a NaN in one attended K row, or one score that overflows: exactly the
+    output rows that contain it are NaN, in every channel.  The others are bit-equal to a run without
+    it (overflow: within the bar, because that score moves the references beside it), and a token in
+    front of the start of its sequence stays zeros."""
+    _say("not a number in prefill: %s, %s" % (name, poison))
+    Hkv, n_new, cap = 2, 150, 192
+    lens = np.asarray([cap - 5, 40], dtype=np.int64)              # the second sequence starts inside the chunk
+    rng = np.random.Generator(np.random.PCG64(811 + P + dv))
+    scale = 1.0 / math.sqrt(2 * P)
+    k = rng.standard_normal((2, Hkv, cap, 2 * P))
+    k[..., 0] = np.where(np.arange(cap) == 61, 256.0 if fp8 else 2.0 ** 70, 0.0)
+    ks = vs = np.full(Hkv, 1.0, dtype=np.float32) if fp8 else None
+    v = rng.standard_normal((2, Hkv, cap, dv))
+    kd, vd, kdev, vdev, ksd, vsd, pg = H.encode_cache(rap, rng, k, v, lens, fp8, page_rows, ks, vs)
+    qv = rng.standard_normal((2, n_new, G * Hkv, 2 * P))
+    qv[..., 0] = 0.0
+    shp = rap.shape(2, G * Hkv, Hkv, 128, P, dv, cap, 5e5)
+    sl = torch.from_numpy(lens.astype(np.int32)).to(DEV)
+
+    def run(q, kc):
+        go, out = H.guarded_out((2, n_new, G * Hkv, dv), DEV)
+        rap.rap_prefill_attn_ex(shp, kc, vdev, ksd, vsd, pg, n_new, q, sl, cap, out, scale)
+        torch.cuda.synchronize()
+        go.check(name)
+        return out.cpu().numpy().copy()
+
+    qb = O.f64_to_bf16_bits_rne(qv)
+    clean = run(I.from_bits(qb, DEV), kdev)
+    ref = O.prefill_attn_q8_ref(qb, kd, vd, ks, vs, lens, scale) if fp8 else O.prefill_attn_ref(qb, kd, vd, lens, scale)
+    H.assert_attn_close(clean, ref, name)
+    want = np.zeros(clean.shape[:3], dtype=bool)
+    shift = int(lens[0]) - n_new
+    if poison == "key":                                           # row 61 of the first sequence, KV head 1
+        bad = kdev.clone()
+        if page_rows:
+            bad[int(pg._keep_alive[0, 61 // page_rows]), 1, 61 % page_rows, 3] = 0x7F if fp8 else float("nan")
+        else:
+            bad[0, 1, 61, 3] = 0x7F if fp8 else float("nan")
+        want[0, max(0, 61 - shift):, G:] = True
+        got = run(I.from_bits(qb, DEV), bad)
+    else:                                                         # token 77, query head G of the first sequence
+        qx = qb.copy()
+        if poison == "query":
+            qx[0, 77, G, 5] = 0x7FC0
+        else:
+            qx[0, 77, G, 0] = 0x7F00                              # 2^127, times 256 or 2^70
+        want[0, 77, G] = True
+        got = run(I.from_bits(qx, DEV), kdev)
+    nan = np.isnan(got)
+    assert np.array_equal(nan.all(-1), want) and np.array_equal(nan.any(-1), want), "NaN in %d rows, expected in %d" % (nan.any(-1).sum(), want.sum())
+    if poison == "overflow":
+        H.assert_attn_close(got[~want], ref[~want], name)
+    else:
+        assert np.array_equal(got[~want].view(np.uint32), clean[~want].view(np.uint32))
+    assert not got[1, :n_new - 40].any()                          # in front of the start of the second sequence
