@@ -75,14 +75,12 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4_t;
 struct __attribute__((packed, aligned(1))) Bytes16 { uint32_t w[4]; };
 typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_dw;
 
-// maximum of three floats in one instruction.  Written as the instruction because the compiler,
-// asked for nested two-operand maxima of matrix-instruction results, first passes every operand
-// through a max(x, x) of its own to quiet a possible signalling NaN: eleven instructions where
-// three do (the instruction quiets NaNs by itself).
+// Maximum of three floats, NaNs left out: one instruction (v_max3_f32).  Not written as the
+// instruction, because the compiler puts no wait between a matrix instruction and inline code that
+// reads its result, which takes eight wait states; and not as fmaxf, which is asked to quiet a
+// signalling NaN and passes every operand through a max(x, x) of its own first.
 __device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
+  return __builtin_elementwise_maximumnum(__builtin_elementwise_maximumnum(a, b), c);
 }
 
 // 16 bytes per lane from base + off (any dword-aligned address) straight into LDS: lane i's land at

@@ -1,0 +1,106 @@
+"""CPU tests of the device code itself: the built library is disassembled and the waits that the
+instruction set asks of the program, not of the hardware, are looked for on every path.
+
+The compiler puts them in between its own instructions, but not around inline code: it sees neither
+what that reads nor what it loads.  No GPU is involved."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2602_02599_amd import build as B
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+# wait states between a matrix instruction of four passes and a vector or memory instruction that
+# reads its result
+MFMA_WAIT = {"v_mfma_f32_16x16x32_bf16": 8}
+LINE = re.compile(r"^\t(\S+)\s*(.*?)\s*// ([0-9A-F]+): (?:[0-9A-F]{8} ?)+(?:<(\S+)\+0x([0-9a-f]+)>)?")
+REG = re.compile(r"\b([vas])(?:(\d+)|\[(\d+):(\d+)\])")
+
+
+def _regs(text):
+    out = set()
+    for kind, one, lo, hi in REG.findall(text):
+        out.update((kind, i) for i in (range(int(lo), int(hi) + 1) if lo else [int(one)]))
+    return out
+
+
+@pytest.fixture(scope="module")
+def functions(tmp_path_factory):
+    """[(name, [(mnemonic, [operands], index of the branch target or None)])] of every kernel."""
+    if not os.path.exists(OBJDUMP) or not os.path.exists(B.LIB):
+        pytest.skip("no disassembler, or the library is not built")
+    d = tmp_path_factory.mktemp("image")
+    lib = shutil.copy(B.LIB, d / "librap.so")
+    subprocess.run([OBJDUMP, "--offloading", lib], cwd=d, stdout=subprocess.DEVNULL, check=True)
+    out = []
+    for image in sorted(p for p in os.listdir(d) if p.endswith("gfx950")):
+        text = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", str(d / image)], stdout=subprocess.PIPE, text=True, check=True).stdout
+        for part in re.split(r"^(?=[0-9a-f]{16} <)", text, flags=re.M)[1:]:
+            head = re.match(r"([0-9a-f]{16}) <(.+)>:", part)
+            start, code, at, jumps = int(head.group(1), 16), [], {}, []
+            for line in part.splitlines()[1:]:
+                m = LINE.match(line)
+                if not m:
+                    continue
+                at[int(m.group(3), 16)] = len(code)
+                to = None
+                if m.group(1).startswith(("s_branch", "s_cbranch")):
+                    assert m.group(4) == head.group(2) or m.group(5) is None, line
+                    to = start + int(m.group(5) or "0", 16)
+                    jumps.append(len(code))
+                code.append([m.group(1), [x.strip() for x in m.group(2).split(",")], to])
+            for i in jumps:
+                code[i][2] = at[code[i][2]]
+            out.append((head.group(2), code))
+    assert sum(len(c) for _, c in out) > 100000
+    return out
+
+
+def _after(code, i, wait):
+    """Instructions that can run fewer than `wait` wait states after instruction i, on any path."""
+    todo, best = [(i + 1, 0)], {}
+    while todo:
+        j, d = todo.pop()
+        while j < len(code) and d < wait and best.get(j, wait) > d:
+            best[j] = d
+            op, args, to = code[j]
+            yield op, args
+            d += int(args[0], 0) + 1 if op == "s_nop" else 1
+            if op == "s_endpgm":
+                break
+            if to is not None:
+                if op != "s_branch":
+                    todo.append((j + 1, d))
+                j = to
+            else:
+                j += 1
+
+
+def _is_memory(op):
+    return op.startswith(("global_", "buffer_", "flat_", "scratch_", "ds_"))
+
+
+def _read(op, args):
+    also_first = op.startswith(("v_fmac", "v_mac", "v_swap")) or "_swap" in op or "store" in op or "write" in op
+    return _regs(",".join(args if also_first else args[1:]))
+
+
+def test_matrix_results_are_not_read_too_early(functions):
+    """Eight wait states from a matrix instruction to a vector or memory instruction that reads its
+    result (matrix instructions themselves are interlocked or waited for by their own rule)."""
+    n, bad = 0, []
+    for name, code in functions:
+        for i, (op, args, _) in enumerate(code):
+            if not op.startswith(("v_mfma", "v_smfma")):
+                continue
+            n += 1
+            dst = _regs(args[0])
+            for op2, args2 in _after(code, i, MFMA_WAIT[op]):
+                if (op2.startswith("v_") and not op2.startswith("v_mfma") or _is_memory(op2)) and _read(op2, args2) & dst:
+                    bad.append("%s: %s %s ... %s %s" % (name, op, args[0], op2, ", ".join(args2)))
+                    break
+    assert n > 5000
+    assert not bad, "%d of %d, first: %s" % (len(bad), n, bad[0])
