@@ -14,8 +14,10 @@ from paper_2602_02599_amd import build as B
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 # wait states between a matrix instruction of four passes and a vector or memory instruction that
-# reads its result
+# reads its result, and between a vector instruction that writes a scalar register and a memory
+# instruction that takes its address from there
 MFMA_WAIT = {"v_mfma_f32_16x16x32_bf16": 8}
+SGPR_WAIT = 5
 LINE = re.compile(r"^\t(\S+)\s*(.*?)\s*// ([0-9A-F]+): (?:[0-9A-F]{8} ?)+(?:<(\S+)\+0x([0-9a-f]+)>)?")
 REG = re.compile(r"\b([vas])(?:(\d+)|\[(\d+):(\d+)\])")
 
@@ -104,3 +106,65 @@ def test_matrix_results_are_not_read_too_early(functions):
                     break
     assert n > 5000
     assert not bad, "%d of %d, first: %s" % (len(bad), n, bad[0])
+
+
+def test_load_addresses_are_not_read_too_early(functions):
+    """Five wait states from a vector instruction that writes a scalar register to a memory
+    instruction that reads it; the hand-written load into LDS keeps them within itself, whatever the
+    compiler puts in front of it."""
+    bad, loads = [], 0
+    for name, code in functions:
+        for i, (op, args, _) in enumerate(code):
+            if op.startswith(("v_readlane", "v_readfirstlane")):
+                dst = _regs(args[0])
+                bad += ["%s: %s %s ... %s %s" % (name, op, args[0], op2, args2) for op2, args2 in _after(code, i, SGPR_WAIT)
+                        if _is_memory(op2) and _regs(",".join(args2)) & dst]
+            if op == "global_load_lds_dwordx4":
+                loads += 1
+                waits, j = 0, i
+                while waits < SGPR_WAIT:
+                    j -= 1
+                    o, a, _ = code[j]
+                    if o == "s_mov_b32" and a[0] == "m0":
+                        waits += 1
+                        break
+                    if o != "s_nop":
+                        break
+                    waits += int(a[0], 0) + 1
+                if waits < SGPR_WAIT:
+                    bad.append("%s: %d wait states of its own before %s %s" % (name, waits, op, args))
+    assert loads > 100
+    assert not bad, "%d, first: %s" % (len(bad), bad[0])
+
+
+PROBE = r"""
+#include "%s/rap_prefill_kernel.h"
+namespace rap { namespace {
+typedef __attribute__((address_space(1))) const void* gp;
+typedef __attribute__((address_space(3))) void* lp;
+__global__ void probe(const unsigned char* p, uint32_t slot, float* out) {
+  __shared__ unsigned char area[4096];
+  __builtin_amdgcn_global_load_lds((gp)p, (lp)area, 4, 0, 0);
+  load_to_lds(p, 16 * threadIdx.x, slot);
+  __builtin_amdgcn_global_load_lds((gp)(p + 64), (lp)area, 4, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  out[threadIdx.x] = area[threadIdx.x];
+}
+} }
+void launch() { hipLaunchKernelGGL(rap::probe, dim3(1), dim3(64), 0, 0, nullptr, 0, nullptr); }
+"""
+
+
+def test_hand_written_load_declares_m0(tmp_path):
+    """A load into LDS by the compiler's own form on either side of the hand-written one: m0 has to be
+    set again for the second (compiled only, never run)."""
+    if not os.path.exists("/opt/rocm/bin/hipcc"):
+        pytest.skip("hipcc not available")
+    src, asm = tmp_path / "probe.hip", tmp_path / "probe.s"
+    src.write_text(PROBE % B.CSRC)
+    subprocess.run([B.hipcc(), *B.FLAGS, "--cuda-device-only", "-S", str(src), "-o", str(asm)], check=True,
+                   stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=120)
+    steps = re.findall(r"s_mov_b32 m0|global_load_lds_dword\w*", asm.read_text())
+    assert steps == ["s_mov_b32 m0", "global_load_lds_dword", "s_mov_b32 m0", "global_load_lds_dwordx4",
+                     "s_mov_b32 m0", "global_load_lds_dword"], steps
