@@ -87,12 +87,12 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 // lane0_slot + 16 i.  Written as the instruction because the compiler, which cannot tell the buffer
 // being filled from the one being read, waits for every outstanding load of the builtin's form in
 // front of the next LDS read: the whole latency of a tile's loads, once per tile.  The caller waits
-// (s_waitcnt, then the workgroup barrier) before anybody reads the slots.  The four cycles of s_nop
-// after the move to m0 make five wait states in front of the load, what a load needs after a vector
-// instruction has written its base address (v_readlane, v_readfirstlane): the compiler does not see
-// a load in here and puts none in front.
+// (s_waitcnt, then the workgroup barrier) before anybody reads the slots.  The LDS address goes in
+// m0, which the compiler sets and keeps track of.  It does not see a load in here: the s_nop is the
+// five wait states that one needs after a vector instruction has written its base address
+// (v_readlane, v_readfirstlane), and covers the one it needs after a move to m0.
 __device__ __forceinline__ void load_to_lds(const unsigned char* base, int off, uint32_t lane0_slot) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lane0_slot) : "memory", "m0");
+  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "{m0}"(lane0_slot) : "memory");
 }
 
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>): a loop whose index is a

@@ -121,16 +121,8 @@ def test_load_addresses_are_not_read_too_early(functions):
                         if _is_memory(op2) and _regs(",".join(args2)) & dst]
             if op == "global_load_lds_dwordx4":
                 loads += 1
-                waits, j = 0, i
-                while waits < SGPR_WAIT:
-                    j -= 1
-                    o, a, _ = code[j]
-                    if o == "s_mov_b32" and a[0] == "m0":
-                        waits += 1
-                        break
-                    if o != "s_nop":
-                        break
-                    waits += int(a[0], 0) + 1
+                before = code[i - 1]
+                waits = int(before[1][0], 0) + 1 if before[0] == "s_nop" else 0
                 if waits < SGPR_WAIT:
                     bad.append("%s: %d wait states of its own before %s %s" % (name, waits, op, args))
     assert loads > 100
