@@ -91,15 +91,6 @@ __host__ __device__ __forceinline__ float f64_to_f32_odd_clamped448(double y) {
   return bits_f32(bits);
 }
 
-// Which loads of a cache tile the decode kernel issues.  A tile (32 rows of any width: a multiple
-// of 64 bytes for two-byte elements, of 32 for one-byte ones, 16-byte aligned) is fetched as n_ld
-// wave-wide loads of 1 KB, lane l of load j taking bytes [1024 j + 16 l, + 16).  n_ld is fixed at
-// compile time from the instantiation (KCH = ceil(d_k / 32) score steps; NT output tiles of 16
-// channels: ceil(d_v / 16) for bf16 caches, blocks of 64 channels, i.e. 4 or 8 tiles, for one-byte
-// codes) and can exceed the number of loads the tile needs by one whole load (bf16 K tiles: 2 KCH
-// against ceil(d_k / 16); one-byte V tiles: NT / 2 against ceil(d_v / 32)).  The last n_trim loads
-// are therefore trimmed to the tile by lane, all earlier ones are issued whole.  In a partial tile
-// (the last rows of a sequence) every load is trimmed to the bytes of the rows that exist.
 // ---- 4-bit caches: microscaling FP4 (E2M1 elements, one E8M0 scale byte per block of 32) --------
 // E2M1 code (S.EE.M; magnitudes 0, 0.5, 1, 1.5, 2, 3, 4, 6) nearest to y, ties to the code with
 // mantissa bit 0, magnitudes above 6 saturate.  The thresholds are the midpoints between
@@ -129,6 +120,15 @@ constexpr int mx_blocks(int d) { return (d + 31) / 32; }
 // (two blocks) that way, else eight.
 constexpr int mx4_lane_channels(int nb) { return nb <= 2 ? 4 : 8; }
 
+// Which loads of a cache tile the decode kernel issues.  A tile (32 rows of any width: a multiple
+// of 64 bytes for two-byte elements, of 32 for one-byte ones, 16-byte aligned) is fetched as n_ld
+// wave-wide loads of 1 KB, lane l of load j taking bytes [1024 j + 16 l, + 16).  n_ld is fixed at
+// compile time from the instantiation (KCH = ceil(d_k / 32) score steps; NT output tiles of 16
+// channels: ceil(d_v / 16) for bf16 caches, blocks of 64 channels, i.e. 4 or 8 tiles, for one-byte
+// codes) and can exceed the number of loads the tile needs by one whole load (bf16 K tiles: 2 KCH
+// against ceil(d_k / 16); one-byte V tiles: NT / 2 against ceil(d_v / 32)).  The last n_trim loads
+// are therefore trimmed to the tile by lane, all earlier ones are issued whole.  In a partial tile
+// (the last rows of a sequence) every load is trimmed to the bytes of the rows that exist.
 constexpr int decode_v_tiles(int d_v, bool q8) { return q8 ? 4 * ((d_v + 63) / 64) : (d_v + 15) / 16; }
 constexpr int k_tile_loads(int kch, bool q8) { return q8 ? kch : 2 * kch; }
 constexpr int v_tile_loads(int nt, bool q8) { return q8 ? (nt + 1) / 2 : nt; }
@@ -137,6 +137,30 @@ constexpr int v_tile_trimmed(bool q8) { return q8 ? 2 : 1; }
 __host__ __device__ __forceinline__ bool tile_load_issued(int j, int lane, int n_ld, int n_trim, int bytes, bool whole_tile) {
   if (whole_tile && j < n_ld - n_trim) return true;
   return 1024 * j + 16 * lane < bytes;
+}
+
+// Which bytes of a cache tile the prefill kernel loads.  A tile is up to kPrefillTile rows of `pitch`
+// bytes, fetched in 16-byte pieces from the start of every row; piece c of a tile is piece
+// c % per_row of row c / per_row.  With `repeat` (loads straight into LDS, where per_row counts the
+// 16-byte slots of a padded LDS row) the slots behind a row take its last piece again, so that in a
+// whole tile every slot has something to load; else a slot behind the row loads nothing.
+constexpr int kPrefillTile = 64, kNoPiece = 0x7fffffff;
+__host__ __device__ __forceinline__ int prefill_piece_offset(int c, int per_row, int pitch, bool repeat) {
+  const int row = c / per_row;
+  int piece = c - row * per_row;
+  if (repeat) piece = piece < (pitch - 1) >> 4 ? piece : (pitch - 1) >> 4;
+  return row < kPrefillTile && 16 * piece < pitch ? row * pitch + 16 * piece : kNoPiece;
+}
+// Whether the piece at such an offset, inside a tile whose readable rows make `bytes` bytes, is read
+// whole; else only what is left of those.  A row's last piece runs on into the next row, at the last
+// readable row into the rows behind it: those exist, eight of them or sixteen for one-byte
+// elements, unless the cache ends there (prefill_rows_follow).
+__host__ __device__ __forceinline__ bool prefill_piece_whole(int off, int bytes, bool rows_follow) {
+  return rows_follow || bytes - off >= 16;
+}
+// Readable rows and capacities are multiples of eight (sixteen), so one row more is as many more.
+__host__ __device__ __forceinline__ bool prefill_rows_follow(long long first_row, int rows, long long all_rows) {
+  return first_row + rows < all_rows;
 }
 
 }  // namespace rap

@@ -162,7 +162,7 @@ struct PrefillPlan {
 // d_v > 96), and the pitches of a tile's rows in LDS (K: 16 bytes past a multiple of 64, V: an odd
 // multiple of 32 bytes, so that neither kind of read meets its own banks).  The plan, the kernel
 // and the launch all go by these.
-constexpr int kPrefillWaves = 4, kPrefillTile = 64;
+constexpr int kPrefillWaves = 4;
 enum { kTilesDirect = 0, kTilesOddV = 1, kTilesCodes = 2 };   // bf16 rows of even width, odd V rows, one-byte codes
 constexpr int prefill_k_pitch(int k_steps) { return 64 * k_steps + 16; }
 constexpr int prefill_v_pitch(int channel_tiles) { return 32 * (channel_tiles | 1); }

@@ -195,32 +195,19 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const int len8 = Q8 ? (len + 15) & ~15 : (len + 7) & ~7;
 
   // ---- tile loads.  A thread's load j covers 16-byte slot (or piece) c = j * NT + tid of the tile:
-  // offset of its source inside the cache tile, or beyond any tile where there is nothing to load
-  // (direct loads: a slot of the gap behind a row repeats the row's last piece, so that no load of
-  // a whole tile needs a lane mask).
-  constexpr int kNothing = 0x7fffffff;
+  // offset of its source inside the cache tile, or beyond any tile where there is nothing to load.
   int kgo[NLK], vgo[NLV];
 #pragma unroll
-  for (int j = 0; j < NLK; ++j) {
-    const int c = j * NT + tid, row = c / (K_DIRECT ? SLK : PCK);
-    int piece = c - row * (K_DIRECT ? SLK : PCK);
-    if (K_DIRECT) piece = min(piece, (pitch_k - 1) >> 4);
-    kgo[j] = row < kPrefillTile && 16 * piece < pitch_k ? row * pitch_k + 16 * piece : kNothing;
-  }
+  for (int j = 0; j < NLK; ++j) kgo[j] = prefill_piece_offset(j * NT + tid, K_DIRECT ? SLK : PCK, pitch_k, K_DIRECT);
 #pragma unroll
-  for (int j = 0; j < NLV; ++j) {
-    const int c = j * NT + tid, row = c / (V_DIRECT ? SLV : PCV);
-    int piece = c - row * (V_DIRECT ? SLV : PCV);
-    if (V_DIRECT) piece = min(piece, (pitch_v - 1) >> 4);
-    vgo[j] = row < kPrefillTile && 16 * piece < pitch_v ? row * pitch_v + 16 * piece : kNothing;
-  }
+  for (int j = 0; j < NLV; ++j) vgo[j] = prefill_piece_offset(j * NT + tid, V_DIRECT ? SLV : PCV, pitch_v, V_DIRECT);
   // LDS address of this wavefront's first slot
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)smem))) + 1024 * wave;
-  // one tile straight into LDS at `area`: `src` its first byte, `rows` those that are readable,
-  // `whole`: 16 bytes may be read from the last piece of the last row without leaving the cache
-  auto load_direct = [&](const int* off, auto n_loads, auto wave_loads, const unsigned char* src, int rows, int pitch, bool whole, int area) {
+  // one tile straight into LDS at `area`: `src` its first byte, `rows` those that are readable, `follow`:
+  // more rows of the cache come behind them
+  auto load_direct = [&](const int* off, auto n_loads, auto wave_loads, const unsigned char* src, int rows, int pitch, bool follow, int area) {
     const int bytes = rows * pitch;
-    if (whole && rows == kPrefillTile) {
+    if (follow && rows == kPrefillTile) {
       static_for<decltype(n_loads)::value>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         if (j * NW + NW <= decltype(wave_loads)::value || j * NW + wave < decltype(wave_loads)::value)
@@ -230,19 +217,19 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
       static_for<decltype(n_loads)::value>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         const int o = off[j];
-        if (o < bytes && (whole || bytes - o >= 16)) load_to_lds(src, o, lds0 + area + j * NT * 16);
-        if (o < bytes && !whole && bytes - o < 16)                        // the cache ends inside this piece (whole dwords)
+        if (o < bytes && prefill_piece_whole(o, bytes, follow)) load_to_lds(src, o, lds0 + area + j * NT * 16);
+        if (o < bytes && !prefill_piece_whole(o, bytes, follow))          // the cache ends inside this piece (whole dwords)
           for (int i = 0; i < bytes - o; i += 4)
             *reinterpret_cast<uint32_t*>(smem + area + (j * NT + tid) * 16 + i) = *reinterpret_cast<const uint32_t*>(src + o + i);
       });
     }
   };
-  auto load_regs = [&](const int* off, auto n_loads, const unsigned char* src, int bytes, bool whole, uint4* st) {
+  auto load_regs = [&](const int* off, auto n_loads, const unsigned char* src, int bytes, bool follow, uint4* st) {
     static_for<decltype(n_loads)::value>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
       const int o = off[j];
       if (o < bytes) {
-        if (whole || bytes - o >= 16) {
+        if (prefill_piece_whole(o, bytes, follow)) {
           const Bytes16 v = *reinterpret_cast<const Bytes16*>(src + o);
           st[j] = make_uint4(v.w[0], v.w[1], v.w[2], v.w[3]);
         } else {
@@ -277,15 +264,15 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   if constexpr (!V_DIRECT) static_for<NLV>([&](auto j) { vst[decltype(j)::value] = make_uint4(0, 0, 0, 0); });
   auto issue_k = [&](int t, long long trow) {
     const int rows = min(kPrefillTile, len8 - t * kPrefillTile);
-    const bool whole = trow + rows < all_rows;
-    if constexpr (K_DIRECT) load_direct(kgo, std::integral_constant<int, NLK>(), std::integral_constant<int, SLK>(), kcache + trow * pitch_k, rows, pitch_k, whole, (t & 1) * KBUF);
-    else load_regs(kgo, std::integral_constant<int, NLK>(), kcache + trow * pitch_k, rows * pitch_k, whole, kst);
+    const bool follow = prefill_rows_follow(trow, rows, all_rows);
+    if constexpr (K_DIRECT) load_direct(kgo, std::integral_constant<int, NLK>(), std::integral_constant<int, SLK>(), kcache + trow * pitch_k, rows, pitch_k, follow, (t & 1) * KBUF);
+    else load_regs(kgo, std::integral_constant<int, NLK>(), kcache + trow * pitch_k, rows * pitch_k, follow, kst);
   };
   auto issue_v = [&](int t, long long trow) {
     const int rows = min(kPrefillTile, len8 - t * kPrefillTile);
-    const bool whole = trow + rows < all_rows;
-    if constexpr (V_DIRECT) load_direct(vgo, std::integral_constant<int, NLV>(), std::integral_constant<int, SLV>(), vcache + trow * pitch_v, rows, pitch_v, whole, 2 * KBUF + (t & 1) * VBUF);
-    else load_regs(vgo, std::integral_constant<int, NLV>(), vcache + trow * pitch_v, rows * pitch_v, whole, vst);
+    const bool follow = prefill_rows_follow(trow, rows, all_rows);
+    if constexpr (V_DIRECT) load_direct(vgo, std::integral_constant<int, NLV>(), std::integral_constant<int, SLV>(), vcache + trow * pitch_v, rows, pitch_v, follow, 2 * KBUF + (t & 1) * VBUF);
+    else load_regs(vgo, std::integral_constant<int, NLV>(), vcache + trow * pitch_v, rows * pitch_v, follow, vst);
   };
   // start row of a tile, looked up (paged) one tile ahead of its loads
   auto row_of_tile = [&](int t) -> long long { return t < n_tiles ? tile_row(t * kPrefillTile) : 0; };

@@ -14,6 +14,11 @@
 //   rap_arith_host loadplan-trim1  the same with only the LAST load of a run trimmed (a planted
 //                               mistake: bf16 K tiles whose width needs an odd number of loads
 //                               then read past the tile; the tests expect this one to fail)
+//   rap_arith_host pieceplan -> text, one line per (kind, element size, width): what the prefill
+//                               kernel's tile loads touch, in the middle of a cache and at its end; exit
+//                               status 1 if any leaves the cache, or misses a byte of a readable row
+//   rap_arith_host pieceplan-whole  the same with every piece read whole (a planted mistake: the
+//                               last row's last piece then runs past the end of the cache)
 #include <stdio.h>
 #include <string.h>
 
@@ -69,15 +74,56 @@ int loadplan(bool trim_one_only) {
   return bad;
 }
 
+// The pieces of a tile as prefill_kernel walks them: straight into LDS (slots of padded rows: bf16,
+// even widths) or through registers.  `over`: bytes read beyond what exists behind the tile, `missed`:
+// bytes of readable rows that no piece covers, `idle`: slots of a whole tile, loaded without a lane
+// mask, that have nothing to load.
+int pieceplan(bool read_whole) {
+  int bad = 0;
+  for (int eb = 1; eb <= 2; ++eb) {
+    const int quantum = eb == 1 ? 16 : 8;                         // rows come in such groups, and so do capacities
+    for (int kind = 0; kind < 2; ++kind) {                        // 0: K tile (even widths), 1: V tile
+      for (int d = kind == 0 ? 2 : 1; d <= 128; d += kind == 0 ? 2 : 1) {
+        const int pitch = eb * d;
+        const bool direct = eb == 2 && (d & 1) == 0;
+        const int per_row = kind == 0 ? (direct ? 4 * ((d + 31) / 32) + 1 : 2 * ((d + 31) / 32))
+                                      : (direct ? 2 * ((d + 15) / 16 | 1) : (eb == 1 ? 1 : 2) * ((d + 15) / 16));
+        int over = 0, missed = 0, idle = 0;
+        for (int rows = quantum; rows <= rap::kPrefillTile; rows += quantum) {
+          for (int groups_behind = 0; groups_behind < 2; ++groups_behind) {
+            const bool follow = rap::prefill_rows_follow(1000 * quantum, rows, 1000 * quantum + rows + groups_behind * quantum);
+            const int bytes = rows * pitch, exist = bytes + groups_behind * quantum * pitch;
+            std::vector<char> hit(static_cast<size_t>(rap::kPrefillTile) * pitch + 64, 0);
+            const int slots = (rap::kPrefillTile * per_row + 255) / 256 * 256;
+            for (int c = 0; c < slots; ++c) {
+              const int o = rap::prefill_piece_offset(c, per_row, pitch, direct);
+              if (direct && rows == rap::kPrefillTile && follow) idle += c < rap::kPrefillTile * per_row && o == rap::kNoPiece;
+              const int n = o >= bytes ? 0 : read_whole || rap::prefill_piece_whole(o, bytes, follow) ? 16 : bytes - o;
+              if (n > 0 && o + n - exist > over) over = o + n - exist;
+              for (int i = 0; i < n; ++i) hit[o + i] = 1;
+            }
+            for (int i = 0; i < bytes; ++i) missed += hit[i] == 0;
+          }
+        }
+        printf("%s eb=%d d=%d direct=%d over=%d missed=%d idle=%d\n", kind == 0 ? "K" : "V", eb, d, direct, over, missed, idle);
+        bad += over > 0 || missed != 0 || idle != 0;
+      }
+    }
+  }
+  return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   if (argc != 2) {
-    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1\n");
+    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole\n");
     return 2;
   }
   if (strcmp(argv[1], "loadplan") == 0) return loadplan(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "loadplan-trim1") == 0) return loadplan(true) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "pieceplan") == 0) return pieceplan(false) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "pieceplan-whole") == 0) return pieceplan(true) == 0 ? 0 : 1;
   const std::vector<double> in = read_doubles();
   if (strcmp(argv[1], "bf16") == 0) {
     std::vector<uint16_t> out(in.size());

@@ -219,3 +219,24 @@ def test_prefill_split_plan_from_the_outside(rap):
 def test_missing_library_fails_loudly(tmp_path):
     with pytest.raises(pkg.RapError):
         pkg.Rap(str(tmp_path / "librap.so"))
+
+
+def _ranges(rap, need, batch, n_q, d_v):
+    """Ranges whose partials (accumulators, then reference and sum, one slot spare) fill `need` bytes."""
+    up = lambda x: (x + 255) // 256 * 256
+    n = [n for n in range(1, 600) if up(batch * n_q * (n + 1) * d_v * 4) + up(batch * n_q * (n + 1) * 8) + 256 == need]
+    assert len(n) == 1, need
+    return n[0]
+
+
+# sequences, longest, query heads, d_v -> ranges of the plan, of the plain rule (two workgroups per compute
+# unit, ranges of 512 to 4096 rows, up to 8192 where that avoids a partly filled second round), 8 KV heads
+@pytest.mark.parametrize("batch,ctx,n_q,d_v,plan,plain", [
+    (1, 512, 32, 90, 4, 1), (1, 2048, 32, 90, 16, 4), (1, 8192, 32, 90, 32, 16), (24, 8192, 32, 90, 4, 2), (40, 4096, 32, 90, 4, 1),
+    (64, 16384, 32, 90, 8, 4), (4, 131072, 32, 64, 16, 16), (32, 1024, 32, 90, 1, 2), (16, 512, 32, 90, 1, 1),
+    (64, 16384, 64, 128, 4, 4)])                                  # the last: partials of 8 ranges would not fit the static array
+def test_split_plan_ranges(rap, batch, ctx, n_q, d_v, plan, plain):
+    """The automatic plan's ranges through the size query, which returns the larger of the two rules."""
+    shp = rap.shape(batch, n_q, 8, 128, 45, d_v, ctx, 5e5)
+    need = rap.rap_decode_attn_workspace_bytes(shp, ctx)
+    assert _ranges(rap, need, batch, n_q, d_v) == max(plan, plain)

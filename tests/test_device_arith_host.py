@@ -193,3 +193,19 @@ def test_decode_tile_loads_stay_inside_the_tile(harness):
             if ln.startswith("K q8=0") and "rows=32" in ln
             and int(dict(kv.split("=") for kv in ln.split()[1:])["top"]) > int(dict(kv.split("=") for kv in ln.split()[1:])["bytes"])}
     assert {34, 76, 102} <= over and not ({64, 90, 116, 128} & over)
+
+
+def test_prefill_tile_loads_stay_inside_the_cache(harness):
+    """Every piece the prefill kernel loads of a K or V tile, for every width the library accepts, both
+    element sizes, every number of readable rows, in the middle of a cache and at its end: nothing
+    beyond the cache, every byte of every readable row, no idle slot in an unmasked load."""
+    rc, text = _run(harness, "pieceplan")
+    lines = [ln.split() for ln in text.splitlines() if ln]
+    assert rc == 0 and len(lines) == 2 * (64 + 128), text[-500:]
+    assert all(ln[4:] == ["over=0", "missed=0", "idle=0"] for ln in lines)
+    # with every piece read whole, all widths but those of whole pieces read past the end
+    rc_whole, text_whole = _run(harness, "pieceplan-whole")
+    assert rc_whole == 1
+    for ln in text_whole.splitlines():
+        f = dict(kv.split("=") for kv in ln.split()[1:])
+        assert (int(f["over"]) > 0) == (int(f["eb"]) * int(f["d"]) % 16 != 0), ln
