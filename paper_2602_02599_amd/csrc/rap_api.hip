@@ -96,8 +96,8 @@ int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap:
 //    step; cutting into ranges adds a combining launch, 2.7 us.  So while one range per compute unit
 //    is at most 512 rows, that is the range, if it spares three steps or more (1 x 2048 rows: 14.0 us
 //    in ranges of 512, 10.5 in 128; 1 x 8192: 15.0 in 512, 13.5 in 256; 16 x 512: 13.2 in 256, 12.0
-//    whole); and with a slab for every compute unit up to 1024 rows stay whole (32 x 1024: 23.4 us
-//    in two ranges, 22.1 in one).
+//    whole; 14 x 790, seven steps or four: 17.0 us whole, 15.7 in 512); and with a slab for every
+//    compute unit up to 1024 rows stay whole (32 x 1024: 23.4 us in two ranges, 22.1 in one).
 //  * Beyond that the chip wants at least two workgroups per compute unit, of 512 rows or more.
 //    Where the slabs leave more than a fifth of that number over, more and shorter ranges that come
 //    out even are better: 24 x 8192 (192 slabs) 102 us with 2 ranges per slab, 95 with 4; 40 x 4096
@@ -144,7 +144,7 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
   const int64_t k1 = cus / slabs > 1 ? cus / slabs : 1;                        // ranges per slab with one workgroup per compute unit
   const int64_t per_cu = round_to_quantum((max_seq_len + k1 - 1) / k1);
   if (per_cu <= 512 && slabs <= cus) {
-    r = max_seq_len - per_cu >= 3 * rap::kSplitQuantum ? per_cu : round_to_quantum(max_seq_len);
+    r = round_to_quantum(max_seq_len) - per_cu >= 3 * rap::kSplitQuantum ? per_cu : round_to_quantum(max_seq_len);
   } else if (slabs >= cus && max_seq_len <= 1024) {
     r = round_to_quantum(max_seq_len);
   } else {

@@ -130,7 +130,7 @@ def _slots_bytes(B, Hq, dv, n_split):
     return up(B * Hq * (n_split + 1) * dv * 4) + up(B * Hq * (n_split + 1) * 8) + 256
 
 
-@pytest.mark.parametrize("B,ctx,plan,plain", [(1, 512, 4, 1), (1, 2048, 16, 4), (2, 384, 1, 1), (3, 5000, 10, 10), (1, 130, 1, 1), (24, 1100, 2, 2), (32, 1024, 1, 2)])
+@pytest.mark.parametrize("B,ctx,plan,plain", [(1, 512, 4, 1), (1, 2048, 16, 4), (2, 384, 1, 1), (3, 5000, 10, 10), (1, 130, 1, 1), (24, 1100, 2, 2), (32, 1024, 1, 2), (14, 790, 2, 2)])
 def test_plan_and_smaller_workspace(rap, B, ctx, plan, plain):
     """The ranges of the automatic plan at few sequences and ragged lengths, and the same call with a
     workspace that only holds the plain rule's ranges (none where that is a single range); what the
