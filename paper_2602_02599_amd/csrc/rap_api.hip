@@ -101,15 +101,26 @@ int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap:
 //  * Beyond that the chip wants at least two workgroups per compute unit, of 512 rows or more.
 //    Where the slabs leave more than a fifth of that number over, more and shorter ranges that come
 //    out even are better: 24 x 8192 (192 slabs) 102 us with 2 ranges per slab, 95 with 4; 40 x 4096
-//    (320 slabs) 94 us with one, 82 with 4.  With less left over they are not: 18 x 8192 (144 slabs)
+//    (320 slabs) 92 us with one, 80 with 4.  With less left over they are not: 18 x 8192 (144 slabs)
 //    72 us with 3 ranges, 75 with 7; 14 x 9738 at 16 query rows per slab 74 us with 4, 78 with 9.
+//    From 257 slabs on, where rows would be whole, three or more ranges of 768 rows or more: two are
+//    good for equal lengths only (whole / 2 / 3 ranges: 40 x 3000 69 / 65 / 63 us, ragged 45 / 49 / 42;
+//    fp8, d = 128, 48 x 3000 66 / 60 / 68, ragged 57 / 68 / 53; 44 x 2600 67 / 64 / 65, ragged 49 / 49 / 41).
 //  * Long ranges save a little on equal lengths and cost a lot on ragged ones, whose workgroups are
 //    then few and unequal: an eighth of max_seq_len, no less than 2048 and no more than 4096 rows.
 //    64 x 16384: 451 / 456 / 464 us in 8192 / 4096 / 2048 rows, ragged 327 / 274 / 265; 32 x 16384
 //    230 / 231 / 232, ragged 159 / 145 / 141; fp8 32 x 16384 137 / 147 / 137, ragged 117 / 89 / 87;
-//    64 x 32768 892 / 902 / 931, ragged 539 / 520 / 515.  Up to 16 sequences keep the plain rule's
-//    ranges of up to 8192 rows where those bring the job into a single round (4 x 131072, d = 64: 167
-//    us in 8192 rows, 171 in 4096).
+//    64 x 32768 892 / 902 / 931, ragged 539 / 520 / 515.  What equal lengths lose is most where rows
+//    were whole or ranges few: 64 x 8192 in 4 ranges 234 us, whole 229, ragged 138 and 160; fp8 at d = 64
+//    93 and 81, ragged 63 and 69; fp8 28 x 8192 75 us in 4, 69 in 2, ragged 49 and 66.  Hence not for
+//    the sake of a little (112 slabs of 9738 rows: 73 us in 2560, 81 in 2048), nor of two ranges where rows
+//    are whole (64 x 4096: 115 us whole, 121 in two, ragged 83 and 94); and into equal ranges (64 x 5000:
+//    153 us in three of 1792, 161 in 2048 with a short third; whole 147; ragged 99, 102 and 108).
+//  * Up to 16 sequences keep the plain rule's ranges of up to 8192 rows where those bring the job into a
+//    single round.  In 8192 / 4096 / 2048 rows: 4 x 131072 228 / 231 / 236 us, at d = 64 171 / 175 / 174, fp8 130
+//    / 147 / 133; 8 x 65536 229 / 231 / 234, 16 x 32768 229 / 228 / 230, fp8 131 / 146 / 130.  That is for
+//    equal lengths; ragged batches pay for it: 4 x 131072 154 / 149 / 135 us, at d = 64 162 / 127 / 111; 8 x
+//    65536 160 / 147 / 138; 16 x 32768 157 / 145 / 139, fp8 117 / 86 / 86.
 //  * The plan never takes more partials than the static scratch array holds where the plain rule
 //    (two workgroups per compute unit, ranges of 512 to 4096 rows, up to 8192 where that avoids a
 //    partly filled second round of workgroups) would not, so that what a caller with that much
@@ -148,6 +159,7 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
   } else if (slabs >= cus && max_seq_len <= 1024) {
     r = round_to_quantum(max_seq_len);
   } else {
+    auto rows_in = [&](int64_t c) { return round_to_quantum((max_seq_len + c - 1) / c); };
     // how evenly c ranges per slab fill the compute units, less a little for every further range
     auto evenness = [&](int64_t c) {
       const int64_t n = slabs * c, rounds = (n + cus - 1) / cus;
@@ -155,13 +167,15 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
     };
     int64_t k = k0;
     if (evenness(k0) < 0.78) {
-      for (int64_t c = k0 + 1; c <= 4 * k0 && max_seq_len >= 1024 * c; ++c)
+      const int64_t least = k0 == 1 ? 768 : 1024;
+      for (int64_t c = k0 == 1 ? 3 : k0 + 1; c <= 4 * k0 && max_seq_len >= least * c; ++c)
         if (evenness(c) > evenness(k) + 0.02) k = c;
     }
     const int64_t eighth = round_to_quantum(max_seq_len / 8);
     const int64_t most = eighth < 2048 ? 2048 : (eighth > 4096 ? 4096 : eighth);
-    r = round_to_quantum((max_seq_len + k - 1) / k);
-    r = r < 512 ? 512 : (r > most + most / 2 ? most : r);      // not for the sake of a little: 112 slabs of 9738 rows 73 us in 2560, 81 in 2048
+    r = rows_in(k);
+    if (r > (k == 1 ? 2 * most : most + most / 2)) r = rows_in((max_seq_len + most - 1) / most);
+    if (r < 512) r = 512;
     if (single_round && s->batch <= 16) r = halves;
   }
   if (ranges_of(r) > p->n_split && partial_bytes(s, ranges_of(r), 1) > RAP_STATIC_SCRATCH_BYTES) return RAP_OK;   // plain
