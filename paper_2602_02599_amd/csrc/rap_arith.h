@@ -139,6 +139,33 @@ __host__ __device__ __forceinline__ bool tile_load_issued(int j, int lane, int n
   return 1024 * j + 16 * lane < bytes;
 }
 
+// Which sequence, row range and KV head scanning workgroup `wg` of a decode launch takes:
+// sequence by sequence, within a sequence range by range, the KV heads innermost.  Hardware places
+// workgroup L on XCD L mod 8, so with eight KV heads (or a multiple) every XCD gets the same rows
+// whatever the lengths are.  Measured against slab by slab with the ranges innermost, which leaves the
+// XCDs' shares of a ragged batch to chance: 64 sequences of 1024 to 16384 rows in ranges of 4096 rows 296
+// -> 268 us, 64 up to 65536 rows 994 -> 977 us, fp8 32 up to 16384 92 -> 88 us; equal lengths 32 x 16384
+// 237 -> 232 us.
+//  * Within an XCD the workgroups go round its compute units in turn, and in a ragged batch the first
+//    ranges are the ones that hold rows: those of following sequences should lie an odd number of
+//    workgroups apart.  With an odd number of ranges they do; an even number is rotated by the
+//    sequence.  Rotating odd ones too put them an even number apart: 12 sequences up to 51691 rows, d =
+//    64, 13 ranges, 173 us, not rotated 126; fp8, d = 90, 120 and 87 (equal lengths, d = 64, 210 and 226).
+//    Not rotating even ones: 24 up to 32768, d = 64, 8 ranges, 197 us, rotated 178; fp8 100 and 79.
+//    With fewer KV heads than XCDs the same keeps the first ranges off the same XCDs.
+//  * With up to eight sequences no ranges are rotated, but the heads are, by range and sequence, so that
+//    the ranges of a head meet all XCDs: 4 x 131072 rows at d = 64, where the heads lie a power of two
+//    apart, 171.5 -> 167 us, 8 x 65536 175 -> 171.5.  From 12 to 16 sequences either way is the same to 1 %,
+//    from 24 on rotated heads cost 1 % on equal lengths (32 x 16384 238 -> 240.5).
+__host__ __device__ __forceinline__ void decode_place(int wg, int n_split, int n_kv, int batch, int* b, int* split, int* h) {
+  const int seq_range = wg / n_kv;
+  *b = seq_range / n_split;
+  const int nth = seq_range - *b * n_split;
+  const bool few = batch <= 8;
+  *split = few || (n_split & 1) != 0 ? nth : (nth + *b) % n_split;
+  *h = (wg - seq_range * n_kv + (few ? nth + *b : 0)) % n_kv;
+}
+
 // Which bytes of a cache tile the prefill kernel loads.  A tile is up to kPrefillTile rows of `pitch`
 // bytes, fetched in 16-byte pieces from the start of every row; piece c of a tile is piece
 // c % per_row of row c / per_row.  With `repeat` (loads straight into LDS, where per_row counts the

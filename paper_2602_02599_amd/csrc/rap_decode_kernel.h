@@ -265,27 +265,17 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction
   const int l16 = lane & 15;
   const int lg = lane >> 4;
-  // One-dimensional grid: sequence by sequence, within a sequence range by range, the KV heads
-  // innermost.  Hardware places workgroup L on XCD L mod 8, so with eight KV heads (or a multiple)
-  // every XCD gets the same rows whatever the lengths are; with fewer, the ranges are rotated by the
-  // sequence so that the first ones, which always hold rows, do not all meet on the same XCDs.
-  // Measured against slab by slab with the ranges innermost, which leaves the XCDs' shares of a ragged
-  // batch to chance: 64 sequences of 1024 to 16384 rows in ranges of 4096 rows 296 -> 268 us, 64 up to
-  // 65536 rows 994 -> 977 us, fp8 32 up to 16384 92 -> 88 us; equal lengths 32 x 16384 237 -> 232 us.
-  // With up to eight sequences the heads are rotated by the range as well, so that the ranges of a
-  // head meet all XCDs: 4 x 131072 rows at d = 64, where the heads lie a power of two apart, 173 -> 167
-  // us (slab by slab 168); with more sequences that costs 2 % (32 x 16384: 236 us).
-  // The workgroups after those, one per (b, h), exist in the decode step only and take the new
-  // token; coming last they do not disturb the placement of the scanning workgroups.
+  // The workgroups behind the scanning ones, one per (b, h), exist in the decode step only and take
+  // the new token; coming last they do not disturb the placement of the others.
   const int n_scan = a.n_split * a.n_kv * a.batch;
-  const bool scans = static_cast<int>(blockIdx.x) < n_scan;
-  const int wg = scans ? blockIdx.x : blockIdx.x - n_scan;
-  const int seq_range = wg / a.n_kv;
-  const int b = scans ? seq_range / a.n_split : seq_range;
-  const int nth = seq_range - b * a.n_split;
-  const bool few = a.batch <= 8;
-  const int split = !scans ? a.n_split : (few ? nth : (nth + b) % a.n_split);
-  const int h = (wg - seq_range * a.n_kv + (scans && few ? nth + b : 0)) % a.n_kv;
+  const int wg = blockIdx.x;
+  int b, h, split = a.n_split;
+  if (wg < n_scan) {
+    decode_place(wg, a.n_split, a.n_kv, a.batch, &b, &split, &h);
+  } else {
+    b = (wg - n_scan) / a.n_kv;
+    h = (wg - n_scan) - b * a.n_kv;
+  }
 
   int len = a.seq_lens[b];
   len = len < 0 ? 0 : (len > a.max_len ? a.max_len : len);

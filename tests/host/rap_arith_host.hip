@@ -14,6 +14,12 @@
 //   rap_arith_host loadplan-trim1  the same with only the LAST load of a run trimmed (a planted
 //                               mistake: bf16 K tiles whose width needs an odd number of loads
 //                               then read past the tile; the tests expect this one to fail)
+//   rap_arith_host place     -> text, one line per (ranges, KV heads, sequences): whether every
+//                               (sequence, range, head) is placed once, and on how many of eight
+//                               neighbouring compute units the first ranges of eight following
+//                               sequences lie, at least; exit status 1 if placed wrongly or on fewer than 4
+//   rap_arith_host place-rotated  the same with every number of ranges rotated by the sequence (a
+//                               planted mistake: odd numbers then pile up)
 //   rap_arith_host pieceplan -> text, one line per (kind, element size, width): what the prefill
 //                               kernel's tile loads touch, in the middle of a cache and at its end; exit
 //                               status 1 if any leaves the cache, or misses a byte of a readable row
@@ -74,6 +80,33 @@ int loadplan(bool trim_one_only) {
   return bad;
 }
 
+int place(bool always_rotated) {
+  int bad = 0;
+  for (int n_kv = 1; n_kv <= 16; n_kv = n_kv < 8 ? n_kv + 1 : n_kv + 8)
+    for (int n_split = 1; n_split <= 33; ++n_split)
+      for (int batch : {1, 3, 8, 9, 12, 24, 64}) {
+        std::vector<int> hit(static_cast<size_t>(batch) * n_split * n_kv, 0), first(batch, 0);
+        for (int wg = 0; wg < batch * n_split * n_kv; ++wg) {
+          int b, split, h;
+          rap::decode_place(wg, n_split, n_kv, batch, &b, &split, &h);
+          if (always_rotated && (n_split & 1) != 0) split = (split + b) % n_split;
+          if (b < 0 || b >= batch || split < 0 || split >= n_split || h < 0 || h >= n_kv) return 1000000;
+          hit[(static_cast<size_t>(b) * n_split + split) * n_kv + h] += 1;
+          if (split == 0 && h == 0) first[b] = wg / n_kv;         // its turn among the workgroups of an XCD
+        }
+        int wrong = 0, units = 8;
+        for (int x : hit) wrong += x != 1;
+        for (int b = 0; batch > 8 && n_split >= 4 && b + 8 <= batch; ++b) {
+          unsigned seen = 0;
+          for (int i = 0; i < 8; ++i) seen |= 1u << (first[b + i] & 7);
+          units = __builtin_popcount(seen) < units ? __builtin_popcount(seen) : units;
+        }
+        printf("ranges=%d heads=%d sequences=%d wrong=%d units=%d\n", n_split, n_kv, batch, wrong, units);
+        bad += wrong != 0 || units < 4;
+      }
+  return bad;
+}
+
 // The pieces of a tile as prefill_kernel walks them: straight into LDS (slots of padded rows: bf16,
 // even widths) or through registers.  `over`: bytes read beyond what exists behind the tile, `missed`:
 // bytes of readable rows that no piece covers, `idle`: slots of a whole tile, loaded without a lane
@@ -117,11 +150,13 @@ int pieceplan(bool read_whole) {
 
 int main(int argc, char** argv) {
   if (argc != 2) {
-    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole\n");
+    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated\n");
     return 2;
   }
   if (strcmp(argv[1], "loadplan") == 0) return loadplan(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "loadplan-trim1") == 0) return loadplan(true) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "place") == 0) return place(false) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "place-rotated") == 0) return place(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "pieceplan") == 0) return pieceplan(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "pieceplan-whole") == 0) return pieceplan(true) == 0 ? 0 : 1;
   const std::vector<double> in = read_doubles();

@@ -209,3 +209,14 @@ def test_prefill_tile_loads_stay_inside_the_cache(harness):
     for ln in text_whole.splitlines():
         f = dict(kv.split("=") for kv in ln.split()[1:])
         assert (int(f["over"]) > 0) == (int(f["eb"]) * int(f["d"]) % 16 != 0), ln
+
+
+def test_decode_workgroups_are_placed_once_and_apart(harness):
+    """Every (sequence, row range, KV head) gets one workgroup, and in batches the first ranges of eight
+    following sequences spread over neighbouring compute units of an XCD."""
+    rc, text = _run(harness, "place")
+    lines = [dict((k, int(v)) for k, v in (kv.split("=") for kv in ln.split())) for ln in text.splitlines()]
+    assert len(lines) == 9 * 33 * 7
+    assert rc == 0, [f for f in lines if f["wrong"] or f["units"] < 4][:5]
+    rc_rotated, text_rotated = _run(harness, "place-rotated")     # odd numbers of ranges rotated as well
+    assert rc_rotated == 1 and any("ranges=13 " in ln and "units=8" not in ln for ln in text_rotated.splitlines())
