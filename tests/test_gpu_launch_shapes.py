@@ -64,13 +64,14 @@ def test_prefill_widths(rap, fp8, P, dv, Hq, Hkv, n_new, page_rows):
         H.assert_attn_close(cut.cpu().numpy(), ref, "prefill in key ranges")
 
 
-# eight slots per thread and round; one, two, four or eight groups of threads
-@pytest.mark.parametrize("n_tok", [1, 2, 5])
+# eight slots per thread and round; one, two, four or eight groups of threads; loops over one, up to four,
+# up to eight and up to sixteen new tokens
+@pytest.mark.parametrize("n_tok", [1, 2, 5, 11])
 @pytest.mark.parametrize("n_split", [7, 8, 9, 16, 17, 32, 33, 64, 65, 130])
 def test_range_counts(rap, n_split, n_tok):
     """Ranges of 128 rows up to more than the combining kernel's groups read at once: full sequences,
     one that leaves the last ranges empty, an empty one (NaN in every slot of the workspace)."""
-    P, dv, Hq, Hkv = 10, 21, 3, 1
+    P, dv, Hq, Hkv = 10, 21, 3 if n_tok <= 5 else 1, 1
     cap = 128 * n_split
     lens = np.asarray([cap, cap - 128 * (n_split // 3) - 5, 0, cap - 1], dtype=np.int64)
     _say("ranges %d tokens %d" % (n_split, n_tok))
