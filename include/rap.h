@@ -38,7 +38,7 @@ typedef enum rap_status {
   RAP_ERR_SHAPE = 2,       /* inconsistent shape: G not integral, P > D/2, cap % 8 != 0, ...    */
   RAP_ERR_UNSUPPORTED = 3, /* consistent, but outside what the kernels are built for            */
   RAP_ERR_CAPACITY = 4,    /* max_seq_len exceeds cache_cap                                     */
-  RAP_ERR_WORKSPACE = 5,   /* workspace missing or smaller than rap_decode_attn_workspace_bytes */
+  RAP_ERR_WORKSPACE = 5,   /* workspace missing, misaligned or smaller than the call accepts    */
   RAP_ERR_HIP = 6,         /* the HIP runtime refused a launch                                  */
   RAP_ERR_STATIC_LIMIT = 7 /* rap_decode_attn_static: the shape needs more scratch than
                               RAP_STATIC_SCRATCH_BYTES                                          */
@@ -119,8 +119,11 @@ rap_status_t rap_rope_append(const rap_shape_t* shape, int32_t n_new,
                              const int32_t* pos, const int32_t* keep_pair_idx,
                              void* k_cache, void* v_cache, void* stream);
 
-/* Bytes of device scratch rap_decode_attn needs for sequences up to max_seq_len rows with the
- * given tuning (NULL = auto).  Returns 0 for an invalid shape.  Never more than a few MB. */
+/* Bytes of device scratch for rap_decode_attn over sequences up to max_seq_len rows with the given
+ * tuning (NULL = auto): one slot of d_v + 2 floats per query row and row range, and one more per query
+ * row.  13 MB for 64 sequences of 65536 rows with 32 query heads and d_v = 90; it grows with batch,
+ * query heads and ranges.  An array sized for the largest batch and the longest sequence serves all
+ * smaller ones.  Returns 0 for an invalid shape. */
 size_t rap_decode_attn_workspace_bytes(const rap_shape_t* shape, int64_t max_seq_len,
                                        const rap_tuning_t* tuning);
 
@@ -143,11 +146,21 @@ size_t rap_decode_attn_workspace_bytes(const rap_shape_t* shape, int64_t max_seq
  *                                   clamped to max_seq_len on the device
  *   max_seq_len host: upper bound on seq_lens, sizes the grid; 1 <= max_seq_len <= cache_cap
  *   out        dev  fp32  [batch, n_q_heads, d_v]
- *   workspace  dev, at least rap_decode_attn_workspace_bytes(shape, max_seq_len, tuning) bytes,
+ *   workspace  dev, rap_decode_attn_workspace_bytes(shape, max_seq_len, tuning) bytes or more,
  *              256-byte aligned; contents before and after the call are unspecified (the size
  *              depends on the compute-unit count of the current device: ask on the device the
- *              call will run on)
+ *              call will run on).  With that many bytes the call cuts the rows as it finds best.  A
+ *              smaller workspace is accepted while it holds the ranges of a plainer rule (about two
+ *              workgroups per compute unit, ranges of 512 to 4096 rows, up to 8192 where those fit
+ *              the chip at once; none at all if that is one range), and gets those ranges, which can
+ *              be slower; below that RAP_ERR_WORKSPACE.  So the cut, and with it the order of the
+ *              fp32 sums, depends on shape, max_seq_len, tuning, device and on whether the workspace
+ *              holds the queried size, and on nothing else.  No cut needs more than
+ *              RAP_STATIC_SCRATCH_BYTES where the plainer rule's does not.
  * Cache rows at or beyond seq_lens[b] are never used in the result, whatever bits they hold.
+ * An output row whose attended rows or query hold a NaN, or whose score overflows, is stored as zeros
+ * where that makes its sum a NaN; a row range none of whose scores is a number counts as empty.
+ * rap_prefill_attn shows such rows as NaN.
  */
 rap_status_t rap_decode_attn(const rap_shape_t* shape, const void* q,
                              const void* k_cache, const void* v_cache,
@@ -223,6 +236,7 @@ rap_status_t rap_rope_queries(const rap_shape_t* shape, int32_t n_new, const voi
  *   k_cache, v_cache, seq_lens, max_seq_len, scale      as for rap_decode_attn
  *   out       dev  fp32  [batch, n_new, n_q_heads, d_v] every row written; p < 0 (a sequence
  *                                                        shorter than n_new) gives a zero row
+ * A NaN in a query row or in a row it attends, or a score that overflows, makes that output row NaN.
  * No workspace: a workgroup owns a block of query tokens and walks the rows they see.
  * Errors as rap_decode_attn; n_new < 0 is RAP_ERR_SHAPE, n_new == 0 returns RAP_OK at once.
  */
@@ -425,7 +439,8 @@ rap_status_t rap_prefill_attn_ex(const rap_shape_t* shape, const rap_kv_cache_t*
  * shape, n_new and max_seq_len alone: rap_prefill_attn_split_workspace_bytes returns the bytes
  * needed, 0 when the launch is not cut (then workspace may be NULL and the call is
  * rap_prefill_attn_ex).  A missing, misaligned (256 bytes) or too small workspace is
- * RAP_ERR_WORKSPACE.  Results equal those of rap_prefill_attn_ex up to fp32 rounding. */
+ * RAP_ERR_WORKSPACE.  Results equal those of rap_prefill_attn_ex up to fp32 rounding; where the launch
+ * is cut, rows that the former makes NaN come out as rap_decode_attn has them. */
 size_t rap_prefill_attn_split_workspace_bytes(const rap_shape_t* shape, int32_t n_new, int64_t max_seq_len);
 rap_status_t rap_prefill_attn_split(const rap_shape_t* shape, const rap_kv_cache_t* cache, int32_t n_new,
                                     const void* q, const int32_t* seq_lens, int64_t max_seq_len,
@@ -441,8 +456,9 @@ rap_status_t rap_prefill_attn_split(const rap_shape_t* shape, const rap_kv_cache
  * side by side through the matrix instruction: that product must not exceed 16, else
  * RAP_ERR_UNSUPPORTED (use rap_prefill_attn_ex).  n_tok = 1 is rap_decode_attn over `cache`.
  *   q   dev bf16 [batch, n_tok, n_q_heads, d_k] rotated;  out dev fp32 [batch, n_tok, n_q_heads, d_v]
- *   workspace: at least n_tok * rap_decode_attn_workspace_bytes(shape, max_seq_len, tuning) bytes,
- *   256-byte aligned, always needed when n_tok > 1; tuning->kernel must be 0 or 2.
+ *   workspace: n_tok * rap_decode_attn_workspace_bytes(shape, max_seq_len, tuning) bytes or more,
+ *   256-byte aligned, always needed when n_tok > 1 (a smaller one as for rap_decode_attn);
+ *   tuning->kernel must be 0 or 2.
  * Everything else as in rap_decode_attn / rap_decode_step_ex; the caches are only read. */
 rap_status_t rap_decode_attn_multi(const rap_shape_t* shape, const rap_kv_cache_t* cache, int32_t n_tok,
                                    const void* q, const int32_t* seq_lens, int64_t max_seq_len,

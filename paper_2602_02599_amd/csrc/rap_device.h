@@ -157,11 +157,16 @@ struct PrefillArgs {
 struct PrefillPlan {
   int tok_per_wg, n_qblk, n_ksplit, tiles_per_split;
 };
-// The prefill kernel's sizes: wavefronts of a workgroup, keys of a staged tile, blocks of 16 query
-// columns per wavefront (four where the registers hold their accumulators, three at d_k > 96 or
-// d_v > 96), and the pitches of a tile's rows in LDS (K: 16 bytes past a multiple of 64, V: an odd
-// multiple of 32 bytes, so that neither kind of read meets its own banks).  The plan, the kernel
-// and the launch all go by these.
+// The prefill kernel's sizes: wavefronts of a workgroup, blocks of 16 query columns per wavefront, and
+// the pitches of a tile's rows in LDS (K: 16 bytes past a multiple of 64, V: an odd multiple of 32
+// bytes, so that neither kind of read meets its own banks).  The plan, the kernel and the launch all go
+// by these.  Four blocks where the registers hold their accumulators, three at d_k > 96 or d_v > 96.
+// With d_v above 80 and three score steps the accumulators fit but not all that goes with them: odd
+// rows and codes, which pass through registers, spill 36 to 64 bytes per lane, even rows without a spare
+// channel 20 (codes at d_v = 80: 12, odd rows at d_k and d_v above 112, three blocks: 28).  Four
+// blocks are still the faster: 8 x 8192 tokens, 32/8 heads, four and three blocks: codes 90/90 4.32 and 4.45
+// ms, 90/96 4.37 and 4.47, 90/89 4.30 and 4.46, 90/80 4.04 and 4.21; bf16 90/89 4.31 and 4.58, 90/96 4.28
+// and 4.33, 90/90 (no spill) 4.24 and 4.30.
 constexpr int kPrefillWaves = 4;
 enum { kTilesDirect = 0, kTilesOddV = 1, kTilesCodes = 2 };   // bf16 rows of even width, odd V rows, one-byte codes
 constexpr int prefill_k_pitch(int k_steps) { return 64 * k_steps + 16; }
