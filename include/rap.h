@@ -122,8 +122,8 @@ rap_status_t rap_rope_append(const rap_shape_t* shape, int32_t n_new,
 /* Bytes of device scratch for rap_decode_attn over sequences up to max_seq_len rows with the given
  * tuning (NULL = auto): one slot of d_v + 2 floats per query row and row range, and one more per query
  * row.  13 MB for 64 sequences of 65536 rows with 32 query heads and d_v = 90; it grows with batch,
- * query heads and ranges.  An array sized for the largest batch and the longest sequence serves all
- * smaller ones.  Returns 0 for an invalid shape. */
+ * query heads and ranges.  An array sized for the largest batch and the longest sequence of otherwise
+ * the same shape and tuning is accepted for all smaller ones.  Returns 0 for an invalid shape. */
 size_t rap_decode_attn_workspace_bytes(const rap_shape_t* shape, int64_t max_seq_len,
                                        const rap_tuning_t* tuning);
 

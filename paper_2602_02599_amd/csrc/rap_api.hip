@@ -80,10 +80,13 @@ int device_cus() {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Bytes of the partials of n_split ranges (and the extra slot): accumulators, then (reference, sum).
+// Bytes of that many partials: accumulators, then (reference, sum); and of those of n_split ranges (with
+// the extra slot).
+size_t slot_bytes(size_t slots, int d_v) {
+  return align_up(slots * d_v * sizeof(float), 256) + align_up(slots * 2 * sizeof(float), 256) + 256;
+}
 size_t partial_bytes(const rap_shape_t* s, int n_split, int n_tok) {
-  const size_t slots = static_cast<size_t>(s->batch) * n_tok * s->n_q_heads * (n_split + 1);
-  return align_up(slots * s->d_v * sizeof(float), 256) + align_up(slots * 2 * sizeof(float), 256) + 256;
+  return slot_bytes(static_cast<size_t>(s->batch) * n_tok * s->n_q_heads * (n_split + 1), s->d_v);
 }
 
 int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap::kSplitQuantum * rap::kSplitQuantum; }
@@ -195,6 +198,15 @@ size_t part_acc_bytes(const rap_shape_t* s, const Plan& p, int n_tok = 1) {
   return align_up(static_cast<size_t>(s->batch) * n_tok * s->n_q_heads * (p.n_split + 1) * s->d_v * sizeof(float), 256);
 }
 size_t workspace_need(const rap_shape_t* s, const Plan& p, int n_tok = 1) { return partial_bytes(s, p.n_split, n_tok); }
+
+// What one call can use: the plan's partials, no less than the plain rule's, which every call has to
+// bring; 0 for arguments that no call accepts.
+size_t call_workspace_bytes(const rap_shape_t* shape, int64_t max_seq_len, const rap_tuning_t* tuning) {
+  Plan p, base;
+  if (check_shape(shape) != RAP_OK || max_seq_len < 1 || max_seq_len > shape->cache_cap) return 0;
+  if (make_plan(shape, max_seq_len, tuning, &p) != RAP_OK || make_plan(shape, max_seq_len, tuning, &base, true) != RAP_OK) return 0;
+  return std::max(workspace_need(shape, p), workspace_need(shape, base));
+}
 
 // page_rows a power of two in [32, 65536], table present, logical capacity consistent
 rap_status_t check_paging(const rap_shape_t* s, const rap_paging_t* pg, int* shift) {
@@ -716,14 +728,15 @@ rap_status_t rap_rope_queries(const rap_shape_t* shape, int32_t n_new, const voi
 }
 
 size_t rap_decode_attn_workspace_bytes(const rap_shape_t* shape, int64_t max_seq_len, const rap_tuning_t* tuning) {
-  if (check_shape(shape) != RAP_OK || max_seq_len < 1 || max_seq_len > shape->cache_cap) return 0;
-  Plan p;
-  if (make_plan(shape, max_seq_len, tuning, &p) != RAP_OK) return 0;
-  // no less than the plain rule's, which every call has to bring: an array sized for the largest
-  // batch then also serves smaller ones whose plan has more ranges (32 x 1024 rows: whole; 31: two)
-  Plan base;
-  make_plan(shape, max_seq_len, tuning, &base, true);
-  return std::max(workspace_need(shape, p), workspace_need(shape, base));
+  const size_t need = call_workspace_bytes(shape, max_seq_len, tuning);
+  if (need == 0 || (tuning && tuning->rows_per_split != 0)) return need;
+  // The array also serves smaller batches and shorter sequences, which the plain rule may cut into
+  // more ranges (32 x 2200 rows: two, 33: one): a slab then has at most two ranges per compute unit's
+  // share, none shorter than 512 rows, or as many as 4096 rows give it.
+  const int64_t b = shape->batch, cuts = 2LL * device_cus() / shape->n_kv_heads;
+  const int64_t by_512 = b * ((max_seq_len + 511) / 512), by_4096 = b * ((max_seq_len + 4095) / 4096);
+  const int64_t ranges = std::max(std::min(cuts, by_512), by_4096);
+  return std::max(need, slot_bytes(static_cast<size_t>(ranges + b) * shape->n_q_heads, shape->d_v));
 }
 
 rap_status_t rap_decode_attn(const rap_shape_t* shape, const void* q, const void* k_cache, const void* v_cache,
@@ -760,7 +773,7 @@ rap_status_t rap_decode_attn_static(const rap_shape_t* shape, const void* q, con
   r.tuning = tuning;
   r.stream = stream;
   // an invalid shape, length or tuning gives 0 here and its own error from decode_impl below
-  const size_t need = rap_decode_attn_workspace_bytes(shape, max_seq_len, tuning);
+  const size_t need = call_workspace_bytes(shape, max_seq_len, tuning);
   if (need > RAP_STATIC_SCRATCH_BYTES) return RAP_ERR_STATIC_LIMIT;
   if (need > 0 && shape->batch > 0) {
     void* ptr = nullptr;

@@ -221,16 +221,31 @@ def test_missing_library_fails_loudly(tmp_path):
         pkg.Rap(str(tmp_path / "librap.so"))
 
 
-def _ranges(rap, need, batch, n_q, d_v):
-    """Ranges whose partials (accumulators, then reference and sum, one slot spare) fill `need` bytes."""
+def _slots_bytes(slots, d_v):
+    """Accumulators, then reference and sum."""
     up = lambda x: (x + 255) // 256 * 256
-    n = [n for n in range(1, 600) if up(batch * n_q * (n + 1) * d_v * 4) + up(batch * n_q * (n + 1) * 8) + 256 == need]
-    assert len(n) == 1, need
-    return n[0]
+    return up(slots * d_v * 4) + up(slots * 8) + 256
 
 
-# sequences, longest, query heads, d_v -> ranges of the plan, of the plain rule (two workgroups per compute
-# unit, ranges of 512 to 4096 rows, up to 8192 where that avoids a partly filled second round), 8 KV heads
+def _plain_ranges(batch, n_kv, ctx, d_k):
+    """The plain rule: two workgroups per compute unit, ranges of 512 to 4096 rows, up to 8192 where that
+    avoids a partly filled second round."""
+    slabs, div = batch * n_kv, lambda a, b: -(-a // b)
+    k0 = max(512 // slabs, 1)
+    halves = div(div(ctx, k0), 128) * 128
+    r = min(max(halves, 512), 4096)
+    places = 256 * (3 if d_k <= 96 else 2)
+    if places < slabs * div(ctx, r) < 2 * places and halves <= 8192:
+        r = halves
+    return div(ctx, r)
+
+
+def _array_slots(batch, n_kv, n_q, ctx):
+    """Slots that serve the plain rule at any smaller batch and length."""
+    return (max(min(512 // n_kv, batch * -(-ctx // 512)), batch * -(-ctx // 4096)) + batch) * n_q
+
+
+# sequences, longest, query heads, d_v -> ranges of the plan, of the plain rule, 8 KV heads
 @pytest.mark.parametrize("batch,ctx,n_q,d_v,plan,plain", [
     (1, 512, 32, 90, 4, 1), (1, 2048, 32, 90, 16, 4), (1, 8192, 32, 90, 32, 16), (24, 8192, 32, 90, 4, 2), (40, 4096, 32, 90, 4, 1),
     (64, 16384, 32, 90, 8, 4), (4, 131072, 32, 64, 16, 16), (32, 1024, 32, 90, 1, 2), (16, 512, 32, 90, 1, 1),
@@ -238,7 +253,22 @@ def _ranges(rap, need, batch, n_q, d_v):
     (48, 2200, 32, 90, 1, 1), (48, 4096, 32, 90, 4, 1),
     (64, 16384, 64, 128, 4, 4)])                                  # the last: partials of 8 ranges would not fit the static array
 def test_split_plan_ranges(rap, batch, ctx, n_q, d_v, plan, plain):
-    """The automatic plan's ranges through the size query, which returns the larger of the two rules."""
+    """The automatic plan's ranges through the size query, which returns what the larger of the two rules
+    needs, and no less than smaller batches and lengths may."""
+    assert _plain_ranges(batch, 8, ctx, 90) == plain
     shp = rap.shape(batch, n_q, 8, 128, 45, d_v, ctx, 5e5)
-    need = rap.rap_decode_attn_workspace_bytes(shp, ctx)
-    assert _ranges(rap, need, batch, n_q, d_v) == max(plan, plain)
+    slots = max(batch * n_q * (max(plan, plain) + 1), _array_slots(batch, 8, n_q, ctx))
+    assert rap.rap_decode_attn_workspace_bytes(shp, ctx) == _slots_bytes(slots, d_v)
+
+
+@pytest.mark.parametrize("n_kv,pairs", [(1, 45), (2, 45), (8, 45), (8, 64), (5, 32)])
+def test_workspace_of_the_largest_call_serves_smaller_ones(rap, n_kv, pairs):
+    """What the query returns holds the plain rule's ranges (what a call has to bring) at every smaller
+    batch and length: 32 sequences of 2200 rows have two ranges, 33 one."""
+    lengths = [130, 500, 700, 1024, 1500, 2200, 3000, 4096, 4100, 5000, 8192, 12000, 20480, 50000]
+    worst = {}                                                    # slots the plain rule needs up to (batch, length)
+    for i, ctx in enumerate(lengths):
+        for b in range(1, 131):
+            worst[b, i] = max(b * (_plain_ranges(b, n_kv, ctx, 2 * pairs) + 1), worst.get((b - 1, i), 0), worst.get((b, i - 1), 0))
+            shp = rap.shape(b, 4 * n_kv, n_kv, 128, pairs, 90, 65536, 5e5)
+            assert rap.rap_decode_attn_workspace_bytes(shp, ctx) >= _slots_bytes(worst[b, i] * 4 * n_kv, 90), (b, ctx)

@@ -165,5 +165,5 @@ def test_plan_and_smaller_workspace(rap, B, ctx, plan, plain):
         elif g is not None:                                    # a single range stores the output itself
             assert bool((w == 0xFF).all()), "no ranges expected"
     if plain > 1:                                              # one byte less is refused
-        assert ws.numel() == max(_slots_bytes(B, Hq, dv, plan), small.bytes.numel())
+        assert ws.numel() >= max(_slots_bytes(B, Hq, dv, plan), small.bytes.numel())
         assert rap.rap_decode_attn(shp, q, kdev, vdev, sl, ctx, out, scale, small.bytes[:-1], check=False) == 5
