@@ -166,6 +166,37 @@ __host__ __device__ __forceinline__ void decode_place(int wg, int n_split, int n
   *h = (wg - seq_range * n_kv + (few ? nth + *b : 0)) % n_kv;
 }
 
+// Which query block, slab (sequence and KV head) and key range workgroup `wg` of a prefill launch takes.
+// Hardware places workgroup L on XCD L mod 8, each with an L2 of its own, and all query blocks of a slab
+// read the same K and V rows: with a multiple of 8 slabs, all workgroups of a slab go to one XCD, which
+// works on `group` of its slabs side by side, the heaviest query blocks (the last tokens, which see the
+// most rows) of all of them first.  Else the heaviest blocks of all slabs come first.
+// One slab after the other keeps the fewest rows in use, but a launch of few rounds then ends with the heavy
+// blocks of its last slabs; all slabs at once end evenly, but outgrow the caches where they are long.
+// One after the other / 8 at a time / all (n = context; 32/8 heads): d = 90, 8 x 1024 131 / 106 / 106 us, 8 x
+// 2048 350 / 299 / 297, 16 x 4096 2308 / 2195 / 2179, 8 x 8192 4202 / 4152, 16 x 8192 8737 / 8682 / 8839; 8
+// query heads, 8 x 2395 183 / 125 / 125; codes 8 x 2048 377 / 316 / 315.  Wide rows (three column blocks)
+// with 4 / 8 / all: d = 128, 8 x 2048 426 one after the other, 411 / 403 / 402; 32 x 512 187, 181 / 187 / 197; 16 x
+// 8192 11.4 ms, 11.1 / 11.5 / 12.2; 32 x 4096 6.32 ms, 5.89 / 6.01 / 6.87.
+__host__ __device__ __forceinline__ void prefill_place(int wg, int n_qblk, int slabs, int n_ksplit, int group, int* qb, int* slab, int* ks) {
+  int r;
+  if ((slabs & 7) == 0) {
+    const int x = wg >> 3, own = slabs >> 3, per_slab = n_qblk * n_ksplit;
+    const int first = x / per_slab / group * group;                              // of this XCD's slabs
+    const int level = (own - first < group ? own - first : group) * n_ksplit;    // workgroups per query block number
+    r = x - first * per_slab;
+    *qb = n_qblk - 1 - r / level;
+    r = r % level;
+    *slab = (first + r / n_ksplit) * 8 + (wg & 7);
+    *ks = r % n_ksplit;
+  } else {
+    *ks = wg % n_ksplit;
+    r = wg / n_ksplit;
+    *slab = r % slabs;
+    *qb = n_qblk - 1 - r / slabs;
+  }
+}
+
 // Which bytes of a cache tile the prefill kernel loads.  A tile is up to kPrefillTile rows of `pitch`
 // bytes, fetched in 16-byte pieces from the start of every row; piece c of a tile is piece
 // c % per_row of row c / per_row.  With `repeat` (loads straight into LDS, where per_row counts the

@@ -172,28 +172,10 @@ enum { kTilesDirect = 0, kTilesOddV = 1, kTilesCodes = 2 };   // bf16 rows of ev
 constexpr int prefill_k_pitch(int k_steps) { return 64 * k_steps + 16; }
 constexpr int prefill_v_pitch(int channel_tiles) { return 32 * (channel_tiles | 1); }
 constexpr int prefill_blocks(int k_steps, int channel_tiles) { return k_steps > 3 || channel_tiles > 6 ? 3 : 4; }
+// slabs an XCD works on side by side (prefill_place)
+constexpr int prefill_slabs(int k_steps, int channel_tiles) { return prefill_blocks(k_steps, channel_tiles) == 3 ? 4 : 8; }
 constexpr int prefill_tokens_per_wg(int k_steps, int channel_tiles, int group) {
   return 16 * kPrefillWaves * prefill_blocks(k_steps, channel_tiles) / group;
-}
-// Which query block, slab (sequence and KV head) and key range workgroup `wg` takes.  Hardware
-// places workgroup L on XCD L mod 8, each with an L2 of its own, and all query blocks of a slab
-// read the same K and V rows: with a multiple of 8 slabs, an XCD takes one slab after the other.
-// Within a slab the heaviest query blocks (the last tokens, which see the most rows) come first.
-__host__ __device__ __forceinline__ void prefill_place(int wg, int n_qblk, int slabs, int n_ksplit, int* qb, int* slab, int* ks) {
-  const int per_slab = n_qblk * n_ksplit;
-  int r;
-  if ((slabs & 7) == 0) {
-    const int x = wg >> 3;
-    *slab = (x / per_slab) * 8 + (wg & 7);
-    r = x % per_slab;
-    *ks = r % n_ksplit;
-    *qb = n_qblk - 1 - r / n_ksplit;
-  } else {
-    *ks = wg % n_ksplit;
-    r = wg / n_ksplit;
-    *slab = r % slabs;
-    *qb = n_qblk - 1 - r / slabs;
-  }
 }
 PrefillPlan prefill_plan(int batch, int n_kv, int group, int d_k, int d_v, int n_new, int max_len);
 

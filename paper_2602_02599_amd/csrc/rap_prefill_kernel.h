@@ -136,7 +136,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const int lg = lane >> 4;
 
   int qb, slab_id, ks;
-  prefill_place(static_cast<int>(blockIdx.x), a.n_qblk, a.n_kv * a.batch, a.n_ksplit > 1 ? a.n_ksplit : 1, &qb, &slab_id, &ks);
+  prefill_place(static_cast<int>(blockIdx.x), a.n_qblk, a.n_kv * a.batch, a.n_ksplit > 1 ? a.n_ksplit : 1, prefill_slabs(KS, CT),
+                &qb, &slab_id, &ks);
   const int h = slab_id % a.n_kv;
   const int b = slab_id / a.n_kv;
 

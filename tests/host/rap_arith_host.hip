@@ -20,6 +20,9 @@
 //                               sequences lie, at least; exit status 1 if placed wrongly or on fewer than 4
 //   rap_arith_host place-rotated  the same with every number of ranges rotated by the sequence (a
 //                               planted mistake: odd numbers then pile up)
+//   rap_arith_host prefill-place -> text, one line per (query blocks, slabs, key ranges, group): whether every
+//                               (block, slab, range) is placed once, on how many XCDs a slab lies, and how
+//                               often a query block follows a lighter one within a group of slabs
 //   rap_arith_host pieceplan -> text, one line per (kind, element size, width): what the prefill
 //                               kernel's tile loads touch, in the middle of a cache and at its end; exit
 //                               status 1 if any leaves the cache, or misses a byte of a readable row
@@ -77,6 +80,34 @@ int loadplan(bool trim_one_only) {
       }
     }
   }
+  return bad;
+}
+
+int prefill_placed() {
+  int bad = 0;
+  for (int slabs : {1, 3, 8, 10, 16, 24, 64, 72, 128})
+    for (int n_qblk : {1, 2, 5, 16})
+      for (int n_ksplit : {1, 2, 5})
+        for (int group : {1, 4, 8}) {
+          const int n = slabs * n_qblk * n_ksplit;
+          std::vector<int> hit(n, 0), last(static_cast<size_t>(8) * slabs, n_qblk), xcd(slabs, 0);
+          int lighter = 0, wrong = 0;
+          for (int wg = 0; wg < n; ++wg) {
+            int qb, slab, ks;
+            rap::prefill_place(wg, n_qblk, slabs, n_ksplit, group, &qb, &slab, &ks);
+            if (qb < 0 || qb >= n_qblk || slab < 0 || slab >= slabs || ks < 0 || ks >= n_ksplit) return 1000000;
+            hit[(slab * n_qblk + qb) * n_ksplit + ks] += 1;
+            xcd[slab] |= 1 << (wg & 7);
+            int& before = last[(slabs & 7) == 0 ? (wg & 7) * slabs + (slab >> 3) / group : 0];   // the group's blocks so far
+            lighter += qb > before;
+            before = qb;
+          }
+          for (int x : hit) wrong += x != 1;
+          int spread = 1;
+          for (int x : xcd) spread = __builtin_popcount(x) > spread ? __builtin_popcount(x) : spread;
+          printf("blocks=%d slabs=%d ranges=%d group=%d wrong=%d xcds=%d lighter=%d\n", n_qblk, slabs, n_ksplit, group, wrong, spread, lighter);
+          bad += wrong != 0 || lighter != 0 || ((slabs & 7) == 0 && spread != 1);
+        }
   return bad;
 }
 
@@ -150,11 +181,12 @@ int pieceplan(bool read_whole) {
 
 int main(int argc, char** argv) {
   if (argc != 2) {
-    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated\n");
+    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|prefill-place\n");
     return 2;
   }
   if (strcmp(argv[1], "loadplan") == 0) return loadplan(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "loadplan-trim1") == 0) return loadplan(true) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "prefill-place") == 0) return prefill_placed() == 0 ? 0 : 1;
   if (strcmp(argv[1], "place") == 0) return place(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "place-rotated") == 0) return place(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "pieceplan") == 0) return pieceplan(false) == 0 ? 0 : 1;
