@@ -106,8 +106,8 @@ int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap:
 //    out even are better: 24 x 8192 (192 slabs) 102 us with 2 ranges per slab, 95 with 4; 40 x 4096
 //    (320 slabs) 92 us with one, 80 with 4.  With less left over they are not: 18 x 8192 (144 slabs)
 //    72 us with 3 ranges, 75 with 7; 14 x 9738 at 16 query rows per slab 74 us with 4, 78 with 9.
-//    From 257 slabs on, where rows would be whole, three or more ranges of 768 rows or more: two are
-//    good for equal lengths only (whole / 2 / 3 ranges: 40 x 3000 69 / 65 / 63 us, ragged 45 / 49 / 42;
+//    From 257 slabs on, where rows would be whole, three or more ranges (from 2048 rows): two are good
+//    for equal lengths only (whole / 2 / 3 ranges: 40 x 3000 69 / 65 / 63 us, ragged 45 / 49 / 42;
 //    fp8, d = 128, 48 x 3000 66 / 60 / 68, ragged 57 / 68 / 53; 44 x 2600 67 / 64 / 65, ragged 49 / 49 / 41).
 //  * Long ranges save a little on equal lengths and cost a lot on ragged ones, whose workgroups are
 //    then few and unequal: an eighth of max_seq_len, no less than 2048 and no more than 4096 rows.
@@ -173,8 +173,8 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
     };
     int64_t k = k0;
     if (evenness(k0) < 0.78) {
-      const int64_t least = k0 == 1 ? 768 : 1024;
-      for (int64_t c = k0 == 1 ? 3 : k0 + 1; c <= 4 * k0 && max_seq_len >= least * c; ++c)
+      auto long_enough = [&](int64_t c) { return max_seq_len >= (k0 > 1 ? 1024 * c : c == 3 ? 2048 : 768 * c); };
+      for (int64_t c = k0 == 1 ? 3 : k0 + 1; c <= 4 * k0 && long_enough(c); ++c)
         if (evenness(c) > evenness(k) + 0.02) k = c;
     }
     const int64_t eighth = round_to_quantum(max_seq_len / 8);

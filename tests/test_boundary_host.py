@@ -250,7 +250,7 @@ def _array_slots(batch, n_kv, n_q, ctx):
     (1, 512, 32, 90, 4, 1), (1, 2048, 32, 90, 16, 4), (1, 8192, 32, 90, 32, 16), (24, 8192, 32, 90, 4, 2), (40, 4096, 32, 90, 4, 1),
     (64, 16384, 32, 90, 8, 4), (4, 131072, 32, 64, 16, 16), (32, 1024, 32, 90, 1, 2), (16, 512, 32, 90, 1, 1),
     (64, 4096, 32, 90, 1, 1), (128, 4096, 32, 90, 1, 1), (64, 5000, 32, 90, 3, 1), (40, 3000, 32, 90, 3, 1),
-    (48, 2200, 32, 90, 1, 1), (48, 4096, 32, 90, 4, 1),
+    (48, 2040, 32, 90, 1, 1), (40, 2200, 32, 90, 3, 1), (48, 4096, 32, 90, 4, 1),
     (64, 16384, 64, 128, 4, 4)])                                  # the last: partials of 8 ranges would not fit the static array
 def test_split_plan_ranges(rap, batch, ctx, n_q, d_v, plan, plain):
     """The automatic plan's ranges through the size query, which returns what the larger of the two rules
