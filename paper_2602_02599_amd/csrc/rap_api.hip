@@ -18,6 +18,7 @@ hipError_t launch_decode_valu(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_decode_mfma(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_merge(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t stream);
+hipError_t launch_prefill_merge(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_stream_read(const void* src, size_t bytes, void* sink, hipStream_t stream);
 hipError_t launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 hipError_t launch_validate(const int32_t* pos, long long n_pos, long long cap, const int32_t* keep, int n_kv, int n_pairs,
@@ -574,28 +575,7 @@ rap_status_t prefill_impl(const rap_shape_t* shape, const rap_paging_t* paging, 
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (rap::launch_prefill(a, s) != hipSuccess) return RAP_ERR_HIP;
-  if (plan.n_ksplit > 1) {
-    // the combining kernel of the decode path, one block per (b, token, query head), every slot read
-    rap::DecodeArgs m;
-    memset(&m, 0, sizeof(m));
-    m.seq_lens = seq_lens;
-    m.out = a.out;
-    m.part_acc = a.part_acc;
-    m.part_ml = a.part_ml;
-    m.batch = a.batch;
-    m.n_tok = n_new;
-    m.n_q = a.n_q;
-    m.n_kv = a.n_kv;
-    m.group = a.group;
-    m.d_k = a.d_k;
-    m.d_v = a.d_v;
-    m.max_len = a.max_len;
-    m.rows_per_split = plan.tiles_per_split * 64;
-    m.n_split = plan.n_ksplit;
-    m.n_slots = plan.n_ksplit;
-    m.all_slots = 1;
-    if (rap::launch_merge(m, s) != hipSuccess) return RAP_ERR_HIP;
-  }
+  if (plan.n_ksplit > 1 && rap::launch_prefill_merge(a, s) != hipSuccess) return RAP_ERR_HIP;
   return RAP_OK;
 }
 

@@ -110,7 +110,6 @@ struct DecodeArgs {
   // matrix instruction; the causal part among the tokens themselves is added by the combining
   // kernel, which always runs.  "Query row" below is then (b * n_tok + token) * H_q + head.
   int32_t n_tok;
-  int32_t all_slots;        // combining kernel: every slot of every query row was written (prefill key ranges)
   int32_t group_inv16;      // ceil(65536 / group): (c * group_inv16) >> 16 == c / group for c < 16
   float* out;          // [B, H_q, d_v]
   float* part_acc;     // [query rows, n_slots, d_v]   un-normalised accumulators
@@ -149,6 +148,13 @@ struct PrefillArgs {
   int32_t tiles_per_split;
   float* part_acc;          // [B * n_new * H_q, n_ksplit, d_v] un-normalised accumulators
   float* part_ml;           // [B * n_new * H_q, n_ksplit, 2]   (reference in log2 units, sum)
+};
+
+struct PrefillMergeArgs {
+  const float* part_acc;
+  const float* part_ml;
+  float* out;
+  int32_t rows, d_v, n_ksplit;   // query rows, batch * n_new * H_q
 };
 
 // Key ranges per query block of a prefill launch, a function of the shape alone: none while the

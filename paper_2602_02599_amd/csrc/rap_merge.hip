@@ -26,6 +26,7 @@ namespace rap {
 
 constexpr int kMaxTok = 16;
 constexpr int kMergeSlots = 8;                     // slots a thread has in flight
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // MT: 0 for one query token, else an upper bound of n_tok, to which the loops over new tokens are
 // unrolled: four, eight or sixteen.  Unrolled to sixteen, five to eight tokens cost 2 to 4 us more (attention
@@ -135,12 +136,9 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
       }
     }
   }
-  int n = a.n_split;                               // ranges that hold rows (prefill key ranges: every slot was written)
-  if (!a.all_slots) {
-    if (len > 0 && t_new == len - 1) len -= 1;     // the first stage stopped before the new token's row
-    if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;   // or before the new tokens' rows
-    n = (len + a.rows_per_split - 1) / a.rows_per_split;
-  }
+  if (len > 0 && t_new == len - 1) len -= 1;       // the first stage stopped before the new token's row
+  if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;     // or before the new tokens' rows
+  const int n = (len + a.rows_per_split - 1) / a.rows_per_split;   // ranges that hold rows
   float mstar = m_tok, den = 0.f, num = 0.f;
   if (m_tok > -INFINITY) {
     den = l_tok;
@@ -196,6 +194,106 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
   if (live) a.out[hq * a.d_v + c] = den > 0.f ? num / den : 0.f;
 }
 
+// The same for a prefill launch in key ranges (every slot of every query row is written there), whose query rows are
+// many and whose ranges are few, so that reading the partials is what bounds it: 32 lanes per query row, four
+// channels per lane in 16-byte loads (where d_v is no multiple of four the last lane repeats channels of its
+// neighbour), eight rows per workgroup.  Up to eight ranges are one round trip; more are shared by 2, 4 or 8 sets
+// of lanes, which meet in LDS.  One workgroup of 128 threads per query row, as above, spends its time on starting
+// workgroups: 72336 rows of 2 ranges, d_v = 56, 42.9 us, so 17.2; 16384 rows of 8, d_v = 90 (48 MB), 14.9 and 9.5;
+// 1800 rows of 10, d_v = 74, 4.7 and 4.0.
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_dw;
+template <int GRP>
+__global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) {
+  constexpr int ROWS = 8 / GRP;                    // per workgroup
+  const int lane = threadIdx.x & 31, set = threadIdx.x >> 5;
+  const int grp = set % GRP;
+  const int row = static_cast<int>(blockIdx.x) * ROWS + set / GRP;
+  const bool live = row < a.rows;
+  const int n = live ? a.n_ksplit : 0;
+  const int dv = a.d_v;
+  const int c = dv < 4 ? 0 : (4 * lane < dv - 4 ? 4 * lane : dv - 4);
+  const bool has = 4 * lane < dv;
+  const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + static_cast<long long>(row) * a.n_ksplit;
+  const float* acc = a.part_acc + static_cast<long long>(row) * a.n_ksplit * dv + c;
+  float mstar = -INFINITY, den = 0.f;
+  f32x4_dw num = {0.f, 0.f, 0.f, 0.f};
+  float m[kMergeSlots], l[kMergeSlots];
+  f32x4_dw v[kMergeSlots];
+  auto request = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < kMergeSlots; ++u) {
+      const bool have = s0 + u < n;
+      const float2 x = have ? ml[s0 + u] : make_float2(-INFINITY, 0.f);
+      m[u] = x.x;
+      l[u] = x.y;
+      v[u] = f32x4_dw{0.f, 0.f, 0.f, 0.f};
+      if (have && has) {
+        const float* p = acc + (s0 + u) * dv;
+        if (dv >= 4) {
+          v[u] = *reinterpret_cast<const f32x4_dw*>(p);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 3; ++e) v[u][e] = e < dv ? p[e] : 0.f;
+        }
+      }
+    }
+  };
+  for (int s0 = kMergeSlots * grp; s0 < n; s0 += kMergeSlots * GRP) {
+    request(s0);
+    float gmax = m[0];
+#pragma unroll
+    for (int u = 1; u < kMergeSlots; ++u) gmax = fmaxf(gmax, m[u]);
+    if (gmax > mstar) {                            // the reference follows the running maximum
+      const float r = mstar > -INFINITY ? exp2f(mstar - gmax) : 0.f;
+      den *= r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] *= r;
+      mstar = gmax;
+    }
+#pragma unroll
+    for (int u = 0; u < kMergeSlots; ++u) {
+      const bool some = m[u] > -INFINITY;          // an empty range leaves only its reference and sum
+      const float w = some ? exp2f(m[u] - mstar) : 0.f;
+      den = fmaf(w, l[u], den);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] = fmaf(w, some ? v[u][e] : 0.f, num[e]);
+    }
+  }
+  if constexpr (GRP > 1) {
+    __shared__ float s_m[8], s_den[8];
+    __shared__ f32x4 s_num[8][32];
+    if (lane == 0) {
+      s_m[set] = mstar;
+      s_den[set] = den;
+    }
+    s_num[set][lane] = f32x4{num[0], num[1], num[2], num[3]};
+    __syncthreads();
+    if (grp != 0) return;
+#pragma unroll
+    for (int g = 1; g < GRP; ++g) mstar = fmaxf(mstar, s_m[set + g]);
+    den = 0.f;
+    num = f32x4_dw{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < GRP; ++g) {
+      const float w = s_m[set + g] > -INFINITY ? exp2f(s_m[set + g] - mstar) : 0.f;
+      den = fmaf(w, s_den[set + g], den);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] = fmaf(w, s_num[set + g][lane][e], num[e]);
+    }
+  }
+  if (!live || !has) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) num[e] = den > 0.f ? num[e] / den : 0.f;
+  float* dst = a.out + static_cast<long long>(row) * dv + c;
+  if (dv >= 4) {
+    *reinterpret_cast<f32x4_dw*>(dst) = num;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (e < dv) dst[e] = num[e];
+  }
+}
+
 namespace {
 
 template <int MT>
@@ -209,10 +307,27 @@ void launch_groups(const DecodeArgs& a, hipStream_t stream) {
   else hipLaunchKernelGGL((merge_kernel<MT, 8>), grid, dim3(1024), 0, stream, a);
 }
 
+template <int GRP>
+hipError_t launch_prefill_groups(const PrefillMergeArgs& a, long long rows, hipStream_t stream) {
+  const long long wgs = (rows * GRP + 7) / 8;
+  if (rows > 0x7fffffff - 8 || wgs * 256 >= (1ll << 32)) return hipErrorInvalidValue;     // fewer than 384 query blocks are cut
+  hipLaunchKernelGGL((prefill_merge_kernel<GRP>), dim3(static_cast<unsigned>(wgs)), dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
+hipError_t launch_prefill_merge(const PrefillArgs& p, hipStream_t stream) {
+  const long long rows = static_cast<long long>(p.batch) * p.n_new * p.n_q;
+  const PrefillMergeArgs a = {p.part_acc, p.part_ml, p.out, static_cast<int32_t>(rows), p.d_v, p.n_ksplit};
+  if (p.n_ksplit <= kMergeSlots) return launch_prefill_groups<1>(a, rows, stream);
+  if (p.n_ksplit <= 2 * kMergeSlots) return launch_prefill_groups<2>(a, rows, stream);
+  if (p.n_ksplit <= 4 * kMergeSlots) return launch_prefill_groups<4>(a, rows, stream);
+  return launch_prefill_groups<8>(a, rows, stream);
+}
+
 hipError_t launch_merge(const DecodeArgs& a, hipStream_t stream) {
-  if (a.n_tok <= 1 || a.all_slots) launch_groups<0>(a, stream);
+  if (a.n_tok <= 1) launch_groups<0>(a, stream);
   else if (a.n_tok <= 4) launch_groups<4>(a, stream);
   else if (a.n_tok <= 8) launch_groups<8>(a, stream);
   else launch_groups<kMaxTok>(a, stream);

@@ -90,6 +90,29 @@ def test_range_counts(rap, n_split, n_tok):
     H.assert_attn_close(out.cpu().numpy(), O.prefill_attn_ref(qb, kd, vd, lens, scale), "%d ranges" % n_split)
 
 
+# one, two, four or eight sets of lanes per query row; channels in fours, with a last four that overlaps, fewer than four
+@pytest.mark.parametrize("rows,dv", [(2048, 90), (2049, 1), (4096, 3), (4100, 4), (8192, 5), (8200, 128), (16640, 127)])
+def test_prefill_range_counts(rap, rows, dv):
+    """A few tokens at the end of sequences in ranges of 256 rows, up to more ranges than the combining kernel reads
+    at once: a full sequence, one that leaves the last ranges empty, one shorter than the chunk (NaN in every slot)."""
+    P, Hq, Hkv, n_new, cap = 9, 3, 1, 5, (rows + 15) // 16 * 16
+    lens = np.asarray([rows, rows - rows // 3, 2], dtype=np.int64)
+    _say("prefill ranges rows=%d dv=%d" % (rows, dv))
+    rng = np.random.Generator(np.random.PCG64(1900 + rows))
+    kd, vd, kdev, vdev, _, _, _, _, _ = _caches(rap, rng, 3, Hkv, cap, P, dv, lens, False, 0)
+    qb = O.f64_to_bf16_bits_rne(rng.standard_normal((3, n_new, Hq, 2 * P)))
+    q, sl = I.from_bits(qb, DEV), torch.from_numpy(lens.astype(np.int32)).to(DEV)
+    shp, scale = rap.shape(3, Hq, Hkv, 128, P, dv, cap, 5e5), 0.25
+    need = rap.rap_prefill_attn_split_workspace_bytes(shp, n_new, rows)
+    gw, (go, out) = H.Guarded(need, DEV), H.guarded_out((3, n_new, Hq, dv), DEV)
+    gw.bytes.fill_(0xFF)
+    rap.rap_prefill_attn_split(shp, kdev, vdev, None, None, None, n_new, q, sl, rows, out, scale, gw.bytes)
+    torch.cuda.synchronize()
+    gw.check("workspace")
+    go.check("out")
+    H.assert_attn_close(out.cpu().numpy(), O.prefill_attn_ref(qb, kd, vd, lens, scale), "%d rows in ranges" % rows)
+
+
 @pytest.mark.parametrize("P,dv", [(16, 65), (5, 128), (17, 32), (30, 96), (32, 97), (40, 31), (48, 64), (45, 128), (49, 1), (64, 33), (56, 95)])
 def test_mx4_block_counts(rap, P, dv):
     """4-bit rows with every pairing of one to four K and V blocks, sequence lengths at the edges of the
