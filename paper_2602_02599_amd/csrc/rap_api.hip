@@ -497,15 +497,15 @@ bool live_call(const rap_shape_t* shape, int64_t max_seq_len) { return shape && 
 // Shared body of rap_prefill_attn, rap_prefill_attn_paged and rap_prefill_attn_ex (k_scale and
 // v_scale non-null: the caches hold E4M3 codes).
 // Workspace of the prefill attention with key ranges: partial accumulators [B * n_new * H_q,
-// n_ksplit, d_v] and (reference, sum) pairs, fp32, each block rounded up to 256 bytes; nothing
-// when the launch is not split.
-size_t prefill_part_acc_bytes(const rap_shape_t* s, int32_t n_new, const rap::PrefillPlan& p) {
-  return align_up(static_cast<size_t>(s->batch) * n_new * s->n_q_heads * p.n_ksplit * s->d_v * sizeof(float), 256);
+// ranges, d_v] and (reference, sum) pairs, fp32, each block rounded up to 256 bytes; nothing
+// when the launch is never split.  It has room for plan.slots ranges, of which a launch uses n_ksplit.
+size_t prefill_part_acc_bytes(const rap_shape_t* s, int32_t n_new, int ranges) {
+  return align_up(static_cast<size_t>(s->batch) * n_new * s->n_q_heads * ranges * s->d_v * sizeof(float), 256);
 }
 size_t prefill_workspace_need(const rap_shape_t* s, int32_t n_new, const rap::PrefillPlan& p) {
-  if (p.n_ksplit <= 1) return 0;
-  return prefill_part_acc_bytes(s, n_new, p) +
-         align_up(static_cast<size_t>(s->batch) * n_new * s->n_q_heads * p.n_ksplit * 2 * sizeof(float), 256) + 256;
+  if (p.slots <= 1) return 0;
+  return prefill_part_acc_bytes(s, n_new, p.slots) +
+         align_up(static_cast<size_t>(s->batch) * n_new * s->n_q_heads * p.slots * 2 * sizeof(float), 256) + 256;
 }
 rap::PrefillPlan prefill_plan_of(const rap_shape_t* s, int32_t n_new, int64_t max_seq_len) {
   return rap::prefill_plan(s->batch, s->n_kv_heads, s->n_q_heads / s->n_kv_heads, 2 * s->n_pairs, s->d_v, n_new,
@@ -535,8 +535,8 @@ rap_status_t prefill_impl(const rap_shape_t* shape, const rap_paging_t* paging, 
   if (misaligned(k_cache, 16) || misaligned(v_cache, 16) || misaligned(q, 4) || misaligned(out, 4)) return RAP_ERR_SHAPE;
   if (static_cast<int64_t>(shape->batch) * n_new > kInt32Max) return RAP_ERR_UNSUPPORTED;
   rap::PrefillPlan plan = prefill_plan_of(shape, n_new, max_seq_len);
-  if (!split) plan.n_ksplit = 1;
-  if (plan.n_ksplit > 1) {
+  if (!split) plan.slots = plan.n_ksplit = 1;
+  if (plan.slots > 1) {
     if (!workspace || workspace_bytes < prefill_workspace_need(shape, n_new, plan) || misaligned(workspace, 256))
       return RAP_ERR_WORKSPACE;
     if (static_cast<int64_t>(shape->batch) * n_new * shape->n_q_heads > kInt32Max) return RAP_ERR_UNSUPPORTED;
@@ -566,16 +566,23 @@ rap_status_t prefill_impl(const rap_shape_t* shape, const rap_paging_t* paging, 
     a.n_pages = paging->n_pages;
     a.max_pages = paging->max_pages;
   }
+  if (plan.slots > 1)
+    rap::prefill_cut_plan(&plan, a.n_kv * a.batch, a.group, a.d_k, a.d_v, n_new, a.max_len, a.order);
   a.n_ksplit = plan.n_ksplit;
+  a.as_combined = plan.slots > 1;
   if (plan.n_ksplit > 1) {
+    a.n_ranges = plan.n_ranges;
     a.tiles_per_split = plan.tiles_per_split;
     a.tok_per_wg = plan.tok_per_wg;
+    a.n_qblk = plan.n_qblk;
     a.part_acc = static_cast<float*>(workspace);
-    a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + prefill_part_acc_bytes(shape, n_new, plan));
+    a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + prefill_part_acc_bytes(shape, n_new, plan.n_ksplit));
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (rap::launch_prefill(a, s) != hipSuccess) return RAP_ERR_HIP;
-  if (plan.n_ksplit > 1 && rap::launch_prefill_merge(a, s) != hipSuccess) return RAP_ERR_HIP;
+  if (plan.n_ksplit > 1) {
+    if (rap::launch_prefill_merge(a, s) != hipSuccess) return RAP_ERR_HIP;
+  }
   return RAP_OK;
 }
 

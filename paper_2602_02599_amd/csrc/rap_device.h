@@ -122,6 +122,7 @@ struct DecodeArgs {
   float scale_log2e;   // softmax scale * log2(e): exponentials are taken as exp2
 };
 
+constexpr int kMaxOrdered = 128;
 struct PrefillArgs {
   const uint16_t* q;        // [B, n_new, H_q, d_k] rotated
   const uint16_t* k_cache;
@@ -141,27 +142,35 @@ struct PrefillArgs {
   int64_t cap;
   float scale_log2e;
   // Key ranges (n_ksplit > 1, for launches whose query blocks alone would not fill the chip): a
-  // query block is served by n_ksplit workgroups, each over tiles_per_split 64-row tiles of the
-  // rows it sees, which leave partials in the form of the decode kernel's (every slot of every
-  // query row is written, an empty range as reference -inf and sum 0); a combining launch follows.
+  // query block is served by up to n_ksplit workgroups, each over tiles_per_split 64-row tiles of the
+  // rows it sees (PrefillCut).  Where there are several they leave partials in the form of the decode kernel's
+  // (an empty range as reference -inf and sum 0); a combining launch follows.
   int32_t n_ksplit;
   int32_t tiles_per_split;
+  int32_t as_combined;      // the call may be cut: rows whose sum is not a number are zeros, as the combining launch leaves them
+  int32_t n_ranges;         // of a slab, over all its query blocks; not cut: the blocks, where all workgroups start together, else 0
+  uint32_t slab_inv;        // prefill_inv
+  // those from the longest to the shortest, where they are no more than this: query block, range << 9, and
+  // the top bit where the block has several
+  uint32_t order[kMaxOrdered];
   float* part_acc;          // [B * n_new * H_q, n_ksplit, d_v] un-normalised accumulators
   float* part_ml;           // [B * n_new * H_q, n_ksplit, 2]   (reference in log2 units, sum)
 };
-
 struct PrefillMergeArgs {
   const float* part_acc;
   const float* part_ml;
   float* out;
-  int32_t rows, d_v, n_ksplit;   // query rows, batch * n_new * H_q
+  PrefillCut cut;
+  int32_t batch, n_q, d_v, n_ksplit, tok0;   // tok0: the first token whose block has several ranges
 };
+__host__ __device__ __forceinline__ PrefillCut prefill_cut_of(const PrefillArgs& a) {
+  return PrefillCut{a.max_len, a.n_new, a.tok_per_wg, a.n_qblk, a.tiles_per_split};
+}
 
-// Key ranges per query block of a prefill launch, a function of the shape alone: none while the
-// query blocks number at least one and a half per CU or the context is short, else enough for
-// about 512 workgroups, none shorter than four tiles.
+// Key ranges of a prefill launch, a function of the shape alone.  `slots`: ranges per query row that the
+// workspace has to hold, 1 where the launch is never cut; the launch itself uses n_ksplit of them.
 struct PrefillPlan {
-  int tok_per_wg, n_qblk, n_ksplit, tiles_per_split;
+  int tok_per_wg, n_qblk, slots, n_ksplit, tiles_per_split, n_ranges;
 };
 // The prefill kernel's sizes: wavefronts of a workgroup, blocks of 16 query columns per wavefront, and
 // the pitches of a tile's rows in LDS (K: 16 bytes past a multiple of 64, V: an odd multiple of 32
@@ -184,6 +193,7 @@ constexpr int prefill_tokens_per_wg(int k_steps, int channel_tiles, int group) {
   return 16 * kPrefillWaves * prefill_blocks(k_steps, channel_tiles) / group;
 }
 PrefillPlan prefill_plan(int batch, int n_kv, int group, int d_k, int d_v, int n_new, int max_len);
+void prefill_cut_plan(PrefillPlan* p, int slabs, int group, int d_k, int d_v, int n_new, int max_len, uint32_t* order);
 
 // fp64 -> E4M3 code (finite-only 8-bit float: 4 exponent bits, bias 7, 3 mantissa bits, no
 // infinity, S.1111.111 = NaN): nearest value, ties to the even mantissa, magnitudes above 448

@@ -136,9 +136,12 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
       }
     }
   }
-  if (len > 0 && t_new == len - 1) len -= 1;       // the first stage stopped before the new token's row
-  if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;     // or before the new tokens' rows
-  const int n = (len + a.rows_per_split - 1) / a.rows_per_split;   // ranges that hold rows
+  int n;                                           // ranges that hold rows
+  {
+    if (len > 0 && t_new == len - 1) len -= 1;     // the first stage stopped before the new token's row
+    if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;   // or before the new tokens' rows
+    n = (len + a.rows_per_split - 1) / a.rows_per_split;
+  }
   float mstar = m_tok, den = 0.f, num = 0.f;
   if (m_tok > -INFINITY) {
     den = l_tok;
@@ -194,22 +197,23 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
   if (live) a.out[hq * a.d_v + c] = den > 0.f ? num / den : 0.f;
 }
 
-// The same for a prefill launch in key ranges (every slot of every query row is written there), whose query rows are
-// many and whose ranges are few, so that reading the partials is what bounds it: 32 lanes per query row, four
+// The same for a prefill launch in key ranges, whose query rows are many and whose ranges are few, so that reading the partials is what bounds it: 32 lanes per query row, four
 // channels per lane in 16-byte loads (where d_v is no multiple of four the last lane repeats channels of its
 // neighbour), eight rows per workgroup.  Up to eight ranges are one round trip; more are shared by 2, 4 or 8 sets
 // of lanes, which meet in LDS.  One workgroup of 128 threads per query row, as above, spends its time on starting
 // workgroups: 72336 rows of 2 ranges, d_v = 56, 42.9 us, so 17.2; 16384 rows of 8, d_v = 90 (48 MB), 14.9 and 9.5;
-// 1800 rows of 10, d_v = 74, 4.7 and 4.0.
+// 1800 rows of 10, d_v = 74, 4.7 and 4.0.  Rows of one range
+// were stored by the attention kernel itself: the launch begins at the first token whose block has several.
 typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_dw;
 template <int GRP>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) {
   constexpr int ROWS = 8 / GRP;                    // per workgroup
   const int lane = threadIdx.x & 31, set = threadIdx.x >> 5;
   const int grp = set % GRP;
-  const int row = static_cast<int>(blockIdx.x) * ROWS + set / GRP;
-  const bool live = row < a.rows;
-  const int n = live ? a.n_ksplit : 0;
+  const int tok0 = a.tok0;
+  const int in_seq = static_cast<int>(blockIdx.x) * ROWS + set / GRP;
+  const bool live = in_seq < (a.cut.n_new - tok0) * a.n_q;
+  const int row = (static_cast<int>(blockIdx.y) * a.cut.n_new + tok0) * a.n_q + in_seq;
   const int dv = a.d_v;
   const int c = dv < 4 ? 0 : (4 * lane < dv - 4 ? 4 * lane : dv - 4);
   const bool has = 4 * lane < dv;
@@ -217,12 +221,13 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) 
   const float* acc = a.part_acc + static_cast<long long>(row) * a.n_ksplit * dv + c;
   float mstar = -INFINITY, den = 0.f;
   f32x4_dw num = {0.f, 0.f, 0.f, 0.f};
+  // the first slots are requested, whatever they hold, before it is known how many this row's block wrote
   float m[kMergeSlots], l[kMergeSlots];
   f32x4_dw v[kMergeSlots];
   auto request = [&](int s0) {
 #pragma unroll
     for (int u = 0; u < kMergeSlots; ++u) {
-      const bool have = s0 + u < n;
+      const bool have = live && s0 + u < a.n_ksplit;
       const float2 x = have ? ml[s0 + u] : make_float2(-INFINITY, 0.f);
       m[u] = x.x;
       l[u] = x.y;
@@ -238,8 +243,12 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) 
       }
     }
   };
+  request(kMergeSlots * grp);
+  const int n = live ? prefill_ranges(a.cut, (tok0 + in_seq / a.n_q) / a.cut.tok_per_wg) : 0;
   for (int s0 = kMergeSlots * grp; s0 < n; s0 += kMergeSlots * GRP) {
-    request(s0);
+    if (s0 != kMergeSlots * grp) request(s0);
+#pragma unroll
+    for (int u = 0; u < kMergeSlots; ++u) m[u] = s0 + u < n ? m[u] : -INFINITY;      // unwritten: any bits
     float gmax = m[0];
 #pragma unroll
     for (int u = 1; u < kMergeSlots; ++u) gmax = fmaxf(gmax, m[u]);
@@ -254,7 +263,7 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) 
     for (int u = 0; u < kMergeSlots; ++u) {
       const bool some = m[u] > -INFINITY;          // an empty range leaves only its reference and sum
       const float w = some ? exp2f(m[u] - mstar) : 0.f;
-      den = fmaf(w, l[u], den);
+      den = fmaf(w, some ? l[u] : 0.f, den);
 #pragma unroll
       for (int e = 0; e < 4; ++e) num[e] = fmaf(w, some ? v[u][e] : 0.f, num[e]);
     }
@@ -281,7 +290,7 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) 
       for (int e = 0; e < 4; ++e) num[e] = fmaf(w, s_num[set + g][lane][e], num[e]);
     }
   }
-  if (!live || !has) return;
+  if (!live || !has || n <= 1) return;
 #pragma unroll
   for (int e = 0; e < 4; ++e) num[e] = den > 0.f ? num[e] / den : 0.f;
   float* dst = a.out + static_cast<long long>(row) * dv + c;
@@ -308,22 +317,24 @@ void launch_groups(const DecodeArgs& a, hipStream_t stream) {
 }
 
 template <int GRP>
-hipError_t launch_prefill_groups(const PrefillMergeArgs& a, long long rows, hipStream_t stream) {
-  const long long wgs = (rows * GRP + 7) / 8;
-  if (rows > 0x7fffffff - 8 || wgs * 256 >= (1ll << 32)) return hipErrorInvalidValue;     // fewer than 384 query blocks are cut
-  hipLaunchKernelGGL((prefill_merge_kernel<GRP>), dim3(static_cast<unsigned>(wgs)), dim3(256), 0, stream, a);
+hipError_t launch_prefill_groups(const PrefillMergeArgs& a, hipStream_t stream) {
+  // fewer than 384 query blocks are cut, so the rows are few enough for any arithmetic here
+  const int per_seq = (a.cut.n_new - a.tok0) * a.n_q;
+  hipLaunchKernelGGL((prefill_merge_kernel<GRP>), dim3((per_seq * GRP + 7) / 8, a.batch), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
+// `a` as the attention launch had it, tok_per_wg and n_qblk included.
 hipError_t launch_prefill_merge(const PrefillArgs& p, hipStream_t stream) {
-  const long long rows = static_cast<long long>(p.batch) * p.n_new * p.n_q;
-  const PrefillMergeArgs a = {p.part_acc, p.part_ml, p.out, static_cast<int32_t>(rows), p.d_v, p.n_ksplit};
-  if (p.n_ksplit <= kMergeSlots) return launch_prefill_groups<1>(a, rows, stream);
-  if (p.n_ksplit <= 2 * kMergeSlots) return launch_prefill_groups<2>(a, rows, stream);
-  if (p.n_ksplit <= 4 * kMergeSlots) return launch_prefill_groups<4>(a, rows, stream);
-  return launch_prefill_groups<8>(a, rows, stream);
+  const PrefillCut c = prefill_cut_of(p);
+  const int tok0 = (c.n_qblk - prefill_blocks_beyond(c, 1)) * c.tok_per_wg;
+  const PrefillMergeArgs a = {p.part_acc, p.part_ml, p.out, c, p.batch, p.n_q, p.d_v, p.n_ksplit, tok0};
+  if (p.n_ksplit <= kMergeSlots) return launch_prefill_groups<1>(a, stream);
+  if (p.n_ksplit <= 2 * kMergeSlots) return launch_prefill_groups<2>(a, stream);
+  if (p.n_ksplit <= 4 * kMergeSlots) return launch_prefill_groups<4>(a, stream);
+  return launch_prefill_groups<8>(a, stream);
 }
 
 hipError_t launch_merge(const DecodeArgs& a, hipStream_t stream) {

@@ -135,9 +135,27 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   const int l16 = lane & 15;
   const int lg = lane >> 4;
 
-  int qb, slab_id, ks;
-  prefill_place(static_cast<int>(blockIdx.x), a.n_qblk, a.n_kv * a.batch, a.n_ksplit > 1 ? a.n_ksplit : 1, prefill_slabs(KS, CT),
-                &qb, &slab_id, &ks);
+  int qb, slab_id, ks = 0;
+  const bool cut = a.n_ksplit > 1;
+  bool in_ranges = false;                          // this block's rows are shared with other workgroups
+  if (a.n_ranges > 0) {                            // cut, or all workgroups start together
+    int nth;
+    prefill_place_cut(static_cast<int>(blockIdx.x), a.n_ranges, a.n_kv * a.batch, a.slab_inv, &nth, &slab_id);
+    if (!cut) {
+      qb = a.n_qblk - 1 - nth;
+    } else if (a.n_ranges <= kMaxOrdered) {
+      const uint32_t r = a.order[nth];
+      qb = r & 0x1ff;
+      ks = (r >> 9) & 0x3fffff;
+      in_ranges = (r >> 31) != 0;
+    } else {
+      const PrefillCut c = prefill_cut_of(a);
+      prefill_range(nth, c, &qb, &ks);
+      in_ranges = prefill_ranges(c, qb) > 1;
+    }
+  } else {
+    prefill_place(static_cast<int>(blockIdx.x), a.n_qblk, a.n_kv * a.batch, 1, prefill_slabs(KS, CT), &qb, &slab_id, &ks);
+  }
   const int h = slab_id % a.n_kv;
   const int b = slab_id / a.n_kv;
 
@@ -154,8 +172,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
 
   const int n_tiles_all = (n_keys + kPrefillTile - 1) / kPrefillTile;
   const int t_first = ks * a.tiles_per_split;                       // key range of this workgroup, in tiles
-  const int n_tiles = a.n_ksplit > 1 ? min(n_tiles_all, t_first + a.tiles_per_split) : n_tiles_all;
-  if (a.n_ksplit > 1 && t_first >= n_tiles) {
+  const int n_tiles = in_ranges ? min(n_tiles_all, t_first + a.tiles_per_split) : n_tiles_all;
+  if (in_ranges && t_first >= n_tiles) {
     // nothing of this range is visible to the block (or the block lies before the start of its
     // sequence): empty partials, which the combining kernel drops
     for (int r = tid; r < (i_end - i0) * G; r += NT) {
@@ -508,7 +526,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
       float mul;
       float* dst;
       bool live = true;
-      if (a.n_ksplit > 1) {
+      if (in_ranges) {
         // partial of this key range: reference (log2 units), sum, un-normalised accumulators
         live = shift + i >= 0 && m_run[nb] > -INFINITY;
         const long long slot = row * a.n_ksplit + ks;
@@ -521,7 +539,8 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
       } else {
         // a token in front of its sequence is zeros; for one that exists a sum that is not a number
         // has made the accumulators so too, and they are multiplied, not replaced, so that it shows
-        live = shift + i >= 0;
+        // (in a call that may be cut all rows are as the combining kernel leaves them, which stores zeros there)
+        live = shift + i >= 0 && (!a.as_combined || l > 0.f);
         mul = l > 0.f ? 1.f / l : 0.f;
         dst = a.out + row * dv;
       }
@@ -552,7 +571,10 @@ hipError_t launch_prefill_inst(PrefillArgs a, hipStream_t stream) {
   a.tok_per_wg = prefill_tokens_per_wg(KS, CT, a.group);
   a.n_qblk = (a.n_new + a.tok_per_wg - 1) / a.tok_per_wg;
   constexpr size_t lds = 2 * static_cast<size_t>(kPrefillTile) * (prefill_k_pitch(KS) + prefill_v_pitch(CT));
-  const long long n_wg = static_cast<long long>(a.n_qblk) * a.n_kv * a.batch * (a.n_ksplit > 1 ? a.n_ksplit : 1);
+  const long long slabs = static_cast<long long>(a.n_kv) * a.batch;
+  if (a.n_ksplit <= 1) a.n_ranges = a.n_qblk * slabs <= 512 ? a.n_qblk : 0;
+  if (a.n_ranges > 0) a.slab_inv = prefill_inv(static_cast<int>(slabs));
+  const long long n_wg = slabs * (a.n_ranges > 0 ? a.n_ranges : a.n_qblk);
   if (n_wg > 0x7fffffffLL) return hipErrorInvalidValue;
   if (lds > 64 * 1024) {
     const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(&prefill_kernel<KS, CT, MODE, ONES, NB>), static_cast<int>(lds));

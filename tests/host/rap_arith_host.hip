@@ -23,6 +23,9 @@
 //   rap_arith_host prefill-place -> text, one line per (query blocks, slabs, key ranges, group): whether every
 //                               (block, slab, range) is placed once, on how many XCDs a slab lies, and how
 //                               often a query block follows a lighter one within a group of slabs
+//   rap_arith_host prefill-cut -> text, one line per shape of a prefill launch in key ranges: whether every
+//                               (slab, block, range) is taken once and a block's ranges make up its rows, and
+//                               how often a range follows a shorter one
 //   rap_arith_host pieceplan -> text, one line per (kind, element size, width): what the prefill
 //                               kernel's tile loads touch, in the middle of a cache and at its end; exit
 //                               status 1 if any leaves the cache, or misses a byte of a readable row
@@ -33,7 +36,15 @@
 
 #include <vector>
 
-#include "../../paper_2602_02599_amd/csrc/rap_arith.h"
+#include "../../paper_2602_02599_amd/csrc/rap_prefill.hip"   // the plan; it brings rap_arith.h
+
+// what the plan's file dispatches to
+namespace rap {
+hipError_t launch_prefill_ks1(const PrefillArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_prefill_ks2(const PrefillArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_prefill_ks3(const PrefillArgs&, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t launch_prefill_ks4(const PrefillArgs&, hipStream_t) { return hipErrorInvalidValue; }
+}  // namespace rap
 
 namespace {
 
@@ -111,6 +122,65 @@ int prefill_placed() {
   return bad;
 }
 
+// The ranges of cut prefill launches: every (block, range) of every slab is taken by one workgroup, the ranges of a block
+// make up its tiles, there are no more than the workspace holds, and they come longest first.
+int prefill_cut_up() {
+  int bad = 0;
+  for (int slabs : {1, 2, 3, 4, 7, 8, 12, 16, 24, 40, 56, 64, 96, 128, 200, 383})
+    for (int group : {1, 3, 4, 8, 16})
+      for (int d : {32, 90, 104, 128})
+        for (int n_new : {1, 5, 60, 64, 65, 300, 1000, 5000, 20000})
+          for (int max_len : {3, 449, 512, 700, 2048, 5001, 32768, 100000}) {
+            rap::PrefillPlan p = rap::prefill_plan(slabs, 1, group, d, d, n_new, max_len);
+            if (p.slots <= 1) continue;
+            std::vector<uint32_t> order(rap::kMaxOrdered, 0xffffffffu);
+            rap::prefill_cut_plan(&p, slabs, group, d, d, n_new, max_len, order.data());
+            const rap::PrefillCut c = {max_len, n_new, p.tok_per_wg, p.n_qblk, p.tiles_per_split};
+            const uint32_t inv = rap::prefill_inv(slabs);
+            int wrong = p.n_ksplit > p.slots || p.tiles_per_split < 4, unordered = 0, spread = 1;
+            if (p.n_ksplit == 1) {
+              wrong += p.n_ranges != p.n_qblk;
+            }
+            std::vector<int> hit(static_cast<size_t>(slabs) * p.n_qblk * p.n_ksplit, 0), xcd(slabs, 0);
+            int before = 1 << 30;
+            for (int wg = 0; wg < p.n_ranges * slabs; ++wg) {
+              int nth, slab, qb, k;
+              rap::prefill_place_cut(wg, p.n_ranges, slabs, inv, &nth, &slab);
+              if (nth < 0 || nth >= p.n_ranges || slab < 0 || slab >= slabs) return 1000000;
+              rap::prefill_range(nth, c, &qb, &k);
+              if (p.n_ranges <= rap::kMaxOrdered) {
+                qb = order[nth] & 0x1ff;
+                k = (order[nth] >> 9) & 0x3fffff;
+                if (qb < c.n_qblk) wrong += (order[nth] >> 31) != (rap::prefill_ranges(c, qb) > 1);
+              }
+              if (qb < 0 || qb >= c.n_qblk || k < 0 || k >= p.n_ksplit) return 1000000;
+              hit[(static_cast<size_t>(slab) * c.n_qblk + qb) * p.n_ksplit + k] += 1;
+              xcd[slab] |= 1 << (wg & 7);
+              if (p.n_ranges <= rap::kMaxOrdered && p.n_ranges * slabs > 512) {
+                const int tiles = rap::prefill_range_tiles(c, qb, k) / (c.per / 256 + 1);
+                unordered += tiles > before;
+                before = tiles;
+              }
+            }
+            for (int qb = 0; qb < c.n_qblk; ++qb) {
+              const int n = rap::prefill_ranges(c, qb), tokens = (qb + 1) * c.tok_per_wg < n_new ? (qb + 1) * c.tok_per_wg : n_new;
+              const int rows = max_len - n_new + tokens;
+              int tiles = 0;
+              for (int k = 0; k < p.n_ksplit; ++k) {
+                for (int s = 0; s < slabs; ++s) wrong += hit[(static_cast<size_t>(s) * c.n_qblk + qb) * p.n_ksplit + k] != (k < n);
+                if (k < n && rows > 0) tiles += rap::prefill_range_tiles(c, qb, k);
+                wrong += rap::prefill_blocks_beyond(c, k) < c.n_qblk - qb && k < n;
+              }
+              wrong += rows > 0 && tiles != (rows + 63) / 64;
+            }
+            for (int x : xcd) spread = __builtin_popcount(x) > spread ? __builtin_popcount(x) : spread;
+            printf("slabs=%d group=%d d=%d new=%d rows=%d ranges=%d of=%d wrong=%d unordered=%d xcds=%d\n", slabs, group, d, n_new, max_len,
+                   p.n_ranges, p.n_ksplit, wrong, unordered, spread);
+            bad += wrong != 0 || unordered != 0 || ((slabs & 7) == 0 && spread != 1);
+          }
+  return bad;
+}
+
 int place(bool always_rotated) {
   int bad = 0;
   for (int n_kv = 1; n_kv <= 16; n_kv = n_kv < 8 ? n_kv + 1 : n_kv + 8)
@@ -181,12 +251,13 @@ int pieceplan(bool read_whole) {
 
 int main(int argc, char** argv) {
   if (argc != 2) {
-    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|prefill-place\n");
+    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|prefill-place|prefill-cut\n");
     return 2;
   }
   if (strcmp(argv[1], "loadplan") == 0) return loadplan(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "loadplan-trim1") == 0) return loadplan(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "prefill-place") == 0) return prefill_placed() == 0 ? 0 : 1;
+  if (strcmp(argv[1], "prefill-cut") == 0) return prefill_cut_up() == 0 ? 0 : 1;
   if (strcmp(argv[1], "place") == 0) return place(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "place-rotated") == 0) return place(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "pieceplan") == 0) return pieceplan(false) == 0 ? 0 : 1;

@@ -229,3 +229,13 @@ def test_prefill_workgroups_are_placed_once_heavy_ones_first(harness):
     lines = [dict((k, int(v)) for k, v in (kv.split("=") for kv in ln.split())) for ln in text.splitlines()]
     assert len(lines) == 9 * 4 * 3 * 3
     assert rc == 0, [f for f in lines if f["wrong"] or f["lighter"] or (f["slabs"] % 8 == 0 and f["xcds"] != 1)][:5]
+
+
+def test_prefill_key_ranges_cover_every_block_once(harness):
+    """Every range of every query block and slab gets one workgroup, a block's ranges make up the rows it
+    sees and fit the workspace, and in launches of several rounds no range follows a shorter one."""
+    rc, text = _run(harness, "prefill-cut")
+    lines = [dict((k, int(v)) for k, v in (kv.split("=") for kv in ln.split())) for ln in text.splitlines()]
+    assert len(lines) > 1000
+    assert any(f["of"] == 1 for f in lines) and any(f["ranges"] > 128 for f in lines)
+    assert rc == 0, [f for f in lines if f["wrong"] or f["unordered"] or (f["slabs"] % 8 == 0 and f["xcds"] != 1)][:5]
