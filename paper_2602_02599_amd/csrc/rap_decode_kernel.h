@@ -1,6 +1,6 @@
 // Matrix-core decode attention over the compact cache: the default kernel of rap_decode_attn
-// (compiled by rap_decode_mfma.hip for bf16 caches and by rap_decode_mfma_q8.hip for one-byte codes,
-// so that the two sets of instantiations build side by side).
+// (compiled by rap_decode_bf16_k1.hip .. _k4.hip for bf16 caches, by rap_decode_mfma_q8.hip for one-byte codes and by
+// rap_decode_mfma_mx4.hip for 4-bit ones, so that the sets of instantiations build side by side).
 //
 // Eq. (attn) with the GQA remark, evaluated as online softmax over tiles of 32 cache rows.
 // The path is bound by HBM: every K and V byte is needed exactly once per decode step, and the
@@ -33,6 +33,7 @@
 #ifndef RAP_DECODE_KERNEL_H_
 #define RAP_DECODE_KERNEL_H_
 
+#include <type_traits>
 #include <utility>
 
 #include "rap_device.h"
@@ -211,6 +212,16 @@ __device__ __forceinline__ void static_for_pairs(F&& f) {
   static_for_pairs_seq(std::make_integer_sequence<int, N>(), f);
 }
 
+// Wavefronts per SIMD that an instantiation's registers are to leave room for: what its tile and accumulators allow
+// without spilling (fp8, 30 pairs, d_v = 60, 16 x 16384 rows: four 47.1 us, three 53.2).
+constexpr int decode_waves(int kch, int nt, bool vpair, bool q8, int mx4b, bool lean) {
+  if (mx4b > 0) return nt == 4 && kch <= 3 ? 4 : 3;
+  if (!lean) return kch <= 3 ? 3 : 2;
+  if (q8) return nt == 4 && kch <= 2 ? 4 : kch <= 3 ? 3 : 2;
+  if (2 * kch + nt <= 8 && !(vpair && kch + nt >= 6)) return 4;
+  return kch <= 3 || nt <= 4 ? 3 : 2;
+}
+
 constexpr int kMaxCols = 16;   // columns of the matrix instruction: query rows of one (b, h) with several tokens
 
 // KCH = ceil(d_k / 32) score k-steps, NT = 16-channel output tiles.  VPAIR (even d_v): a lane
@@ -246,8 +257,11 @@ constexpr int kMaxCols = 16;   // columns of the matrix instruction: query rows 
 // -> 93 us (3.4 -> 4.6 TB/s); 64 wide 87 -> 68, 128 wide 130 -> 102 us.  What bounds it now is the
 // vector ALU, 255 instructions per 32 rows and 60 % busy; row masks and clamped V rows are off the
 // common path for that reason (without that 103 us).
-template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, int MX4B = 0>
-__global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B > 0 || KCH <= 3) ? 3 : 2)) void decode_mfma_kernel(DecodeArgs a) {
+// FORM: kShortRanges, one loop for all tiles; kLongRanges, a lean loop in front of it (which over codes costs short ranges
+// nothing, so that there is no other form of them).
+enum { kShortRanges = 0, kLongRanges = 1 };
+template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, int MX4B, int FORM>
+__global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM == kLongRanges)) void decode_mfma_kernel(DecodeArgs a) {
   constexpr bool MX4 = MX4B > 0;
   // 1 KB wave-loads covering a K tile (d_k <= 32 KCH); MX4: one block per lane and half tile
   constexpr int NLD_K = MX4 ? 2 : k_tile_loads(KCH, Q8);
@@ -364,7 +378,7 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
   for (int u = 0; u < TRIM_K; ++u) k_tail[u] = tile_load_issued(NLD_K - TRIM_K + u, lane, NLD_K, TRIM_K, kTileRows * pitch_k, true);
 #pragma unroll
   for (int u = 0; u < TRIM_V; ++u) v_tail[u] = tile_load_issued(NLD_V - TRIM_V + u, lane, NLD_V, TRIM_V, kTileRows * pitch_v, true);
-  auto issue_loads = [&](int base, long long trow) {
+  auto issue_loads = [&](int base, long long trow, auto whole) {
     const unsigned char* kg = kslab + trow * pitch_k + 16 * lane;
     const unsigned char* vg = vslab + trow * pitch_v + 16 * lane;
     if constexpr (MX4) {
@@ -372,17 +386,17 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
       const int rows = min(kTileRows, len8 - base);
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt)
-        if (16 * rt + l16 < rows) {
+        if (decltype(whole)::value || 16 * rt + l16 < rows) {
           if (lg < KCH) kst[rt] = ld_stream(kslab + (trow + 16 * rt + l16) * pitch_k + 16 * lg);
           kss[rt] = *reinterpret_cast<const uint32_t*>(ksslab + (trow + 16 * rt + l16) * 4);
         }
 #pragma unroll
       for (int j = 0; j < NLD_V; ++j)
-        if (lane + 64 * j < rows * MX4B) vst[j] = ld_stream(vg + 1024 * j);
-      if (lane < rows) vss = *reinterpret_cast<const uint32_t*>(vsslab + (trow + lane) * 4);
+        if (lane + 64 * j < (decltype(whole)::value ? kTileRows : rows) * MX4B) vst[j] = ld_stream(vg + 1024 * j);
+      if (lane < (decltype(whole)::value ? kTileRows : rows)) vss = *reinterpret_cast<const uint32_t*>(vsslab + (trow + lane) * 4);
       return;
     }
-    if (base + kTileRows <= len8) {
+    if (decltype(whole)::value || base + kTileRows <= len8) {
       // common case, a full tile
 #pragma unroll
       for (int j = 0; j < NLD_K; ++j)
@@ -405,7 +419,7 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
 
   // first tile on its way before anything else is fetched
   const int first = r0 + kTileRows * wave;
-  if (first < r1) issue_loads(first, tile_row(first));
+  if (first < r1) issue_loads(first, tile_row(first), std::false_type());
   // paged: the page of the tile after next is looked up one iteration before its loads are issued
   long long trow1 = (PAGED && first + 4 * kTileRows < r1) ? tile_row(first + 4 * kTileRows) : 0;
 
@@ -464,7 +478,9 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
   };
   auto mx4_scale = [&](uint32_t bytes, int blk) -> float { return bits_f32(((bytes >> (8 * blk)) & 0xffu) << 23); };   // 2^(e - 127), e >= 1
 
-  for (int base = first; base < r1; base += 4 * kTileRows) {
+  // One tile.  `lean`: it is whole, holds no row to leave out, and the one after it is whole too.
+  auto tile = [&](int base, auto lean) {
+    constexpr bool LEAN = decltype(lean)::value;
     // ---- park the staged tile in LDS, start fetching the next one
     wave_lds_sync();
     uint32_t kw[2][4];            // MX4: word lg of block kk of the lane's two K rows
@@ -495,7 +511,7 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
       for (int j = 0; j < NLD_V; ++j) *reinterpret_cast<uint4*>(vt + 1024 * j + 16 * lane) = vst[j];
     }
     wave_lds_sync();
-    if (base + 4 * kTileRows < r1) issue_loads(base + 4 * kTileRows, PAGED ? trow1 : base + 4 * kTileRows);
+    if (LEAN || base + 4 * kTileRows < r1) issue_loads(base + 4 * kTileRows, PAGED ? trow1 : base + 4 * kTileRows, lean);
     if (PAGED && base + 8 * kTileRows < r1) trow1 = tile_row(base + 8 * kTileRows);
 
 
@@ -543,9 +559,9 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
     // A whole tile with nothing to leave out (all but the last tile of a range, normally) needs no
     // row masks and reads V as laid out; the test is wave-uniform, and the two places that differ
     // are branches around a few instructions, not copies of the arithmetic.
-    const int nv = min(kTileRows, r1 - base);       // valid rows in this tile, >= 1
-    const int skip_rel = t_skip - base;             // the one row to leave out, if it is in this tile
-    const bool plain = nv == kTileRows && (MX4 || static_cast<unsigned>(skip_rel) >= static_cast<unsigned>(kTileRows));
+    const int nv = LEAN ? kTileRows : min(kTileRows, r1 - base);   // valid rows in this tile, >= 1
+    const int skip_rel = LEAN ? -1 : t_skip - base;                // the one row to leave out, if it is in this tile
+    const bool plain = LEAN || (nv == kTileRows && (MX4 || static_cast<unsigned>(skip_rel) >= static_cast<unsigned>(kTileRows)));
     float x[2][4];
     float tmax = -INFINITY;
 #pragma unroll
@@ -553,7 +569,7 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float s = sc[rt][r] * scale_log2e;
-        x[rt][r] = (Q8 || MX4 || ((16 * rt + 4 * lg + r) < nv && (16 * rt + 4 * lg + r) != skip_rel)) ? s : -INFINITY;
+        x[rt][r] = (LEAN || Q8 || MX4 || ((16 * rt + 4 * lg + r) < nv && (16 * rt + 4 * lg + r) != skip_rel)) ? s : -INFINITY;
       }
     if ((Q8 || MX4) && !plain) {
 #pragma unroll
@@ -739,7 +755,21 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
 #pragma unroll
       for (int j = 0; j < 8; ++j) vo_laid[j] = (16 * (j >> 2) + 4 * lg + (j & 3)) * pitch_v + VLANE * l16;
     }
+  };
+  // All tiles but a wavefront's last one or two are lean: loads without a condition need no copies of the registers
+  // they go to (60 to 150 instructions of a tile's 390 to 330), and no row masks.  16 x 32768 rows, 4-bit, 89.4 -> 81.9 us;
+  // fp8 32 x 16384 126.2 -> 121.9, ragged 40 x 7989 48.2 -> 41.8; bf16 10 x 30925 124.7 -> 119.7, 16 x 8192 61.8
+  // -> 61.2 us.  Three score steps with seven or eight channel tiles spill too much for it (33 pairs, d_v = 100: 62.3
+  // us, lean 66.3; paged, two with eight, 66.0 and 69.6).  Ranges of up to four tiles per wavefront gain nothing, and the
+  // second loop in their way costs them up to 1 us (2 x 6000, 24 pairs, 10.0 us, with it 11.1): they have none.
+  int base = first;
+  constexpr bool LEAN_PAYS = FORM != kShortRanges && (Q8 || MX4 || !((KCH == 3 && NT >= 7) || (KCH == 2 && NT == 8 && PAGED)));
+  if constexpr (LEAN_PAYS) {
+    const bool skips = !MX4 && t_skip >= r0 && t_skip < r1;
+    if (!skips)
+      for (; base + 5 * kTileRows <= r1; base += 4 * kTileRows) tile(base, std::true_type());
   }
+  for (; base < r1; base += 4 * kTileRows) tile(base, std::false_type());
 
   // ---- fold lane groups, then the four wavefronts, through LDS
   l_run += __shfl_xor(l_run, 16);
@@ -793,18 +823,25 @@ __global__ __launch_bounds__(256, ((MX4B > 0 && NT == 4 && KCH <= 3) ? 4 : (MX4B
   }
 }
 
-template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL = false, int MX4B = 0>
-hipError_t launch_inst2(const DecodeArgs& a, hipStream_t stream) {
+template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, int MX4B, int FORM>
+hipError_t launch_form(const DecodeArgs& a, hipStream_t stream) {
   // scanning workgroups, then (decode step: n_slots = n_split + 1) one per (b, h) for the new token
   dim3 grid(static_cast<unsigned>(a.n_slots) * a.n_kv * a.batch), block(256);
   const size_t lds = 4 * static_cast<size_t>(a.lds_wave_bytes);
   if (lds > 64 * 1024) {
     // more than the default dynamic-LDS limit: raise it once per kernel (gfx950 has 160 KB per CU)
-    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(&decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B>), static_cast<int>(lds));
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(&decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, FORM>), static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B>), grid, block, lds, stream, a);
+  hipLaunchKernelGGL((decode_mfma_kernel<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, FORM>), grid, block, lds, stream, a);
   return hipGetLastError();
+}
+
+template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL = false, int MX4B = 0>
+hipError_t launch_inst2(const DecodeArgs& a, hipStream_t stream) {
+  if constexpr (!Q8 && MX4B == 0)
+    if (a.rows_per_split <= 16 * kTileRows) return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kShortRanges>(a, stream);
+  return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kLongRanges>(a, stream);
 }
 
 }  // namespace

@@ -1,46 +1,15 @@
-// Dispatch of the matrix-core decode kernel over bf16 caches (the kernel itself: rap_decode_kernel.h),
-// and the LDS size both element types need.
+// Dispatch of the matrix-core decode kernel (rap_decode_kernel.h) on the kind of cache and the score width,
+// and the LDS size it needs.
 #include "rap_decode_kernel.h"
 
 namespace rap {
 
+hipError_t launch_decode_bf16_k1(const DecodeArgs& a, hipStream_t stream);   // rap_decode_bf16_k1.hip .. _k4.hip
+hipError_t launch_decode_bf16_k2(const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_decode_bf16_k3(const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_decode_bf16_k4(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_decode_mfma_q8(const DecodeArgs& a, hipStream_t stream);   // rap_decode_mfma_q8.hip
 hipError_t launch_decode_mfma_mx4(const DecodeArgs& a, hipStream_t stream);  // rap_decode_mfma_mx4.hip
-
-namespace {
-
-template <int KCH, int NT, bool VPAIR>
-hipError_t launch_inst(const DecodeArgs& a, hipStream_t stream) {
-  if (a.block_table != nullptr) return launch_inst2<KCH, NT, VPAIR, true, false>(a, stream);
-  return launch_inst2<KCH, NT, VPAIR, false, false>(a, stream);
-}
-
-template <int KCH>
-hipError_t launch_k(const DecodeArgs& a, hipStream_t stream) {
-  const int nt = decode_v_tiles(a.d_v, false);
-  if ((a.d_v & 1) == 0 && (nt & 1) == 0) {   // paired 4-byte V reads
-    switch (nt) {
-      case 2: return launch_inst<KCH, 2, true>(a, stream);
-      case 4: return launch_inst<KCH, 4, true>(a, stream);
-      case 6: return launch_inst<KCH, 6, true>(a, stream);
-      case 8: return launch_inst<KCH, 8, true>(a, stream);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (nt) {
-    case 1: return launch_inst<KCH, 1, false>(a, stream);
-    case 2: return launch_inst<KCH, 2, false>(a, stream);
-    case 3: return launch_inst<KCH, 3, false>(a, stream);
-    case 4: return launch_inst<KCH, 4, false>(a, stream);
-    case 5: return launch_inst<KCH, 5, false>(a, stream);
-    case 6: return launch_inst<KCH, 6, false>(a, stream);
-    case 7: return launch_inst<KCH, 7, false>(a, stream);
-    case 8: return launch_inst<KCH, 8, false>(a, stream);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-}  // namespace
 
 // LDS bytes one wavefront needs: its K tile, its V tile and slack for the fragment reads that run
 // past the last row, or the hand-over area of the final fold, whichever is larger.
@@ -58,10 +27,10 @@ hipError_t launch_decode_mfma(const DecodeArgs& a, hipStream_t stream) {
   if (a.k_scales4 != nullptr) return launch_decode_mfma_mx4(a, stream);
   if (a.k_scale != nullptr) return launch_decode_mfma_q8(a, stream);
   switch ((a.d_k + 31) / 32) {
-    case 1: return launch_k<1>(a, stream);
-    case 2: return launch_k<2>(a, stream);
-    case 3: return launch_k<3>(a, stream);
-    case 4: return launch_k<4>(a, stream);
+    case 1: return launch_decode_bf16_k1(a, stream);
+    case 2: return launch_decode_bf16_k2(a, stream);
+    case 3: return launch_decode_bf16_k3(a, stream);
+    case 4: return launch_decode_bf16_k4(a, stream);
     default: return hipErrorInvalidValue;
   }
 }
