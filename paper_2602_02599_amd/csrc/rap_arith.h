@@ -166,6 +166,12 @@ __host__ __device__ __forceinline__ void decode_place(int wg, int n_split, int n
   *h = (wg - seq_range * n_kv + (few ? nth + *b : 0)) % n_kv;
 }
 
+// First unit of piece `nth` of `n` that a sequence of `units` is cut into: the longer ones first.
+__host__ __device__ __forceinline__ int flat_begin(int nth, int n, int units) {
+  const int whole = units / n, more = units - whole * n;
+  return nth * whole + (nth < more ? nth : more);
+}
+
 // Which query block, slab (sequence and KV head) and key range workgroup `wg` of a prefill launch takes.
 // Hardware places workgroup L on XCD L mod 8, each with an L2 of its own, and all query blocks of a slab
 // read the same K and V rows: with a multiple of 8 slabs, all workgroups of a slab go to one XCD, which

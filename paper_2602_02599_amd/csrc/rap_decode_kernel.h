@@ -191,7 +191,8 @@ __device__ __forceinline__ void token_finish(const DecodeArgs& a, int b, int h, 
       float part = lane < P ? fmaf(bf16_to_f32(qx), kxf, bf16_to_f32(qy) * kyf) : 0.f;
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
-      const long long slot = (static_cast<long long>(b) * a.n_q + h * a.group + g) * a.n_slots + a.n_split;
+      const long long slot = a.flat_wgs > 0 ? (static_cast<long long>(h) * a.flat_slots + a.flat_slots - a.batch + b) * a.group + g
+                                            : (static_cast<long long>(b) * a.n_q + h * a.group + g) * a.n_slots + a.n_split;
       if (lane == 0) {
         a.part_ml[slot * 2 + 0] = attended ? part * score_scale : -INFINITY;
         a.part_ml[slot * 2 + 1] = attended ? 1.f : 0.f;
@@ -259,10 +260,11 @@ constexpr int kMaxCols = 16;   // columns of the matrix instruction: query rows 
 // common path for that reason (without that 103 us).
 // FORM: kShortRanges, one loop for all tiles; kLongRanges, a lean loop in front of it (which over codes costs short ranges
 // nothing, so that there is no other form of them).
-enum { kShortRanges = 0, kLongRanges = 1 };
+// kByLength: the lean loop, and ranges by length (DecodeArgs).
+enum { kShortRanges = 0, kLongRanges = 1, kByLength = 2 };
 template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, int MX4B, int FORM>
-__global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM == kLongRanges)) void decode_mfma_kernel(DecodeArgs a) {
-  constexpr bool MX4 = MX4B > 0;
+__global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM != kShortRanges)) void decode_mfma_kernel(DecodeArgs a) {
+  constexpr bool MX4 = MX4B > 0, FLAT = FORM == kByLength;
   // 1 KB wave-loads covering a K tile (d_k <= 32 KCH); MX4: one block per lane and half tile
   constexpr int NLD_K = MX4 ? 2 : k_tile_loads(KCH, Q8);
   constexpr int NLD_V = MX4 ? (kTileRows * MX4B + 63) / 64 : v_tile_loads(NT, Q8);   // same for a V tile (d_v <= 16 NT)
@@ -281,11 +283,28 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM ==
   const int lg = lane >> 4;
   // The workgroups behind the scanning ones, one per (b, h), exist in the decode step only and take
   // the new token; coming last they do not disturb the placement of the others.
-  const int n_scan = a.n_split * a.n_kv * a.batch;
+  const int n_scan = FLAT ? (a.flat_slots - (a.new_pos != nullptr ? a.batch : 0)) * a.n_kv : a.n_split * a.n_kv * a.batch;
   const int wg = blockIdx.x;
-  int b, h, split = a.n_split;
+  const int no_range = FLAT ? -1 : a.n_split;
+  int b, h, split = no_range, row0 = 0, row1 = 0;
   if (wg < n_scan) {
-    decode_place(wg, a.n_split, a.n_kv, a.batch, &b, &split, &h);
+    if constexpr (FLAT) {
+      FlatRange f = flat_range(a, lane, wg / a.n_kv);
+      if (f.b >= a.batch) return;                      // there are fewer ranges
+      b = f.b;
+      split = wg / a.n_kv;                             // its slot
+      // placement as by decode_place
+      h = (wg - split * a.n_kv + (a.batch <= 8 ? f.nth + b : 0)) % a.n_kv;
+      if (a.batch > 8 && (f.n & 1) == 0) {
+        const int turned = (f.nth + b) % f.n;
+        split += turned - f.nth;
+        f.nth = turned;
+      }
+      row0 = flat_begin(f.nth, f.n, f.units) * kSplitQuantum;
+      row1 = flat_begin(f.nth + 1, f.n, f.units) * kSplitQuantum;
+    } else {
+      decode_place(wg, a.n_split, a.n_kv, a.batch, &b, &split, &h);
+    }
   } else {
     b = (wg - n_scan) / a.n_kv;
     h = (wg - n_scan) - b * a.n_kv;
@@ -307,7 +326,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM ==
   // several query tokens: the scan stops in front of their rows; the combining kernel adds the
   // causal part among the tokens themselves
   if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;
-  if (split == a.n_split) {                            // the workgroup of the new token (decode step only)
+  if (split == no_range) {                             // the workgroup of the new token (decode step only)
     TokenRegs tk;
     if (wave == 0) token_load(a, b, h, lane, rope_q, tk);
     if (rope_q) {
@@ -317,7 +336,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM ==
     if (wave == 0) token_finish(a, b, h, lane, t_skip, tok_attended, rope_q ? s_q : nullptr, tk);
     return;
   }
-  const int r0 = split * a.rows_per_split;
+  const int r0 = FLAT ? row0 : split * a.rows_per_split;
   if (r0 >= len) {
     // no rows for this workgroup.  With a single range nobody else writes the output row of an
     // empty sequence; with several ranges the combining kernel does.
@@ -326,7 +345,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM ==
         a.out[(static_cast<long long>(b) * a.n_q + h * a.group) * a.d_v + e] = 0.f;
     return;
   }
-  const int r1 = min(r0 + a.rows_per_split, len);
+  const int r1 = min(FLAT ? row1 : r0 + a.rows_per_split, len);
   // rows below len8 are readable: <= cache_cap (a multiple of 8, of 16 for one-byte elements, which
   // keeps every such group of rows 16-byte aligned whatever the row width)
   const int len8 = Q8 ? (len + 15) & ~15 : (len + 7) & ~7;
@@ -814,10 +833,11 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM ==
     if (a.direct_out) {
       a.out[hq * dv + c] = den > 0.f ? num / den : 0.f;
     } else {
-      a.part_acc[(hq * a.n_slots + split) * dv + c] = num;
+      const long long slot = FLAT ? (static_cast<long long>(h) * a.flat_slots + split) * cols + g : hq * a.n_slots + split;
+      a.part_acc[slot * dv + c] = num;
       if (c == 0) {
-        a.part_ml[(hq * a.n_slots + split) * 2 + 0] = mstar;
-        a.part_ml[(hq * a.n_slots + split) * 2 + 1] = den;
+        a.part_ml[slot * 2 + 0] = mstar;
+        a.part_ml[slot * 2 + 1] = den;
       }
     }
   }
@@ -826,7 +846,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM ==
 template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, int MX4B, int FORM>
 hipError_t launch_form(const DecodeArgs& a, hipStream_t stream) {
   // scanning workgroups, then (decode step: n_slots = n_split + 1) one per (b, h) for the new token
-  dim3 grid(static_cast<unsigned>(a.n_slots) * a.n_kv * a.batch), block(256);
+  dim3 grid((FORM == kByLength ? static_cast<unsigned>(a.flat_slots) : static_cast<unsigned>(a.n_slots) * a.batch) * a.n_kv), block(256);
   const size_t lds = 4 * static_cast<size_t>(a.lds_wave_bytes);
   if (lds > 64 * 1024) {
     // more than the default dynamic-LDS limit: raise it once per kernel (gfx950 has 160 KB per CU)
@@ -839,6 +859,7 @@ hipError_t launch_form(const DecodeArgs& a, hipStream_t stream) {
 
 template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL = false, int MX4B = 0>
 hipError_t launch_inst2(const DecodeArgs& a, hipStream_t stream) {
+  if (a.flat_wgs > 0) return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kByLength>(a, stream);
   if constexpr (!Q8 && MX4B == 0)
     if (a.rows_per_split <= 16 * kTileRows) return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kShortRanges>(a, stream);
   return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kLongRanges>(a, stream);

@@ -118,6 +118,11 @@ struct DecodeArgs {
   int32_t max_len, rows_per_split, n_split;
   int32_t n_slots;          // partial slots per query head: n_split, plus one in the decode step
   int32_t lds_wave_bytes;   // matrix-core kernel: LDS slice of one wavefront
+  // Ranges by length (flat_wgs > 0; matrix-core kernel, up to 64 sequences): how many ranges a sequence has is found on the
+  // device, from its length and the others': flat_full where all have flat_units units of 128 rows, the most they may;
+  // else so many that the ranges are about as long as each other and no more than flat_wgs per KV head.  Partials are
+  // then [H_kv, flat_slots, n_tok * group], sequence by sequence, range by range, the new tokens of a decode step behind.
+  int32_t flat_wgs, flat_slots, flat_full, flat_units;
   int64_t cap;
   float scale_log2e;   // softmax scale * log2(e): exponentials are taken as exp2
 };
@@ -251,6 +256,81 @@ __device__ __forceinline__ void rotate_queries_to_lds(const DecodeArgs& a, int b
     s_q[g * 2 * P + c] = r0;
     s_q[g * 2 * P + c + P] = r1;
   }
+}
+
+// Inclusive sum over the lanes of a wavefront, all of them active.
+__device__ __forceinline__ int wave_sum_to(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// Ranges by length (DecodeArgs): the row ranges of a KV head's sequences, found by each wavefront for itself, lane b
+// with sequence b.
+struct FlatRange {
+  int b, units;       // sequence, and its rows that are scanned (not a new last token, nor the new tokens) in units of 128
+  int nth, n;         // which of the sequence's ranges, and how many it has; b >= batch: there are fewer ranges
+};
+struct FlatLens {
+  int units;          // of sequence `lane`
+  bool full;          // all sequences are as long as they may be
+};
+__device__ __forceinline__ FlatLens flat_lens(const DecodeArgs& a, int lane) {
+  FlatLens r;
+  int len = 0;
+  if (lane < a.batch) {
+    len = a.seq_lens[lane];
+    len = len < 0 ? 0 : (len > a.max_len ? a.max_len : len);
+    if (a.new_pos != nullptr && len > 0 && a.new_pos[lane] == len - 1) len -= 1;
+    if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;
+  }
+  r.units = (len + kSplitQuantum - 1) / kSplitQuantum;
+  r.full = __ballot(lane < a.batch && r.units != a.flat_units) == 0;
+  return r;
+}
+// Ranges of sequence `lane`, and of it and all before it: as many as of a full one where all are of one length, else
+// by the shortest range that leaves no more than flat_wgs of them.
+__device__ __forceinline__ void flat_counts(const DecodeArgs& a, int lane, int units, int* n, int* n_to) {
+  const int first = __builtin_amdgcn_readfirstlane(units);
+  int r;
+  if (__ballot(lane < a.batch && units != first) == 0) {
+    r = first > a.n_split ? (first + a.n_split - 1) / a.n_split : 1;
+  } else {
+    // a sequence has one range that is not whole at most, so no longer ones than hi are needed
+    const int total = __builtin_amdgcn_readlane(wave_sum_to(units), kWave - 1);
+    int hi = total / (a.flat_wgs - a.batch) + 1;
+    r = (total + a.flat_wgs - 1) / a.flat_wgs;
+    while (r < hi) {
+      const int mid = (r + hi) >> 1;
+      if (__builtin_amdgcn_readlane(wave_sum_to((units + mid - 1) / mid), kWave - 1) <= a.flat_wgs) hi = mid;
+      else r = mid + 1;
+    }
+  }
+  *n = (units + r - 1) / r;
+  *n_to = wave_sum_to(*n);
+}
+__device__ __forceinline__ FlatRange flat_range(const DecodeArgs& a, int lane, int which) {
+  const FlatLens l = flat_lens(a, lane);
+  FlatRange r;
+  if (l.full) {
+    r.n = a.flat_full;
+    r.b = which / r.n;
+    r.nth = which - r.b * r.n;
+  } else {
+    int n, n_to;
+    flat_counts(a, lane, l.units, &n, &n_to);
+    r.b = __popcll(__ballot(n_to <= which));           // sequences that end with an earlier range
+    if (r.b >= a.batch) return r;
+    r.n = __builtin_amdgcn_readlane(n, r.b);
+    r.nth = which - (__builtin_amdgcn_readlane(n_to, r.b) - r.n);
+  }
+  if (r.b >= a.batch) return r;
+  r.units = __builtin_amdgcn_readlane(l.units, r.b);
+  return r;
 }
 
 // Host side: a kernel that wants more than the default 64 KB of dynamic LDS has its limit raised

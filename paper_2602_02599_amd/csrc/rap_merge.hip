@@ -31,7 +31,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // MT: 0 for one query token, else an upper bound of n_tok, to which the loops over new tokens are
 // unrolled: four, eight or sixteen.  Unrolled to sixteen, five to eight tokens cost 2 to 4 us more (attention
 // of 5 tokens, 16 x 8192 rows, 24 query heads: 73.9 us, to eight 70.1; fp8 50.0 and 46.4; 9 tokens 71.3).
-template <int MT, int GRP>
+// FLAT: ranges by length (DecodeArgs); an instantiation of its own, because what it takes costs the other form up to 1.5 us.
+template <int MT, int GRP, bool FLAT>
 __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
   constexpr bool MULTI = MT > 0;
   const long long hq = blockIdx.x;                 // query row: (b * n_tok + token) * n_q + query head
@@ -39,25 +40,37 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
   const int c = threadIdx.x & 127;
   const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
   const bool live = c < a.d_v;
-  const float* ml = a.part_ml + hq * a.n_slots * 2;
-  const float* accc = a.part_acc + hq * a.n_slots * a.d_v + (live ? c : 0);
+  // This query row's slots: one behind the other, or (FLAT) `stride` rows apart among those of its KV head, from slot0 on.
+  const int stride = FLAT ? a.n_tok * a.group : 1;
+  long long row0 = hq * a.n_slots;
+  if constexpr (FLAT) {
+    const int qh = static_cast<int>(hq % a.n_q), qt = MULTI ? static_cast<int>((hq / a.n_q) % a.n_tok) : 0;
+    row0 = static_cast<long long>(qh / a.group) * a.flat_slots * stride + qt * a.group + qh % a.group;
+  }
+  int slot0 = FLAT ? b * a.flat_full : 0;
+  const float* ml = a.part_ml + row0 * 2;
+  const float* accc = a.part_acc + row0 * a.d_v + (live ? c : 0);
   // All slots of a query head are allocated, whatever they hold, so this group's first eight are
-  // requested before anything else is known.
+  // requested before anything else is known (FLAT: those that are right where all sequences are as long as they may be).
   float m[kMergeSlots], l[kMergeSlots], v[kMergeSlots];
   auto request = [&](int s0) {
 #pragma unroll
     for (int u = 0; u < kMergeSlots; ++u) {
-      const bool have = s0 + u < a.n_split;
-      m[u] = have ? ml[2 * (s0 + u)] : -INFINITY;
-      l[u] = have ? ml[2 * (s0 + u) + 1] : 0.f;
-      v[u] = have ? accc[static_cast<long long>(s0 + u) * a.d_v] : 0.f;
+      const bool have = FLAT ? slot0 + s0 + u < a.flat_slots : s0 + u < a.n_split;
+      const int at = (slot0 + s0 + u) * stride;
+      m[u] = have ? ml[2 * at] : -INFINITY;
+      l[u] = have ? ml[2 * at + 1] : 0.f;
+      v[u] = have ? accc[static_cast<long long>(at) * a.d_v] : 0.f;
     }
   };
   request(kMergeSlots * grp);
   const bool tok = grp == 0 && a.n_slots > a.n_split;   // the slot behind the ranges is in use
-  float m_tok = tok ? ml[2 * a.n_split] : -INFINITY;
-  float l_tok = tok ? ml[2 * a.n_split + 1] : 0.f;
-  float v_tok = tok ? accc[static_cast<long long>(a.n_split) * a.d_v] : 0.f;
+  const int tok_at = FLAT ? (a.flat_slots - a.batch + b) * stride : a.n_split;
+  float m_tok = tok ? ml[2 * tok_at] : -INFINITY;
+  float l_tok = tok ? ml[2 * tok_at + 1] : 0.f;
+  float v_tok = tok ? accc[static_cast<long long>(tok_at) * a.d_v] : 0.f;
+  FlatLens f;
+  if constexpr (FLAT) f = flat_lens(a, threadIdx.x & (kWave - 1));
   const int t_new = a.new_pos != nullptr ? a.new_pos[b] : -1;
   int len = a.seq_lens[b];
   len = len < 0 ? 0 : (len > a.max_len ? a.max_len : len);
@@ -137,7 +150,19 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
     }
   }
   int n;                                           // ranges that hold rows
-  {
+  if constexpr (FLAT) {
+    n = a.flat_full;
+    if (!f.full) {
+      int n_of, n_to;
+      flat_counts(a, threadIdx.x & (kWave - 1), f.units, &n_of, &n_to);
+      n = __builtin_amdgcn_readlane(n_of, b);
+      const int first = __builtin_amdgcn_readlane(n_to, b) - n;
+      if (first != slot0) {
+        slot0 = first;
+        if (kMergeSlots * grp < n) request(kMergeSlots * grp);
+      }
+    }
+  } else {
     if (len > 0 && t_new == len - 1) len -= 1;     // the first stage stopped before the new token's row
     if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;   // or before the new tokens' rows
     n = (len + a.rows_per_split - 1) / a.rows_per_split;
@@ -305,15 +330,24 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) 
 
 namespace {
 
-template <int MT>
+template <int MT, bool FLAT>
 void launch_groups(const DecodeArgs& a, hipStream_t stream) {
   dim3 grid(static_cast<unsigned>(a.batch) * a.n_tok * a.n_q);
   // a launch holds fewer than 2^32 threads: from 4 M query rows on, fewer groups walk the ranges in turn
   auto fits = [&](unsigned threads) { return static_cast<unsigned long long>(grid.x) * threads < (1ull << 32); };
-  if (a.n_split <= kMergeSlots || !fits(256)) hipLaunchKernelGGL((merge_kernel<MT, 1>), grid, dim3(128), 0, stream, a);
-  else if (a.n_split <= 2 * kMergeSlots || !fits(512)) hipLaunchKernelGGL((merge_kernel<MT, 2>), grid, dim3(256), 0, stream, a);
-  else if (a.n_split <= 4 * kMergeSlots || !fits(1024)) hipLaunchKernelGGL((merge_kernel<MT, 4>), grid, dim3(512), 0, stream, a);
-  else hipLaunchKernelGGL((merge_kernel<MT, 8>), grid, dim3(1024), 0, stream, a);
+  if (a.n_split <= kMergeSlots || !fits(256)) hipLaunchKernelGGL((merge_kernel<MT, 1, FLAT>), grid, dim3(128), 0, stream, a);
+  else if (a.n_split <= 2 * kMergeSlots || !fits(512)) hipLaunchKernelGGL((merge_kernel<MT, 2, FLAT>), grid, dim3(256), 0, stream, a);
+  else if (a.n_split <= 4 * kMergeSlots || !fits(1024)) hipLaunchKernelGGL((merge_kernel<MT, 4, FLAT>), grid, dim3(512), 0, stream, a);
+  else hipLaunchKernelGGL((merge_kernel<MT, 8, FLAT>), grid, dim3(1024), 0, stream, a);
+}
+
+template <bool FLAT>
+hipError_t launch_merge_form(const DecodeArgs& a, hipStream_t stream) {
+  if (a.n_tok <= 1) launch_groups<0, FLAT>(a, stream);
+  else if (a.n_tok <= 4) launch_groups<4, FLAT>(a, stream);
+  else if (a.n_tok <= 8) launch_groups<8, FLAT>(a, stream);
+  else launch_groups<kMaxTok, FLAT>(a, stream);
+  return hipGetLastError();
 }
 
 template <int GRP>
@@ -338,11 +372,7 @@ hipError_t launch_prefill_merge(const PrefillArgs& p, hipStream_t stream) {
 }
 
 hipError_t launch_merge(const DecodeArgs& a, hipStream_t stream) {
-  if (a.n_tok <= 1) launch_groups<0>(a, stream);
-  else if (a.n_tok <= 4) launch_groups<4>(a, stream);
-  else if (a.n_tok <= 8) launch_groups<8>(a, stream);
-  else launch_groups<kMaxTok>(a, stream);
-  return hipGetLastError();
+  return a.flat_wgs > 0 ? launch_merge_form<true>(a, stream) : launch_merge_form<false>(a, stream);
 }
 
 }  // namespace rap

@@ -90,6 +90,67 @@ def test_range_counts(rap, n_split, n_tok):
     H.assert_attn_close(out.cpu().numpy(), O.prefill_attn_ref(qb, kd, vd, lens, scale), "%d ranges" % n_split)
 
 
+# lengths of a batch in units of its longest: all full, all alike but shorter, spread out, empty and single-row ones among
+# long ones, one long one
+LENGTHS = {"full": lambda i, B: 1.0, "alike": lambda i, B: 0.6, "spread": lambda i, B: (i + 1) / B,
+           "gaps": lambda i, B: (0.0, 1.0, 1e-9, 0.37)[i % 4], "one": lambda i, B: 1.0 if i == B - 1 else 0.02}
+
+
+@pytest.mark.parametrize("kind", ["bf16", "fp8", "mx4", "paged"])
+@pytest.mark.parametrize("B,ctx,Hq,Hkv", [(40, 3000, 16, 8), (9, 9000, 8, 8), (3, 50000, 16, 8), (64, 3100, 12, 4), (2, 60000, 15, 3)])
+def test_ranges_by_length(rap, kind, B, ctx, Hq, Hkv):
+    """The automatic ranges, which follow the lengths, against ranges of a fixed number of rows, for every pattern of
+    lengths: plain attention, several tokens, the one-call step (its new row last, in the middle, nowhere)."""
+    P, dv, cap = 6, 10, (ctx + 127) // 128 * 128
+    fixed = rap.tuning(rows_per_split=4096)
+    g = torch.Generator(device=DEV); g.manual_seed(B)
+    rand = lambda *s: torch.randn(s, generator=g, device=DEV)
+    rows = (B * (cap // 128), Hkv, 128) if kind == "paged" else (B, Hkv, cap)
+    shp, scale = rap.shape(B, Hq, Hkv, 128, P, dv, cap, 5e5), 0.3
+    ks = vs = pg = None
+    if kind == "mx4":
+        k, v = (torch.randint(0, 256, rows + (16,), generator=g, device=DEV, dtype=torch.int32).to(torch.uint8) for _ in range(2))
+        sc = torch.randint(123, 128, rows + (4,), generator=g, device=DEV, dtype=torch.int32).to(torch.uint8)
+    else:
+        k, v = rand(*rows, 2 * P).to(torch.bfloat16), rand(*rows, dv).to(torch.bfloat16)
+        if kind == "fp8":
+            k, v = (x.to(torch.float8_e4m3fn).view(torch.uint8) for x in (k, v))
+            ks, vs = (torch.rand(Hkv, generator=g, device=DEV) + 0.5 for _ in range(2))
+        if kind == "paged":
+            pg = rap.paging(128, rows[0], torch.randperm(rows[0], generator=g, device=DEV).to(torch.int32).view(B, -1).contiguous())
+    keep = torch.arange(P, dtype=torch.int32, device=DEV).repeat(Hkv, 1).contiguous()
+
+    def both(shape, call, n_tok=1):
+        outs = []
+        for tun in (None, fixed):
+            gw, ws = H.guarded_workspace(rap, shp, ctx, tun, n_tok=n_tok)
+            go, out = H.guarded_out(shape, DEV)
+            call(out, ws, tun)
+            torch.cuda.synchronize()
+            gw.check("workspace")
+            go.check("out")
+            outs.append(out)
+        assert not torch.isnan(outs[0]).any()
+        worst = ((outs[0] - outs[1]).abs().max() / outs[1].abs().max()).item()
+        assert worst < 2e-5, worst                      # sums of 16-bit probabilities, in another order
+
+    for name, f in LENGTHS.items():
+        _say("by length %s B=%d ctx=%d %s" % (kind, B, ctx, name))
+        lens = torch.tensor([min(ctx, int(math.ceil(ctx * f(i, B)))) for i in range(B)], dtype=torch.int32)
+        lens = lens[torch.randperm(B, generator=torch.Generator().manual_seed(7))].to(DEV)
+        if kind == "mx4":
+            q = rand(B, Hq, 2 * P).to(torch.bfloat16)
+            both((B, Hq, dv), lambda o, w, t: rap.rap_decode_attn_mx4(shp, q, k, sc, v, sc, lens, ctx, o, scale, w, t))
+            continue
+        for n_tok in (1, 2, 3):
+            q = rand(B, n_tok, Hq, 2 * P).to(torch.bfloat16)
+            both((B, n_tok, Hq, dv), lambda o, w, t: rap.rap_decode_attn_multi(shp, k, v, ks, vs, pg, n_tok, q, lens, ctx, o, scale, w, t), n_tok)
+        q1, k1, v1 = rand(B, Hq, 2 * P).to(torch.bfloat16), rand(B, Hkv, 2 * P).to(torch.bfloat16), rand(B, Hkv, dv).to(torch.bfloat16)
+        for at in ("last", "middle", "nowhere"):
+            pos = (lens - 1 if at == "last" else lens // 2 if at == "middle" else lens * 0 - 1).to(torch.int32)
+            both((B, Hq, dv), lambda o, w, t: rap.rap_decode_step_ex(shp, k, v, ks, vs, pg, k1, v1, pos, keep, q1, False, lens, ctx, o, scale, w, t))
+
+
 # one, two, four or eight sets of lanes per query row; channels in fours, with a last four that overlaps, fewer than four
 @pytest.mark.parametrize("rows,dv", [(2048, 90), (2049, 1), (4096, 3), (4100, 4), (8192, 5), (8200, 128), (16640, 127)])
 def test_prefill_range_counts(rap, rows, dv):
