@@ -182,7 +182,10 @@ __global__ __launch_bounds__(256) void append_mx4_kernel(AppendArgs a) {
 //     (error ~1e-16 per step, over at most runs_per_wave * kBulkRun steps).
 // A run whose positions are not t0, t0+1, ... inside [0, cap) takes the general loop below it
 // (exact sincos per token, rows outside the cache skipped), which is the per-token arithmetic.
-constexpr int kBulkRun = 16;
+// In launches of few runs (brief_runs) they are four tokens long: a run is a chain of rotations, and shorter ones are done
+// sooner.  Before and now: 16 tokens, 8 heads, 7.2 -> 4.1 us, 512 tokens 7.7 -> 4.4, fp8 28 tokens 13.9 -> 4.9; 32 query heads, 512
+// tokens, 6.4 -> 5.7 us.  With many they share less of the set-up: 4 x 2048 tokens 13.5 us, so 17.0.
+constexpr int kBulkRun = 16, kShortRun = 4;
 
 // Two values, each with one rounding to bf16, first in the low half.  The fp64 -> fp32 conversion
 // followed by the fp32 -> bf16 instruction is that single rounding unless the fp32 lies exactly
@@ -208,7 +211,7 @@ __device__ __forceinline__ uint32_t lane_read(int byte_addr, uint32_t v) {
 // Q8: the caches hold E4M3 codes (rap_rope_append_q8): every rotated element and every V element is
 // divided by its head's scale in fp64 and rounded once to the nearest code; a lane stores the two
 // code bytes of its own pair, so nothing travels back between lanes.
-template <bool VDWORD, bool QUERY, bool Q8>
+template <bool VDWORD, bool QUERY, bool Q8, int RUN>
 __global__ __launch_bounds__(256) void append_bulk_kernel(AppendArgs a, int runs_per_wave) {
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -252,27 +255,27 @@ __global__ __launch_bounds__(256) void append_bulk_kernel(AppendArgs a, int runs
   int t_next = 0;
 #pragma unroll 1
   for (int r = 0; r < runs_per_wave; ++r) {
-    const int n0 = ((blockIdx.x * 4 + wave) * runs_per_wave + r) * kBulkRun;
+    const int n0 = ((blockIdx.x * 4 + wave) * runs_per_wave + r) * RUN;
     if (n0 >= a.n_new) break;
-    const int cnt = min(kBulkRun, a.n_new - n0);
+    const int cnt = min(RUN, a.n_new - n0);
     const long long tok0 = static_cast<long long>(b) * a.n_new + n0;
     const uint16_t* ksrc0 = a.k_new + (tok0 * a.n_kv + h) * (2 * P);
     const uint16_t* vsrc0 = QUERY ? nullptr : a.v_new + (tok0 * a.n_kv + h) * a.d_v;
     const int tv = lane < cnt ? pos[n0 + lane] : 0;
     const int t0 = __builtin_amdgcn_readfirstlane(tv);
-    // (a last, shorter run takes the general loop: at most kBulkRun - 1 tokens per sequence and head)
+    // (a last, shorter run takes the general loop: at most RUN - 1 tokens per sequence and head)
     // (with paged caches a run must also stay inside one page)
-    const bool in_order = cnt == kBulkRun && __all(lane >= kBulkRun || tv == t0 + lane) &&
-                          (QUERY || (t0 >= 0 && static_cast<long long>(t0) + kBulkRun <= a.cap &&
+    const bool in_order = cnt == RUN && __all(lane >= RUN || tv == t0 + lane) &&
+                          (QUERY || (t0 >= 0 && static_cast<long long>(t0) + RUN <= a.cap &&
                                      (a.block_table == nullptr ||
-                                      (t0 & ((1 << a.page_shift) - 1)) + kBulkRun <= (1 << a.page_shift))));
+                                      (t0 & ((1 << a.page_shift) - 1)) + RUN <= (1 << a.page_shift))));
 
     if (in_order) {
       // Loads are unconditional (straight-line code, all in flight together): lanes with nothing
       // to fetch re-read an element that exists and never store what they got.
-      uint32_t kw[kBulkRun], vw[kBulkRun];
+      uint32_t kw[RUN], vw[RUN];
 #pragma unroll
-      for (int i = 0; i < kBulkRun; ++i) {
+      for (int i = 0; i < RUN; ++i) {
         kw[i] = reinterpret_cast<const uint32_t*>(ksrc0 + i * kstride)[kl];
         if (QUERY) {
           vw[i] = 0;
@@ -289,7 +292,7 @@ __global__ __launch_bounds__(256) void append_bulk_kernel(AppendArgs a, int runs
       const long long kdstride = QUERY ? kstride : 2 * P;          // consecutive cache rows, or the input's layout
       uint16_t* vdst0 = QUERY ? nullptr : a.v_cache + row0 * a.d_v;
 #pragma unroll
-      for (int i = 0; i < kBulkRun; ++i) {
+      for (int i = 0; i < RUN; ++i) {
         {
           const uint32_t xw = lane_read(x_lane, kw[i]), yw = lane_read(y_lane, kw[i]);
           const double x = static_cast<double>(bf16_to_f32(static_cast<uint16_t>(x_half ? xw >> 16 : xw & 0xffffu)));
@@ -338,7 +341,7 @@ __global__ __launch_bounds__(256) void append_bulk_kernel(AppendArgs a, int runs
         }
       }
       anchored = true;
-      t_next = t0 + kBulkRun;
+      t_next = t0 + RUN;
       continue;
     }
 
@@ -397,6 +400,24 @@ __global__ __launch_bounds__(256) void append_bulk_kernel(AppendArgs a, int runs
   }
 }
 
+// Either way: queries, 1024 runs of 16 tokens 6.3 and 5.6 us, 2040 8.8 and 9.1; appends, 1512 9.1 and 8.4, 4096 13.5 and
+// 17.0; fp8, 3160 24.3 and 22.0, 4016 the same.
+constexpr int brief_runs(bool query, bool q8) { return q8 ? 4096 : query ? 1024 : 1536; }
+
+template <bool VDWORD, bool QUERY, bool Q8>
+hipError_t launch_bulk(const AppendArgs& a, hipStream_t stream) {
+  // longer walks per wavefront share the per-lane set-up; short jobs keep one run per wavefront
+  // so that the chip still gets enough wavefronts
+  const long long runs = static_cast<long long>((a.n_new + kBulkRun - 1) / kBulkRun) * a.n_kv * a.batch;
+  const bool brief = runs <= brief_runs(QUERY, Q8);
+  const int rpw = runs >= 32768 ? 4 : runs >= 16384 ? 2 : 1;
+  const int per_wg = 4 * (brief ? kShortRun : rpw * kBulkRun);
+  dim3 grid(static_cast<unsigned>((a.n_new + per_wg - 1) / per_wg), static_cast<unsigned>(a.n_kv), static_cast<unsigned>(a.batch));
+  if (brief) hipLaunchKernelGGL((append_bulk_kernel<VDWORD, QUERY, Q8, kShortRun>), grid, dim3(256), 0, stream, a, 1);
+  else hipLaunchKernelGGL((append_bulk_kernel<VDWORD, QUERY, Q8, kBulkRun>), grid, dim3(256), 0, stream, a, rpw);
+  return hipGetLastError();
+}
+
 hipError_t launch_append(const AppendArgs& a, hipStream_t stream) {
   if (a.k_scales4 != nullptr) {
     const long long n_tok4 = static_cast<long long>(a.batch) * a.n_new;
@@ -404,34 +425,14 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(append_mx4_kernel, grid4, dim3(256), 0, stream, a);
     return hipGetLastError();
   }
-  if (a.k_scale != nullptr && a.n_new >= kBulkRun) {
-    const long long runs = static_cast<long long>((a.n_new + kBulkRun - 1) / kBulkRun) * a.n_kv * a.batch;
-    const int rpw = runs >= 32768 ? 4 : runs >= 16384 ? 2 : 1;
-    const int per_wg = 4 * rpw * kBulkRun;
-    dim3 grid(static_cast<unsigned>((a.n_new + per_wg - 1) / per_wg), static_cast<unsigned>(a.n_kv),
-              static_cast<unsigned>(a.batch));
-    if ((a.d_v & 1) == 0) hipLaunchKernelGGL((append_bulk_kernel<true, false, true>), grid, dim3(256), 0, stream, a, rpw);
-    else hipLaunchKernelGGL((append_bulk_kernel<false, false, true>), grid, dim3(256), 0, stream, a, rpw);
-    return hipGetLastError();
-  }
+  if (a.k_scale != nullptr && a.n_new >= kBulkRun) return (a.d_v & 1) == 0 ? launch_bulk<true, false, true>(a, stream) : launch_bulk<false, false, true>(a, stream);
   if (a.k_scale != nullptr) {
     const long long n_tok8 = static_cast<long long>(a.batch) * a.n_new;
     dim3 grid8(static_cast<unsigned>((n_tok8 + 3) / 4), static_cast<unsigned>(a.n_kv), 1);
     hipLaunchKernelGGL(append_q8_kernel, grid8, dim3(256), 0, stream, a);
     return hipGetLastError();
   }
-  if (a.n_new >= kBulkRun) {
-    // longer walks per wavefront share the per-lane set-up; short jobs keep one run per wavefront
-    // so that the chip still gets enough wavefronts
-    const long long runs = static_cast<long long>((a.n_new + kBulkRun - 1) / kBulkRun) * a.n_kv * a.batch;
-    const int rpw = runs >= 32768 ? 4 : runs >= 16384 ? 2 : 1;
-    const int per_wg = 4 * rpw * kBulkRun;
-    dim3 grid(static_cast<unsigned>((a.n_new + per_wg - 1) / per_wg), static_cast<unsigned>(a.n_kv),
-              static_cast<unsigned>(a.batch));
-    if ((a.d_v & 1) == 0) hipLaunchKernelGGL((append_bulk_kernel<true, false, false>), grid, dim3(256), 0, stream, a, rpw);
-    else hipLaunchKernelGGL((append_bulk_kernel<false, false, false>), grid, dim3(256), 0, stream, a, rpw);
-    return hipGetLastError();
-  }
+  if (a.n_new >= kBulkRun) return (a.d_v & 1) == 0 ? launch_bulk<true, false, false>(a, stream) : launch_bulk<false, false, false>(a, stream);
   const long long n_tok = static_cast<long long>(a.batch) * a.n_new;
   dim3 grid(static_cast<unsigned>((n_tok + 3) / 4), static_cast<unsigned>(a.n_kv), 1);
   hipLaunchKernelGGL(append_kernel, grid, dim3(256), 0, stream, a);
@@ -439,14 +440,6 @@ hipError_t launch_append(const AppendArgs& a, hipStream_t stream) {
 }
 
 // Query rows: k_new = input, k_cache = output (same layout), n_kv = number of query heads, group = G.
-hipError_t launch_rope_queries(const AppendArgs& a, hipStream_t stream) {
-  const long long runs = static_cast<long long>((a.n_new + kBulkRun - 1) / kBulkRun) * a.n_kv * a.batch;
-  const int rpw = runs >= 32768 ? 4 : runs >= 16384 ? 2 : 1;
-  const int per_wg = 4 * rpw * kBulkRun;
-  dim3 grid(static_cast<unsigned>((a.n_new + per_wg - 1) / per_wg), static_cast<unsigned>(a.n_kv),
-            static_cast<unsigned>(a.batch));
-  hipLaunchKernelGGL((append_bulk_kernel<true, true, false>), grid, dim3(256), 0, stream, a, rpw);
-  return hipGetLastError();
-}
+hipError_t launch_rope_queries(const AppendArgs& a, hipStream_t stream) { return launch_bulk<true, true, false>(a, stream); }
 
 }  // namespace rap

@@ -90,6 +90,42 @@ def test_range_counts(rap, n_split, n_tok):
     H.assert_attn_close(out.cpu().numpy(), O.prefill_attn_ref(qb, kd, vd, lens, scale), "%d ranges" % n_split)
 
 
+# around the numbers of 16-token runs up to which they are four tokens long: 1536 (bf16 append), 4096 (fp8), 1024 (queries)
+@pytest.mark.parametrize("n_new", [1024, 1025, 1536, 1537, 4096, 4103])
+def test_bulk_run_lengths(rap, n_new):
+    """A prefill-sized append and rotation as one call against the same tokens in calls of 48, which take the short runs
+    (an oracle test of their own): bit for bit, with a jump in the positions and rows that are skipped."""
+    P, dv, H16 = 9, 11, 16
+    cap = (n_new + 200 + 15) // 16 * 16
+    _say("bulk runs n_new=%d" % n_new)
+    g = torch.Generator(device=DEV); g.manual_seed(n_new)
+    rand = lambda *s: torch.randn(s, generator=g, device=DEV).to(torch.bfloat16)
+    kn, vn, q = rand(1, n_new, H16, 2 * P), rand(1, n_new, H16, dv), rand(1, n_new, 2 * H16, 2 * P)
+    pos = torch.arange(n_new, dtype=torch.int32, device=DEV)
+    pos[n_new // 2:] += 101
+    pos[5] = -1
+    pos = pos[None].contiguous()
+    keep = torch.arange(P, dtype=torch.int32, device=DEV).repeat(H16, 1).contiguous()
+    sc = torch.rand(H16, generator=g, device=DEV) * 0.02 + 0.01
+    shp = rap.shape(1, 2 * H16, H16, 128, P, dv, cap, 5e5)
+    done = []
+    for step in (n_new, 48):
+        k, v, k8, v8 = (torch.zeros((1, H16, cap, d), dtype=t, device=DEV) for t in (torch.bfloat16, torch.uint8) for d in (2 * P, dv))
+        rot = torch.empty_like(q)
+        for at in range(0, n_new, step):
+            n = min(step, n_new - at)
+            part = lambda x: x[:, at:at + n].contiguous()
+            rap.rap_rope_append(shp, n, part(kn), part(vn), part(pos), keep, k, v)
+            rap.rap_rope_append_q8(shp, n, part(kn), part(vn), part(pos), keep, k8, v8, sc, sc)
+            piece = torch.empty_like(part(q))
+            rap.rap_rope_queries(shp, n, part(q), part(pos), keep, piece)
+            rot[:, at:at + n] = piece
+        torch.cuda.synchronize()
+        done.append((k, v, k8, v8, rot))
+    for x, y in zip(*done):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
+
+
 # lengths of a batch in units of its longest: all full, all alike but shorter, spread out, empty and single-row ones among
 # long ones, one long one
 LENGTHS = {"full": lambda i, B: 1.0, "alike": lambda i, B: 0.6, "spread": lambda i, B: (i + 1) / B,
