@@ -435,9 +435,9 @@ rap_status_t rap_prefill_attn_ex(const rap_shape_t* shape, const rap_kv_cache_t*
 /* rap_prefill_attn_ex for launches that would otherwise leave most of the chip idle (a short chunk
  * of new tokens at the end of long sequences, few sequences): with a workspace the rows a query
  * block sees are cut into key ranges as well, each range a workgroup of its own, and a combining
- * launch (the one of rap_decode_attn) follows.  Whether and how a launch is cut depends on the
+ * launch follows.  Whether and how a launch is cut depends on the
  * shape, n_new and max_seq_len alone: rap_prefill_attn_split_workspace_bytes returns the bytes
- * needed, 0 when the launch is not cut (then workspace may be NULL and the call is
+ * needed, 0 when the launch is never cut (then workspace may be NULL and the call is
  * rap_prefill_attn_ex).  A missing, misaligned (256 bytes) or too small workspace is
  * RAP_ERR_WORKSPACE.  Results equal those of rap_prefill_attn_ex up to fp32 rounding; where the launch
  * is cut, rows that the former makes NaN come out as rap_decode_attn has them. */

@@ -94,7 +94,8 @@ size_t partial_bytes(const rap_shape_t* s, int n_split, int n_tok) {
 int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap::kSplitQuantum * rap::kSplitQuantum; }
 
 // Row range per workgroup, a function of the shape and max_seq_len alone.  A workgroup whose range
-// starts at or beyond its sequence's length exits at once.  Measured on MI355X (bf16, d = 90, 8 KV
+// starts at or beyond its sequence's length exits at once.  (From 768 rows on the ranges of unequal sequences follow their
+// lengths instead, plan_by_length; the ragged figures here are from before that and say what fixed ranges cost them.)  Measured on MI355X (bf16, d = 90, 8 KV
 // heads unless said otherwise, attention call in a graph; "ragged": lengths spread evenly from
 // max / 16 to max, which the host cannot see):
 //  * A launch takes 6.9 us with one 128-row step per workgroup and 1.25 us more for each further
@@ -222,7 +223,7 @@ void plan_by_length(rap::DecodeArgs& a, bool fused_step) {
 
 // Workspace = accumulators [B, H_q, n_split + 1, d_v], then (reference, sum) pairs
 // [B, H_q, n_split + 1, 2], fp32, each block rounded up to 256 bytes; the extra slot is the new
-// token's in the one-call step.
+// token's in the one-call step.  (Ranges by length lay the same room out by KV head.)
 // With n_tok query tokens per sequence there are n_tok times as many query rows.
 size_t part_acc_bytes(const rap_shape_t* s, const Plan& p, int n_tok = 1) {
   return align_up(static_cast<size_t>(s->batch) * n_tok * s->n_q_heads * (p.n_split + 1) * s->d_v * sizeof(float), 256);
