@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256) void append_bulk_kernel(AppendArgs a, int runs
 
 // Either way: queries, 1024 runs of 16 tokens 6.3 and 5.6 us, 2040 8.8 and 9.1; appends, 1512 9.1 and 8.4, 4096 13.5 and
 // 17.0; fp8, 3160 24.3 and 22.0, 4016 the same.
-constexpr int brief_runs(bool query, bool q8) { return q8 ? 4096 : query ? 1024 : 1536; }
+constexpr int brief_runs(bool query, bool q8) { return q8 ? 3584 : query ? 1024 : 1536; }
 
 template <bool VDWORD, bool QUERY, bool Q8>
 hipError_t launch_bulk(const AppendArgs& a, hipStream_t stream) {

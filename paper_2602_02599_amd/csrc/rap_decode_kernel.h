@@ -124,6 +124,7 @@ __device__ __forceinline__ void token_load(const DecodeArgs& a, int b, int h, in
   }
 }
 
+template <bool FLAT>
 __device__ __forceinline__ void token_finish(const DecodeArgs& a, int b, int h, int lane, int t, bool attended,
                                              const uint16_t* s_q, const TokenRegs& r) {
   const int P = a.n_pairs;
@@ -191,8 +192,8 @@ __device__ __forceinline__ void token_finish(const DecodeArgs& a, int b, int h, 
       float part = lane < P ? fmaf(bf16_to_f32(qx), kxf, bf16_to_f32(qy) * kyf) : 0.f;
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
-      const long long slot = a.flat_wgs > 0 ? (static_cast<long long>(h) * a.flat_slots + a.flat_slots - a.batch + b) * a.group + g
-                                            : (static_cast<long long>(b) * a.n_q + h * a.group + g) * a.n_slots + a.n_split;
+      const long long slot = FLAT ? (static_cast<long long>(h) * a.flat_slots + a.flat_slots - a.batch + b) * a.group + g
+                                  : (static_cast<long long>(b) * a.n_q + h * a.group + g) * a.n_slots + a.n_split;
       if (lane == 0) {
         a.part_ml[slot * 2 + 0] = attended ? part * score_scale : -INFINITY;
         a.part_ml[slot * 2 + 1] = attended ? 1.f : 0.f;
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM !=
       rotate_queries_to_lds(a, b, h, tid, 256, s_q);
       __syncthreads();
     }
-    if (wave == 0) token_finish(a, b, h, lane, t_skip, tok_attended, rope_q ? s_q : nullptr, tk);
+    if (wave == 0) token_finish<FLAT>(a, b, h, lane, t_skip, tok_attended, rope_q ? s_q : nullptr, tk);
     return;
   }
   const int r0 = FLAT ? row0 : split * a.rows_per_split;

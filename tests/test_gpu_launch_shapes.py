@@ -90,8 +90,8 @@ def test_range_counts(rap, n_split, n_tok):
     H.assert_attn_close(out.cpu().numpy(), O.prefill_attn_ref(qb, kd, vd, lens, scale), "%d ranges" % n_split)
 
 
-# around the numbers of 16-token runs up to which they are four tokens long: 1536 (bf16 append), 4096 (fp8), 1024 (queries)
-@pytest.mark.parametrize("n_new", [1024, 1025, 1536, 1537, 4096, 4103])
+# around the numbers of 16-token runs up to which they are four tokens long: 1536 (bf16 append), 3584 (fp8), 1024 (queries)
+@pytest.mark.parametrize("n_new", [1024, 1025, 1536, 1537, 3584, 3591])
 def test_bulk_run_lengths(rap, n_new):
     """A prefill-sized append and rotation as one call against the same tokens in calls of 48, which take the short runs
     (an oracle test of their own): bit for bit, with a jump in the positions and rows that are skipped."""
