@@ -776,6 +776,17 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM !=
       for (int j = 0; j < 8; ++j) vo_laid[j] = (16 * (j >> 2) + 4 * lg + (j & 3)) * pitch_v + VLANE * l16;
     }
   };
+  // The query fragments are here before the lean loop.  Left to the compiler, a loop in whose first pass they may still be
+  // on their way waits in every pass, between the loads of the next tile and the first matrix instruction, and so for that
+  // tile as well: 4-bit, 29 pairs, d_v = 30, 1 x 131072 rows 30.0 us, so 24.7; bf16, d_v = 62, 24 x 4096 35.2 and 33.4.
+  if constexpr (FORM != kShortRanges) {
+#pragma unroll
+    for (int kk = 0; kk < KCH; ++kk) {
+      u32x4_t f = __builtin_bit_cast(u32x4_t, qf[kk]);
+      asm volatile("" : "+v"(f));
+      qf[kk] = __builtin_bit_cast(bf16x8, f);
+    }
+  }
   // All tiles but a wavefront's last one or two are lean: loads without a condition need no copies of the registers
   // they go to (60 to 150 instructions of a tile's 390 to 330), and no row masks.  16 x 32768 rows, 4-bit, 89.4 -> 81.9 us;
   // fp8 32 x 16384 126.2 -> 121.9, ragged 40 x 7989 48.2 -> 41.8; bf16 10 x 30925 124.7 -> 119.7, 16 x 8192 61.8

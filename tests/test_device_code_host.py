@@ -160,3 +160,81 @@ def test_hand_written_load_declares_m0(tmp_path):
     steps = re.findall(r"s_mov_b32 m0|global_load_lds_dword\w*", asm.read_text())
     assert steps == ["s_mov_b32 m0", "global_load_lds_dword", "s_mov_b32 m0", "global_load_lds_dwordx4",
                      "s_mov_b32 m0", "global_load_lds_dword"], steps
+
+
+def _loops(code):
+    """Sets of instructions that can reach each other: the loops of a function (iterative Tarjan)."""
+    index, low, on, stack, out, n = {}, {}, set(), [], [], 0
+    follow = [([to] if to is not None else []) + ([] if op in ("s_branch", "s_endpgm") or i + 1 == len(code) else [i + 1])
+              for i, (op, _, to) in enumerate(code)]
+    for root in range(len(code)):
+        if root in index:
+            continue
+        work = [(root, iter(follow[root]))]
+        index[root] = low[root] = n
+        n += 1
+        stack.append(root)
+        on.add(root)
+        while work:
+            v, nexts = work[-1]
+            for w in nexts:
+                if w not in index:
+                    index[w] = low[w] = n
+                    n += 1
+                    stack.append(w)
+                    on.add(w)
+                    work.append((w, iter(follow[w])))
+                    break
+                if w in on:
+                    low[v] = min(low[v], index[w])
+            else:
+                work.pop()
+                if work:
+                    low[work[-1][0]] = min(low[work[-1][0]], low[v])
+                if low[v] == index[v]:
+                    part = set()
+                    while True:
+                        w = stack.pop()
+                        on.discard(w)
+                        part.add(w)
+                        if w == v:
+                            break
+                    if len(part) > 1:
+                        out.append(part)
+    return out
+
+
+def test_tile_in_flight_is_not_waited_for(functions):
+    """Decode kernels for long ranges of dense caches: the loop over whole tiles has no wait for all loads between
+    those of the next tile and the first matrix instruction, which works on the tile before it."""
+    n, bad = 0, []
+    for name, code in functions:
+        form = re.search(r"decode_mfma_kernelILi(\d+)ELi(\d+)ELb\dELb(\d)ELb(\d)ELb\dELi(\d+)ELi(\d)E", name)
+        if not form or form.group(3) == "1" or form.group(6) == "0":
+            continue
+        k, nt, q8, mx4 = (int(form.group(i)) for i in (1, 2, 4, 5))
+        tile = 2 + (mx4 + 1) // 2 if mx4 else k + nt // 2 if q8 else 2 * k + nt
+        for part in _loops(code):
+            loads = [i for i in part if code[i][0] == "global_load_dwordx4" and code[i][1][-1].endswith(" nt")]
+            # the loop over the last tiles has loads for parts of a tile beside those of a whole one
+            if not 0 < len(loads) <= tile + 1 or not any(code[i][0].startswith("v_mfma") for i in part):
+                continue
+            n += 1
+            todo, seen = [i + 1 for i in loads], set()
+            while todo:
+                j = todo.pop()
+                while j in part and j not in seen:
+                    seen.add(j)
+                    op, args, to = code[j]
+                    if op.startswith("v_mfma"):
+                        break
+                    if op == "s_waitcnt" and "vmcnt(0)" in ",".join(args):
+                        bad.append("%s at %d" % (name, j))
+                        break
+                    if to is not None:
+                        todo.append(to)
+                    if op in ("s_branch", "s_endpgm"):
+                        break
+                    j += 1
+    assert n > 150
+    assert not bad, "%d, first: %s" % (len(bad), bad[0])
