@@ -95,7 +95,7 @@ int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap:
 
 // Row range per workgroup, a function of the shape and max_seq_len alone.  A workgroup whose range
 // starts at or beyond its sequence's length exits at once.  (From 768 rows on the ranges of unequal sequences follow their
-// lengths instead, plan_by_length; the ragged figures here are from before that and say what fixed ranges cost them.)  Measured on MI355X (bf16, d = 90, 8 KV
+// lengths instead, FlatPlan; the ragged figures here are from before that and say what fixed ranges cost them.)  Measured on MI355X (bf16, d = 90, 8 KV
 // heads unless said otherwise, attention call in a graph; "ragged": lengths spread evenly from
 // max / 16 to max, which the host cannot see):
 //  * A launch takes 6.9 us with one 128-row step per workgroup and 1.25 us more for each further
@@ -193,32 +193,6 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
   p->n_split = ranges_of(r);
   p->flat = p->kernel == 2 && s->batch > 1 && s->batch <= rap::kWave;
   return RAP_OK;
-}
-
-// Ranges by length: how many per KV head, for sequences that are not of one length, and room in the plan's partials for
-// them and for those of full sequences.  Two workgroups per compute unit, all ranges about as long as each other, where
-// that leaves two and a half or more per sequence; else as many as the chip holds (three per unit up to d_k = 96), else
-// four per sequence.  Before and now (lengths spread evenly from max / 16 to max; equal lengths are as before to 1 %): bf16
-// 4 x 131072, d = 64, 163.2 -> 95.0 us, 7 x 125041, 4 KV heads, 154.5 -> 119.3, 10 x 30925 84.1 -> 70.6, 16 x 8192 42.3 -> 38.5,
-// 48 x 3000, 4 KV heads, 32.0 -> 26.2; fp8 40 x 7989, 4 KV heads, 41.8 -> 34.2; 4-bit 16 x 32768 77.6 -> 54.8.  In 384 /
-// 448 / 512 workgroups: 4 x 131072 124 / 108 / 98 us, 16 x 8192 44 / 42 / 41; in 512 / 768 / 1536 / 2048: fp8 32 x 16384 85 /
-// 81 / 83 / 83, bf16 64 x 16384 (one per sequence / ) 285 / 264 / 257.  Not for ranges of full sequences below 768 rows (1024
-// where the combining kernel has more to do): looking at the lengths costs both kernels some 0.5 us.
-void plan_by_length(rap::DecodeArgs& a, bool fused_step) {
-  const int cus = device_cus(), places = cus * (a.d_k <= 96 ? 3 : 2);
-  int w = 2 * cus / a.n_kv;
-  if (2 * w < 5 * a.batch) w = places / a.n_kv;
-  if (2 * w < 5 * a.batch) w = 4 * a.batch;
-  const int room = a.batch * (fused_step ? a.n_split : a.n_split + 1);
-  if (w > room) w = room;
-  const int len = a.max_len - (fused_step ? 1 : a.n_tok > 1 ? a.n_tok : 0);
-  const int shortest = fused_step || a.n_tok > 1 ? 1024 : 768;
-  if (a.n_split < 2 || a.rows_per_split < shortest || w < 2 * a.batch || len < 1) return;
-  a.flat_wgs = w;
-  a.flat_units = (len + rap::kSplitQuantum - 1) / rap::kSplitQuantum;
-  const int r = (a.flat_units + a.n_split - 1) / a.n_split;
-  a.flat_full = (a.flat_units + r - 1) / r;
-  a.flat_slots = (w > a.batch * a.n_split ? w : a.batch * a.n_split) + (fused_step ? a.batch : 0);
 }
 
 // Workspace = accumulators [B, H_q, n_split + 1, d_v], then (reference, sum) pairs
@@ -466,7 +440,13 @@ rap_status_t decode_impl(const DecodeRequest& r) {
     a.v_cache_w = static_cast<uint16_t*>(const_cast<void*>(r.v_cache));
   }
 
-  if (p.flat && combine) plan_by_length(a, fused_step);
+  if (p.flat && combine) {
+    const rap::FlatPlan f = rap::flat_plan(a.batch, a.n_kv, a.d_k, a.n_split, a.rows_per_split, a.max_len, a.n_tok, fused_step, device_cus());
+    a.flat_wgs = f.wgs;
+    a.flat_slots = f.slots;
+    a.flat_full = f.full;
+    a.flat_few = f.few;
+  }
   hipStream_t s = static_cast<hipStream_t>(r.stream);
   if (step && !fused_step) {
     // vector-ALU kernel: the append is a launch of its own ahead of the attention

@@ -166,6 +166,75 @@ __host__ __device__ __forceinline__ void decode_place(int wg, int n_split, int n
   *h = (wg - seq_range * n_kv + (few ? nth + *b : 0)) % n_kv;
 }
 
+// Ranges by length: the rows of a batch's sequences, counted in units of kSplitQuantum rows, are cut into ranges that are
+// about as long as each other whatever the sequences' lengths, which only the device knows.  What the host can say:
+// `wgs` ranges at most per KV head for sequences of unequal length (0: ranges are of a fixed length), `full` of each
+// sequence where all are as long as they may be, `few` of each that the chip holds at once, and room for `slots` partials.
+constexpr int kSplitQuantum = 128;   // rows_per_split granularity
+struct FlatPlan {
+  int wgs, slots, full, few;
+};
+// Two workgroups per compute unit where that leaves two and a half or more per sequence; else as many as the chip holds
+// (three per unit up to d_k = 96), else four per sequence.  Fixed ranges and these (lengths spread evenly from max / 16 to
+// max): bf16 4 x 131072, d = 64, 163.2 -> 95.0 us, 7 x 125041, 4 KV heads, 154.5 -> 119.3, 10 x 30925 84.1 -> 70.6, 16 x 8192 42.3
+// -> 38.5, 48 x 3000, 4 KV heads, 32.0 -> 26.2; fp8 40 x 7989, 4 KV heads, 41.8 -> 34.2; 4-bit 16 x 32768 77.6 -> 54.8.  In 384 /
+// 448 / 512 workgroups: 4 x 131072 124 / 108 / 98 us, 16 x 8192 44 / 42 / 41; in 512 / 768 / 1536 / 2048: fp8 32 x 16384 85 /
+// 81 / 83 / 83, bf16 64 x 16384 (one per sequence / ) 285 / 264 / 257.  As many as the partials' room holds where
+// that is two or more times as many: 33 x 16384, half of them an eighth as long, 146 -> 140 us, but fp8 24 x 16384 57 -> 62
+// to 70, 12 x 30000 50 -> 59.  Not for ranges of full sequences below 768 rows (1024 where the combining kernel has more to
+// do): looking at the lengths costs both kernels some 0.5 us.
+inline FlatPlan flat_plan(int batch, int n_kv, int d_k, int n_split, int rows_per_split, int max_len, int n_tok, bool fused_step,
+                          int cus) {
+  const int places = cus * (d_k <= 96 ? 3 : 2);
+  int w = 2 * cus / n_kv;
+  if (2 * w < 5 * batch) w = places / n_kv;
+  if (2 * w < 5 * batch) w = 4 * batch;
+  const int room = batch * (fused_step ? n_split : n_split + 1);
+  if (w > room) w = room;
+  const int len = max_len - (fused_step ? 1 : n_tok > 1 ? n_tok : 0);
+  const int shortest = fused_step || n_tok > 1 ? 1024 : 768;
+  FlatPlan p = {0, 0, 0, 0};
+  if (n_split < 2 || rows_per_split < shortest || w < 2 * batch || len < 1) return p;
+  p.wgs = w;
+  const int units = (len + kSplitQuantum - 1) / kSplitQuantum, r = (units + n_split - 1) / n_split;
+  p.full = (units + r - 1) / r;
+  p.few = places / (n_kv * batch);
+  p.slots = (w > batch * n_split ? w : batch * n_split) + (fused_step ? batch : 0);
+  return p;
+}
+// Whether sequences of `total` units in all have as many ranges each, cut evenly: where they are shorter than the longest by an
+// eighth at most on average.  Ranges of one length for all of them then come to two or three per sequence at the
+// same time and leave the chip part idle.  One range length for all / as many ranges for each: 24 x 8192 rows, one
+// sequence 128 rows shorter, 96.1 / 88.2 us, lengths in 0.9..1 89.0 / 85.4; 33 x 16384 279 / 243; fp8 36 x 16384 161 /
+// 139.5.  Lengths in 0.5..1: 16 x 8192 49.1 / 48.3, 22 x 8192 66.3 / 66.1, 4 x 131072 179 / 181, 12 x 30000, 4 KV heads, 71.5 /
+// 72.9, 64 x 16384 340 / 347.
+__host__ __device__ __forceinline__ bool flat_alike(int total, int longest, int batch) {
+  return 8LL * total >= 7LL * batch * longest;
+}
+// How many: as many as of full sequences, but none shorter than 8 units beyond what the chip holds at once.  64 sequences of
+// 1024 rows of at most 16384, in 8 ranges 51.6 us, so 38.1; fp8 46.1 -> 26.6; 48 of 512 of at most 4096 24.2 -> 20.3.
+__host__ __device__ __forceinline__ int flat_alike_ranges(int longest, int full, int few) {
+  int n = longest / 8;
+  n = n < few ? few : n;
+  n = n < longest ? n : longest;
+  return n < full ? (n > 0 ? n : 1) : full;
+}
+// Else the shortest range, of four units or more, that leaves no more than `most` of them (most > batch); count(r): how many
+// ranges of up to r units there are.  One unit or more / four: one sequence of 4096 rows and 47 of 256, 21.9 / 17.9 us; one
+// of 8192 and 15 of 512, 17.1 / 15.6, 21 of 512, 17.8 / 18.3.
+constexpr int kFlatLeast = 4;
+template <class Count>
+__host__ __device__ __forceinline__ int flat_length(int total, int batch, int most, Count count) {
+  // a sequence has one range that is not whole at most, so no longer ones than hi are needed
+  int hi = total / (most - batch) + 1, r = (total + most - 1) / most;
+  r = r < kFlatLeast ? kFlatLeast : r;
+  while (r < hi) {
+    const int mid = (r + hi) >> 1;
+    if (count(mid) <= most) hi = mid;
+    else r = mid + 1;
+  }
+  return r;
+}
 // First unit of piece `nth` of `n` that a sequence of `units` is cut into: the longer ones first.
 __host__ __device__ __forceinline__ int flat_begin(int nth, int n, int units) {
   const int whole = units / n, more = units - whole * n;

@@ -16,7 +16,6 @@ constexpr int kMaxPairs = 64;        // P <= 64  (d_k <= 128)
 constexpr int kMaxDv = 128;
 constexpr int kMaxGroup = 8;         // query heads per KV head: vector-ALU kernel, fused query rotation, one-call step
 constexpr int kMaxGroupWide = 16;    // the same for the matrix-core attention kernels (16 columns per instruction)
-constexpr int kSplitQuantum = 128;   // rows_per_split granularity
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -118,11 +117,11 @@ struct DecodeArgs {
   int32_t max_len, rows_per_split, n_split;
   int32_t n_slots;          // partial slots per query head: n_split, plus one in the decode step
   int32_t lds_wave_bytes;   // matrix-core kernel: LDS slice of one wavefront
-  // Ranges by length (flat_wgs > 0; matrix-core kernel, up to 64 sequences): how many ranges a sequence has is found on the
-  // device, from its length and the others': flat_full where all have flat_units units of 128 rows, the most they may;
-  // else so many that the ranges are about as long as each other and no more than flat_wgs per KV head.  Partials are
-  // then [H_kv, flat_slots, n_tok * group], sequence by sequence, range by range, the new tokens of a decode step behind.
-  int32_t flat_wgs, flat_slots, flat_full, flat_units;
+  // Ranges by length (flat_wgs > 0, FlatPlan; matrix-core kernel, up to 64 sequences): how many ranges a sequence has is found
+  // on the device, from its length and the others': as many as every other where they are about of one length, else so many
+  // that the ranges are about as long as each other and no more than flat_wgs per KV head.  Partials are then
+  // [H_kv, flat_slots, n_tok * group], sequence by sequence, range by range, the new tokens of a decode step behind.
+  int32_t flat_wgs, flat_slots, flat_full, flat_few;
   int64_t cap;
   float scale_log2e;   // softmax scale * log2(e): exponentials are taken as exp2
 };
@@ -269,6 +268,17 @@ __device__ __forceinline__ int wave_sum_to(int v) {
   return v;
 }
 
+// The same for the largest, of numbers that are not negative.
+__device__ __forceinline__ int wave_max_to(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+  return v;
+}
+
 // Ranges by length (DecodeArgs): the row ranges of a KV head's sequences, found by each wavefront for itself, lane b
 // with sequence b.
 struct FlatRange {
@@ -277,7 +287,8 @@ struct FlatRange {
 };
 struct FlatLens {
   int units;          // of sequence `lane`
-  bool full;          // all sequences are as long as they may be
+  int total;          // of all
+  int alike;          // ranges that every sequence has, where they are about of one length, else 0
 };
 __device__ __forceinline__ FlatLens flat_lens(const DecodeArgs& a, int lane) {
   FlatLens r;
@@ -289,46 +300,37 @@ __device__ __forceinline__ FlatLens flat_lens(const DecodeArgs& a, int lane) {
     if (a.n_tok > 1) len = len > a.n_tok ? len - a.n_tok : 0;
   }
   r.units = (len + kSplitQuantum - 1) / kSplitQuantum;
-  r.full = __ballot(lane < a.batch && r.units != a.flat_units) == 0;
+  r.total = __builtin_amdgcn_readlane(wave_sum_to(r.units), kWave - 1);
+  const int longest = __builtin_amdgcn_readlane(wave_max_to(r.units), kWave - 1);
+  r.alike = flat_alike(r.total, longest, a.batch) ? flat_alike_ranges(longest, a.flat_full, a.flat_few) : 0;
   return r;
 }
-// Ranges of sequence `lane`, and of it and all before it: as many as of a full one where all are of one length, else
-// by the shortest range that leaves no more than flat_wgs of them.
-__device__ __forceinline__ void flat_counts(const DecodeArgs& a, int lane, int units, int* n, int* n_to) {
-  const int first = __builtin_amdgcn_readfirstlane(units);
-  int r;
-  if (__ballot(lane < a.batch && units != first) == 0) {
-    r = first > a.n_split ? (first + a.n_split - 1) / a.n_split : 1;
-  } else {
-    // a sequence has one range that is not whole at most, so no longer ones than hi are needed
-    const int total = __builtin_amdgcn_readlane(wave_sum_to(units), kWave - 1);
-    int hi = total / (a.flat_wgs - a.batch) + 1;
-    r = (total + a.flat_wgs - 1) / a.flat_wgs;
-    while (r < hi) {
-      const int mid = (r + hi) >> 1;
-      if (__builtin_amdgcn_readlane(wave_sum_to((units + mid - 1) / mid), kWave - 1) <= a.flat_wgs) hi = mid;
-      else r = mid + 1;
-    }
-  }
+// Where they are not alike: ranges of sequence `lane`, and of it and all before it.
+__device__ __forceinline__ void flat_counts(const DecodeArgs& a, const FlatLens& l, int* n, int* n_to) {
+  const uint32_t units = l.units;
+  const uint32_t r = flat_length(l.total, a.batch, a.flat_wgs, [&](uint32_t rows) {
+    return __builtin_amdgcn_readlane(wave_sum_to((units + rows - 1) / rows), kWave - 1);
+  });
   *n = (units + r - 1) / r;
   *n_to = wave_sum_to(*n);
 }
 __device__ __forceinline__ FlatRange flat_range(const DecodeArgs& a, int lane, int which) {
   const FlatLens l = flat_lens(a, lane);
   FlatRange r;
-  if (l.full) {
-    r.n = a.flat_full;
-    r.b = which / r.n;
-    r.nth = which - r.b * r.n;
+  int n = l.alike, first = 0, n_to;
+  if (l.alike > 0) {
+    r.b = which / n;
+    first = r.b * n;
   } else {
-    int n, n_to;
-    flat_counts(a, lane, l.units, &n, &n_to);
+    flat_counts(a, l, &n, &n_to);
     r.b = __popcll(__ballot(n_to <= which));           // sequences that end with an earlier range
     if (r.b >= a.batch) return r;
-    r.n = __builtin_amdgcn_readlane(n, r.b);
-    r.nth = which - (__builtin_amdgcn_readlane(n_to, r.b) - r.n);
+    n = __builtin_amdgcn_readlane(n, r.b);
+    first = __builtin_amdgcn_readlane(n_to, r.b) - n;
   }
   if (r.b >= a.batch) return r;
+  r.n = n;
+  r.nth = which - first;
   r.units = __builtin_amdgcn_readlane(l.units, r.b);
   return r;
 }

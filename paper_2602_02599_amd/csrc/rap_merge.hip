@@ -151,16 +151,19 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
   }
   int n;                                           // ranges that hold rows
   if constexpr (FLAT) {
-    n = a.flat_full;
-    if (!f.full) {
+    int first;
+    if (f.alike > 0) {
+      n = min(f.alike, __builtin_amdgcn_readlane(f.units, b));
+      first = b * f.alike;
+    } else {
       int n_of, n_to;
-      flat_counts(a, threadIdx.x & (kWave - 1), f.units, &n_of, &n_to);
+      flat_counts(a, f, &n_of, &n_to);
       n = __builtin_amdgcn_readlane(n_of, b);
-      const int first = __builtin_amdgcn_readlane(n_to, b) - n;
-      if (first != slot0) {
-        slot0 = first;
-        if (kMergeSlots * grp < n) request(kMergeSlots * grp);
-      }
+      first = __builtin_amdgcn_readlane(n_to, b) - n;
+    }
+    if (first != slot0) {
+      slot0 = first;
+      if (kMergeSlots * grp < n) request(kMergeSlots * grp);
     }
   } else {
     if (len > 0 && t_new == len - 1) len -= 1;     // the first stage stopped before the new token's row

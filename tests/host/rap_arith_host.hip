@@ -20,6 +20,12 @@
 //                               sequences lie, at least; exit status 1 if placed wrongly or on fewer than 4
 //   rap_arith_host place-rotated  the same with every number of ranges rotated by the sequence (a
 //                               planted mistake: odd numbers then pile up)
+//   rap_arith_host flat      -> text, one line per (sequences, KV heads, width, rows, range, several tokens or the one-call
+//                               step, pattern of lengths): whether ranges by length cover every sequence once inside
+//                               the partials' room, and the rows on the fullest of 256 compute units, in units of 128,
+//                               against those of full sequences
+//   rap_arith_host flat-one-length  the same with one range length for all sequences that are not equal (a planted
+//                               mistake: nearly equal lengths then fill the chip worse than equal ones)
 //   rap_arith_host prefill-place -> text, one line per (query blocks, slabs, key ranges, group): whether every
 //                               (block, slab, range) is placed once, on how many XCDs a slab lies, and how
 //                               often a query block follows a lighter one within a group of slabs
@@ -181,6 +187,65 @@ int prefill_cut_up() {
   return bad;
 }
 
+int flat(bool one_length) {
+  const int cus = 256;
+  int bad = 0;
+  for (int batch : {2, 3, 7, 9, 16, 22, 24, 33, 36, 40, 48, 64})
+    for (int n_kv : {1, 3, 4, 8})
+      for (int d_k : {90, 116})
+        for (int max_len : {2500, 4096, 8192, 16384, 50001, 131072})
+          for (int rows : {512, 768, 1024, 1408, 2048, 2816, 4096, 8192})
+            for (int how = 0; how < 3; ++how) {             // plain, five tokens, the one-call step
+              const int n_split = (max_len + rows - 1) / rows, n_tok = how == 1 ? 5 : 1;
+              const rap::FlatPlan p = rap::flat_plan(batch, n_kv, d_k, n_split, rows, max_len, n_tok, how == 2, cus);
+              if (p.wgs == 0) continue;
+              const int most = (max_len - (how == 2 ? 1 : how == 1 ? 5 : 0) + rap::kSplitQuantum - 1) / rap::kSplitQuantum;
+              const int scan_slots = p.slots - (how == 2 ? batch : 0);
+              int equal = 0;                                // rows on the fullest unit where all sequences are full
+              for (int pattern = 0; pattern < 9; ++pattern) {
+                std::vector<int> units(batch, 0);
+                int total = 0, longest = 0;
+                for (int b = 0; b < batch; ++b) {
+                  const int at[] = {most, b == 0 ? most - 1 : most, most - (b * 7 % 11) * most / 110, most - most * b / (4 * batch),
+                                    most / 16 + (most - most / 16) * b / batch, b == 0 ? most : 1, b % 3 == 0 ? 0 : most, most / 5, 0};
+                  units[b] = at[pattern];
+                  total += units[b];
+                  longest = units[b] > longest ? units[b] : longest;
+                }
+                const bool alike = rap::flat_alike(total, longest, batch) && !(one_length && pattern != 0);
+                const int r = alike ? 0 : rap::flat_length(total, batch, p.wgs, [&](int len) {
+                  int n = 0;
+                  for (int u : units) n += (u + len - 1) / len;
+                  return n;
+                });
+                int at = 0, wrong = 0, ranges = 0, longest_range = 0;
+                for (int b = 0; b < batch; ++b) {
+                  const int n = alike ? rap::flat_alike_ranges(longest, p.full, p.few) : (units[b] + r - 1) / r;
+                  int from = 0;
+                  for (int i = 0; i < n; ++i) {
+                    const int begin = rap::flat_begin(i, n, units[b]), end = rap::flat_begin(i + 1, n, units[b]);
+                    // those that hold rows come first: the combining kernel reads the first min(n, units)
+                    wrong += begin != from || end < begin || (end > begin) != (i < units[b]) || (!alike && end - begin > r);
+                    from = end;
+                    ranges += end > begin;
+                    longest_range = end - begin > longest_range ? end - begin : longest_range;
+                  }
+                  wrong += from != units[b];
+                  at += n;
+                }
+                wrong += at > scan_slots || p.slots > batch * (n_split + 1);
+                const int fullest = (ranges * n_kv + cus - 1) / cus * longest_range;
+                if (pattern == 0) equal = fullest;
+                // lengths within a tenth of each other: no more on any unit than with full ones (the chip is full with both)
+                const bool near = pattern <= 2;
+                printf("sequences=%d heads=%d d_k=%d rows=%d range=%d how=%d pattern=%d ranges=%d of=%d wrong=%d fullest=%d equal=%d\n", batch, n_kv,
+                       d_k, max_len, rows, how, pattern, ranges, scan_slots, wrong, fullest, equal);
+                bad += wrong != 0 || (near && fullest > equal);
+              }
+            }
+  return bad;
+}
+
 int place(bool always_rotated) {
   int bad = 0;
   for (int n_kv = 1; n_kv <= 16; n_kv = n_kv < 8 ? n_kv + 1 : n_kv + 8)
@@ -251,11 +316,13 @@ int pieceplan(bool read_whole) {
 
 int main(int argc, char** argv) {
   if (argc != 2) {
-    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|prefill-place|prefill-cut\n");
+    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|flat|flat-one-length|prefill-place|prefill-cut\n");
     return 2;
   }
   if (strcmp(argv[1], "loadplan") == 0) return loadplan(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "loadplan-trim1") == 0) return loadplan(true) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "flat") == 0) return flat(false) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "flat-one-length") == 0) return flat(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "prefill-place") == 0) return prefill_placed() == 0 ? 0 : 1;
   if (strcmp(argv[1], "prefill-cut") == 0) return prefill_cut_up() == 0 ? 0 : 1;
   if (strcmp(argv[1], "place") == 0) return place(false) == 0 ? 0 : 1;

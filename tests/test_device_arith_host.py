@@ -239,3 +239,18 @@ def test_prefill_key_ranges_cover_every_block_once(harness):
     assert len(lines) > 1000
     assert any(f["of"] == 1 for f in lines) and any(f["ranges"] > 128 for f in lines)
     assert rc == 0, [f for f in lines if f["wrong"] or f["unordered"] or (f["slabs"] % 8 == 0 and f["xcds"] != 1)][:5]
+
+
+def test_ranges_by_length_cover_and_fill(harness):
+    """The row ranges of a batch of unequal lengths, as the decode and the combining kernel find them: every unit of 128
+    rows once, inside the partials' room; and lengths within a tenth of each other put no more rows on any compute unit
+    than equal ones do.  One range length for all sequences does (a third more for 24 of 8192 rows, one of them 128
+    rows shorter)."""
+    rc, text = _run(harness, "flat")
+    lines = [dict((k, int(v)) for k, v in (kv.split("=") for kv in ln.split())) for ln in text.splitlines()]
+    assert len(lines) > 5000
+    assert rc == 0, [f for f in lines if f["wrong"] or (f["pattern"] <= 2 and f["fullest"] > f["equal"])][:5]
+    rc, text = _run(harness, "flat-one-length")
+    assert rc == 1
+    bad = [ln for ln in text.splitlines() if ln.startswith("sequences=24 heads=8 d_k=90 rows=8192 range=2048 how=0 pattern=1 ")]
+    assert len(bad) == 1 and bad[0].endswith("wrong=0 fullest=64 equal=48"), bad
