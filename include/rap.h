@@ -101,7 +101,7 @@ typedef struct rap_tuning {
  *   k_cache[b][h][t][c + P] = bf16( k_new[b][n][h][c] sin phi + k_new[b][n][h][c+P] cos phi )
  *   v_cache[b][h][t][:]     = v_new[b][n][h][:]                   (bit copy)
  * with one round-to-nearest-even to bf16.  Rows not named by pos are left untouched.
- * From n_new = 16 on, runs of 16 tokens whose positions go up by one take their first angle as
+ * From n_new = 16 on, runs of 4 or 16 tokens whose positions go up by one take their first angle as
  * above and advance it by one fp64 rotation per position (a difference of order 1e-16 in the
  * sine and cosine, far below the rounding to bf16).
  *
@@ -153,10 +153,18 @@ size_t rap_decode_attn_workspace_bytes(const rap_shape_t* shape, int64_t max_seq
  *              smaller workspace is accepted while it holds the ranges of a plainer rule (about two
  *              workgroups per compute unit, ranges of 512 to 4096 rows, up to 8192 where those fit
  *              the chip at once; none at all if that is one range), and gets those ranges, which can
- *              be slower; below that RAP_ERR_WORKSPACE.  So the cut, and with it the order of the
- *              fp32 sums, depends on shape, max_seq_len, tuning, device and on whether the workspace
- *              holds the queried size, and on nothing else.  No cut needs more than
+ *              be slower; below that RAP_ERR_WORKSPACE.  No cut needs more than
  *              RAP_STATIC_SCRATCH_BYTES where the plainer rule's does not.
+ *              The cut, and with it the order of the fp32 sums and which rows fall into one range,
+ *              depends on shape, max_seq_len, tuning, device, on whether the workspace holds the
+ *              queried size and, where that leaves the choice to the call (rows_per_split 0, a
+ *              workspace of the queried size, more than one sequence), on seq_lens: the ranges of a
+ *              sequence then follow the lengths of all sequences of the batch, so that its output can
+ *              differ in the last bits with the lengths of its neighbours.  It depends on nothing
+ *              else.  With rows_per_split set, or with the smaller workspace, every sequence is cut at
+ *              multiples of one number of rows that seq_lens has no part in, and an output row has the
+ *              same bits whatever the lengths of the other sequences are.  This holds for all decode
+ *              attention calls below (rotating, one-call step, fp8, 4-bit, paged, several tokens).
  * Cache rows at or beyond seq_lens[b] are never used in the result, whatever bits they hold.
  * An output row whose attended rows or query hold a NaN, or whose score overflows, is stored as zeros
  * where that makes its sum a NaN; a row range none of whose scores is a number counts as empty.

@@ -93,11 +93,13 @@ size_t partial_bytes(const rap_shape_t* s, int n_split, int n_tok) {
 
 int64_t round_to_quantum(int64_t r) { return (r + rap::kSplitQuantum - 1) / rap::kSplitQuantum * rap::kSplitQuantum; }
 
-// Row range per workgroup, a function of the shape and max_seq_len alone.  A workgroup whose range
-// starts at or beyond its sequence's length exits at once.  (From 768 rows on the ranges of unequal sequences follow their
-// lengths instead, FlatPlan; the ragged figures here are from before that and say what fixed ranges cost them.)  Measured on MI355X (bf16, d = 90, 8 KV
+// What the host picks: rows of a range, a function of the shape, max_seq_len, the tuning and the device.  Ranges of that many
+// rows are what a call gets with rows_per_split set, with the plain rule's workspace, with one sequence or more than 64, and
+// where they are below 768 rows (FlatPlan); a workgroup whose range starts at or beyond its sequence's length exits at
+// once.  Else the number of ranges comes from here and the device cuts the sequences by their lengths (FlatPlan), which
+// makes the order of a row's sums depend on the other sequences' lengths as well.  Measured on MI355X (bf16, d = 90, 8 KV
 // heads unless said otherwise, attention call in a graph; "ragged": lengths spread evenly from
-// max / 16 to max, which the host cannot see):
+// max / 16 to max, which the host cannot see; all with fixed ranges):
 //  * A launch takes 6.9 us with one 128-row step per workgroup and 1.25 us more for each further
 //    step; cutting into ranges adds a combining launch, 2.7 us.  So while one range per compute unit
 //    is at most 512 rows, that is the range, if it spares three steps or more (1 x 2048 rows: 14.0 us

@@ -1,0 +1,86 @@
+"""Decode attention whose row ranges follow the lengths of the batch, and what the header says of the order of the sums: with
+ranges of a fixed number of rows a sequence's output does not depend on its neighbours."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _say(msg):
+    print("[by length] " + msg, flush=True)
+
+
+class Cache:
+    """A cache of random rows; those at and beyond lens[b], and unused pages, hold NaN patterns."""
+
+    def __init__(self, rap, kind, P, dv, Hkv, cap, lens, seed):
+        B = len(lens)
+        self.kind, self.P, self.dv, self.cap, self.lens = kind, P, dv, cap, lens
+        self.g = g = torch.Generator(device=DEV)
+        g.manual_seed(seed)
+        self.scales, self.pg, self.table = (None, None), None, None
+        dense = []
+        for d in (2 * P, dv):
+            if kind == "mx4":
+                x = torch.randint(0, 256, (B, Hkv, cap, 16 * ((d + 31) // 32)), generator=g, device=DEV, dtype=torch.int32).to(torch.uint8)
+                s = torch.randint(123, 128, (B, Hkv, cap, 4), generator=g, device=DEV, dtype=torch.int32).to(torch.uint8)
+                for b in range(B):
+                    x[b, :, lens[b]:] = s[b, :, lens[b]:] = 0xFF
+                self.scales += (s,)
+            else:
+                x = torch.randn((B, Hkv, cap, d), generator=g, device=DEV, dtype=torch.bfloat16)
+                if kind.startswith("fp8"):
+                    x = (64.0 * x).to(torch.float8_e4m3fn).view(torch.uint8)
+                    self.scales += ((torch.rand(Hkv, generator=g, device=DEV) + 0.5) / 64.0,)
+                for b in range(B):
+                    if x.dtype == torch.uint8:
+                        x[b, :, lens[b]:] = 0x7F
+                    else:
+                        x[b, :, lens[b]:] = float("nan")
+            dense.append(x)
+        if len(self.scales) > 2:
+            self.scales = self.scales[2:]
+        if kind.endswith("paged"):
+            n = B * cap // 128
+            self.table = torch.randperm(n + 2, generator=g, device=DEV)[:n]
+            self.pg = rap.paging(128, n + 2, self.table.to(torch.int32).view(B, -1).contiguous())
+            pools = []
+            for x in dense:
+                pool = torch.full((n + 2, Hkv, 128, x.shape[-1]), 0x7F if x.dtype == torch.uint8 else float("nan"), dtype=x.dtype, device=DEV)
+                pool[self.table] = x.view(B, Hkv, -1, 128, x.shape[-1]).transpose(1, 2).flatten(0, 1)
+                pools.append(pool)
+            dense = pools
+        self.k, self.v = dense
+
+
+@pytest.mark.parametrize("kind", ["bf16", "fp8", "paged"])
+def test_fixed_ranges_do_not_depend_on_neighbours(rap, kind):
+    """24 sequences whose ranges would follow their lengths: with rows_per_split set, and with a workspace that only holds the
+    plainer rule's ranges (two of 4096 rows), an output row keeps its bits when the other sequences' lengths change."""
+    B, Hkv, Hq, P, dv, ctx = 24, 8, 8, 20, 41, 8192
+    c = Cache(rap, kind, P, dv, Hkv, ctx, [ctx] * B, 5)
+    shp = rap.shape(B, Hq, Hkv, 128, P, dv, ctx, 5e5)
+    up = lambda x: (x + 255) // 256 * 256
+    plain = up(B * Hq * 3 * dv * 4) + up(B * Hq * 3 * 8) + 256
+    assert plain < rap.rap_decode_attn_workspace_bytes(shp, ctx, None)
+    rand = lambda *s: torch.randn(s, generator=c.g, device=DEV, dtype=torch.bfloat16)
+    q, kn, vn = rand(B, Hq, 2 * P), rand(B, Hkv, 2 * P), rand(B, Hkv, dv)
+    keep = torch.arange(P, dtype=torch.int32, device=DEV).repeat(Hkv, 1).contiguous()
+    kept = {1: 5001, 13: 8192, 22: 130}
+    for rows in (1024, 0):
+        tun = rap.tuning(rows_per_split=rows)
+        size = rap.rap_decode_attn_workspace_bytes(shp, ctx, tun) if rows else plain
+        seen = []
+        for f in (lambda i: ctx, lambda i: 1 + (ctx - 1) * i // (B - 1), lambda i: 257, lambda i: ctx - 128 * (i % 3)):
+            _say("%s, neighbours change, rows_per_split %d" % (kind, rows))
+            sl = torch.tensor([kept.get(i, f(i)) for i in range(B)], dtype=torch.int32, device=DEV)
+            one, step = (torch.empty((B, Hq, dv), dtype=torch.float32, device=DEV) for _ in range(2))
+            ws = torch.full((size,), 0xFF, dtype=torch.uint8, device=DEV)
+            rap.rap_decode_attn_multi(shp, c.k, c.v, *c.scales, c.pg, 1, q, sl, ctx, one, 0.2, ws, tun)
+            k, v = c.k.clone(), c.v.clone()
+            rap.rap_decode_step_ex(shp, k, v, *c.scales, c.pg, kn, vn, sl - 1, keep, q, True, sl, ctx, step, 0.2, ws, tun)
+            torch.cuda.synchronize()
+            seen.append(torch.stack([x[list(kept)] for x in (one, step)]).view(torch.int32))
+        for x in seen[1:]:
+            assert torch.equal(seen[0], x)
