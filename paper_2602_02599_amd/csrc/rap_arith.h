@@ -274,6 +274,10 @@ __host__ __device__ __forceinline__ void prefill_place(int wg, int n_qblk, int s
 
 // A prefill launch cut into key ranges.  The rows a query block sees, in a sequence of max_len rows, are cut
 // into ranges of `per` 64-row tiles and what is left over: with causal visibility the early blocks of a
+// Compute units of a whole MI355X.  How a prefill launch is cut and dealt out goes by this number and not by the device's, so
+// that the workspace it asks for is a function of the shape alone; a device with fewer (a partition) gets the same results.
+constexpr int kChipUnits = 256;
+
 // long chunk have fewer ranges than the late ones, and a block of one range needs no partials.
 struct PrefillCut {
   int max_len, n_new, tok_per_wg, n_qblk, per;
@@ -331,7 +335,7 @@ __host__ __device__ __forceinline__ uint32_t prefill_inv(int slabs) {
 }
 __host__ __device__ __forceinline__ void prefill_place_cut(int wg, int n, int slabs, uint32_t inv, int* nth, int* slab) {
   const bool own_xcd = (slabs & 7) == 0;
-  const int shift = own_xcd ? 3 : 0, own = slabs >> shift, all = n * own, units = 256 >> shift;
+  const int shift = own_xcd ? 3 : 0, own = slabs >> shift, all = n * own, units = kChipUnits >> shift;
   int x = wg >> shift;
   if (all > units && all <= 2 * units) {
     const int both = all - units;

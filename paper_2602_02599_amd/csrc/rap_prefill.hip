@@ -9,6 +9,9 @@ hipError_t launch_prefill_ks2(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_prefill_ks3(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_prefill_ks4(const PrefillArgs& a, hipStream_t stream);
 
+// Query blocks from which on no launch is cut.
+constexpr int kMostBlocks = 3 * kChipUnits / 2;
+
 // How a call with a workspace is cut.  Nothing is cut while the query blocks number at least one and a half per
 // compute unit or the context is short; else the workspace has room for about 512 workgroups, in ranges of no less than four
 // tiles, which is what callers have to bring.  prefill_cut_plan then picks, within that, the ranges it expects to be
@@ -21,8 +24,8 @@ PrefillPlan prefill_plan(int batch, int n_kv, int group, int d_k, int d_v, int n
   p.tiles_per_split = 0;
   const long long base = static_cast<long long>(p.n_qblk) * n_kv * batch;
   const int tiles = (max_len + kPrefillTile - 1) / kPrefillTile;
-  if (base > 0 && base < 384 && tiles >= 8) {
-    const int want = static_cast<int>((512 + base - 1) / base);
+  if (base > 0 && base < kMostBlocks && tiles >= 8) {
+    const int want = static_cast<int>((2 * kChipUnits + base - 1) / base);
     int per = (tiles + want - 1) / want;
     if (per < 4) per = 4;
     p.slots = (tiles + per - 1) / per;
@@ -39,8 +42,8 @@ namespace {
 struct CutLengths {
   int per, full, n;
   bool ordered;
-  int tiles[384];
-  uint16_t block[384];
+  int tiles[kMostBlocks];
+  uint16_t block[kMostBlocks];
   int length(int nth) const { return nth < full ? per : tiles[nth - full]; }
 };
 void cut_lengths(const PrefillCut& c, CutLengths* out) {
@@ -51,7 +54,7 @@ void cut_lengths(const PrefillCut& c, CutLengths* out) {
   out->n = out->full + c.n_qblk;
   out->ordered = out->n <= kMaxOrdered;
   constexpr int kClasses = 256;                    // counting sort; longer ranges than that in classes
-  int first[kClasses + 1] = {0}, tiles[384];
+  int first[kClasses + 1] = {0}, tiles[kMostBlocks];
   const int step = c.per / kClasses + 1;
   for (int qb = 0; qb < c.n_qblk; ++qb) {
     const int t = prefill_range_tiles(c, qb, prefill_ranges(c, qb) - 1);
@@ -78,21 +81,21 @@ void cut_lengths(const PrefillCut& c, CutLengths* out) {
 double slowest_unit(const CutLengths& l, int slabs, double alone) {
   const int all = l.n * slabs;
   double worst = alone * l.length(0);
-  if (all <= 256) return worst;
-  if (all <= 512) {
-    for (int j = 0; j < all - 256; j += slabs < 8 ? 1 : 8) {
-      const double t = l.length((512 - all + j) / slabs) + l.length((all - 1 - j) / slabs);
+  if (all <= kChipUnits) return worst;
+  if (all <= 2 * kChipUnits) {
+    for (int j = 0; j < all - kChipUnits; j += slabs < 8 ? 1 : 8) {
+      const double t = l.length((2 * kChipUnits - all + j) / slabs) + l.length((all - 1 - j) / slabs);
       worst = t > worst ? t : worst;
     }
     return worst;
   }
-  // more than fit: each of 512 places takes the longest that is left when it is free; places in groups
+  // more than fit: each of the places takes the longest that is left when it is free; places in groups
   // that are free at the same time
   struct Group { double t; int n; };
   constexpr int kGroups = 64;
   Group free_[kGroups];
   int lo = 0, hi = 1;
-  free_[0] = {0.0, 512};
+  free_[0] = {0.0, 2 * kChipUnits};
   worst = 0.0;
   for (int i = 0; i < l.n;) {
     const int tiles = l.length(i);
@@ -124,6 +127,9 @@ double slowest_unit(const CutLengths& l, int slabs, double alone) {
 // rows, d = 86, 18 tiles 145 us, 20: 106; 3 x 512 at 8192 43 tiles 290, 52 and a last range of 24: 241; 5 x 448 at 4096 32
 // tiles 228, 43 and 21: 205; 9 x 200 at 6000, 20/4 heads, 24 tiles 174, 27 and 13: 142.  Chunks as long as their context: 2 x 3014
 // tokens, 12/4 heads, d = 56, 97 -> 78 us, 2048 tokens 92 -> 74, 4 x 600 tokens (left whole) 49 -> 41.
+// The ten or so lengths tried cost the host 1.5 us a call, 8 where there are 370 query blocks (6000 of 6000 tokens over 4 KV heads, a
+// call of 200 us on the device, 100 us less than in the first length that the workspace allows); nothing is kept from
+// one call for the next.
 void prefill_cut_plan(PrefillPlan* p, int slabs, int group, int d_k, int d_v, int n_new, int max_len, uint32_t* order) {
   const int ks = (d_k + 31) / 32, ct = (d_v + 15) / 16;
   const int tiles = (max_len + kPrefillTile - 1) / kPrefillTile, least = p->tiles_per_split, most = p->slots;

@@ -572,7 +572,7 @@ hipError_t launch_prefill_inst(PrefillArgs a, hipStream_t stream) {
   a.n_qblk = (a.n_new + a.tok_per_wg - 1) / a.tok_per_wg;
   constexpr size_t lds = 2 * static_cast<size_t>(kPrefillTile) * (prefill_k_pitch(KS) + prefill_v_pitch(CT));
   const long long slabs = static_cast<long long>(a.n_kv) * a.batch;
-  if (a.n_ksplit <= 1) a.n_ranges = a.n_qblk * slabs <= 512 ? a.n_qblk : 0;
+  if (a.n_ksplit <= 1) a.n_ranges = a.n_qblk * slabs <= 2 * kChipUnits ? a.n_qblk : 0;
   if (a.n_ranges > 0) a.slab_inv = prefill_inv(static_cast<int>(slabs));
   const long long n_wg = slabs * (a.n_ranges > 0 ? a.n_ranges : a.n_qblk);
   if (n_wg > 0x7fffffffLL) return hipErrorInvalidValue;
