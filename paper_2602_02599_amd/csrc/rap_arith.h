@@ -241,7 +241,8 @@ __host__ __device__ __forceinline__ int flat_begin(int nth, int n, int units) {
   return nth * whole + (nth < more ? nth : more);
 }
 
-// Which query block, slab (sequence and KV head) and key range workgroup `wg` of a prefill launch takes.
+// Which query block and slab (sequence and KV head) workgroup `wg` of a prefill launch takes that is not cut into key
+// ranges and whose workgroups do not all start together.
 // Hardware places workgroup L on XCD L mod 8, each with an L2 of its own, and all query blocks of a slab
 // read the same K and V rows: with a multiple of 8 slabs, all workgroups of a slab go to one XCD, which
 // works on `group` of its slabs side by side, the heaviest query blocks (the last tokens, which see the
@@ -253,31 +254,26 @@ __host__ __device__ __forceinline__ int flat_begin(int nth, int n, int units) {
 // query heads, 8 x 2395 183 / 125 / 125; codes 8 x 2048 377 / 316 / 315.  Wide rows (three column blocks)
 // with 4 / 8 / all: d = 128, 8 x 2048 426 one after the other, 411 / 403 / 402; 32 x 512 187, 181 / 187 / 197; 16 x
 // 8192 11.4 ms, 11.1 / 11.5 / 12.2; 32 x 4096 6.32 ms, 5.89 / 6.01 / 6.87.
-__host__ __device__ __forceinline__ void prefill_place(int wg, int n_qblk, int slabs, int n_ksplit, int group, int* qb, int* slab, int* ks) {
-  int r;
+__host__ __device__ __forceinline__ void prefill_place(int wg, int n_qblk, int slabs, int group, int* qb, int* slab) {
   if ((slabs & 7) == 0) {
-    const int x = wg >> 3, own = slabs >> 3, per_slab = n_qblk * n_ksplit;
-    const int first = x / per_slab / group * group;                              // of this XCD's slabs
-    const int level = (own - first < group ? own - first : group) * n_ksplit;    // workgroups per query block number
-    r = x - first * per_slab;
+    const int x = wg >> 3, own = slabs >> 3;
+    const int first = x / n_qblk / group * group;                                // of this XCD's slabs
+    const int level = own - first < group ? own - first : group;                 // workgroups per query block number
+    const int r = x - first * n_qblk;
     *qb = n_qblk - 1 - r / level;
-    r = r % level;
-    *slab = (first + r / n_ksplit) * 8 + (wg & 7);
-    *ks = r % n_ksplit;
+    *slab = (first + r % level) * 8 + (wg & 7);
   } else {
-    *ks = wg % n_ksplit;
-    r = wg / n_ksplit;
-    *slab = r % slabs;
-    *qb = n_qblk - 1 - r / slabs;
+    *slab = wg % slabs;
+    *qb = n_qblk - 1 - wg / slabs;
   }
 }
 
-// A prefill launch cut into key ranges.  The rows a query block sees, in a sequence of max_len rows, are cut
-// into ranges of `per` 64-row tiles and what is left over: with causal visibility the early blocks of a
 // Compute units of a whole MI355X.  How a prefill launch is cut and dealt out goes by this number and not by the device's, so
 // that the workspace it asks for is a function of the shape alone; a device with fewer (a partition) gets the same results.
 constexpr int kChipUnits = 256;
 
+// A prefill launch cut into key ranges.  The rows a query block sees, in a sequence of max_len rows, are cut
+// into ranges of `per` 64-row tiles and what is left over: with causal visibility the early blocks of a
 // long chunk have fewer ranges than the late ones, and a block of one range needs no partials.
 struct PrefillCut {
   int max_len, n_new, tok_per_wg, n_qblk, per;

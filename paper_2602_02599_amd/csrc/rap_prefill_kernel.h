@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
       in_ranges = prefill_ranges(c, qb) > 1;
     }
   } else {
-    prefill_place(static_cast<int>(blockIdx.x), a.n_qblk, a.n_kv * a.batch, 1, prefill_slabs(KS, CT), &qb, &slab_id, &ks);
+    prefill_place(static_cast<int>(blockIdx.x), a.n_qblk, a.n_kv * a.batch, prefill_slabs(KS, CT), &qb, &slab_id);
   }
   const int h = slab_id % a.n_kv;
   const int b = slab_id / a.n_kv;

@@ -103,28 +103,27 @@ int loadplan(bool trim_one_only) {
 int prefill_placed() {
   int bad = 0;
   for (int slabs : {1, 3, 8, 10, 16, 24, 64, 72, 128})
-    for (int n_qblk : {1, 2, 5, 16})
-      for (int n_ksplit : {1, 2, 5})
-        for (int group : {1, 4, 8}) {
-          const int n = slabs * n_qblk * n_ksplit;
-          std::vector<int> hit(n, 0), last(static_cast<size_t>(8) * slabs, n_qblk), xcd(slabs, 0);
-          int lighter = 0, wrong = 0;
-          for (int wg = 0; wg < n; ++wg) {
-            int qb, slab, ks;
-            rap::prefill_place(wg, n_qblk, slabs, n_ksplit, group, &qb, &slab, &ks);
-            if (qb < 0 || qb >= n_qblk || slab < 0 || slab >= slabs || ks < 0 || ks >= n_ksplit) return 1000000;
-            hit[(slab * n_qblk + qb) * n_ksplit + ks] += 1;
-            xcd[slab] |= 1 << (wg & 7);
-            int& before = last[(slabs & 7) == 0 ? (wg & 7) * slabs + (slab >> 3) / group : 0];   // the group's blocks so far
-            lighter += qb > before;
-            before = qb;
-          }
-          for (int x : hit) wrong += x != 1;
-          int spread = 1;
-          for (int x : xcd) spread = __builtin_popcount(x) > spread ? __builtin_popcount(x) : spread;
-          printf("blocks=%d slabs=%d ranges=%d group=%d wrong=%d xcds=%d lighter=%d\n", n_qblk, slabs, n_ksplit, group, wrong, spread, lighter);
-          bad += wrong != 0 || lighter != 0 || ((slabs & 7) == 0 && spread != 1);
+    for (int n_qblk : {1, 2, 5, 10, 16, 25, 80})
+      for (int group : {1, 4, 8}) {
+        const int n = slabs * n_qblk;
+        std::vector<int> hit(n, 0), last(static_cast<size_t>(8) * slabs, n_qblk), xcd(slabs, 0);
+        int lighter = 0, wrong = 0;
+        for (int wg = 0; wg < n; ++wg) {
+          int qb, slab;
+          rap::prefill_place(wg, n_qblk, slabs, group, &qb, &slab);
+          if (qb < 0 || qb >= n_qblk || slab < 0 || slab >= slabs) return 1000000;
+          hit[slab * n_qblk + qb] += 1;
+          xcd[slab] |= 1 << (wg & 7);
+          int& before = last[(slabs & 7) == 0 ? (wg & 7) * slabs + (slab >> 3) / group : 0];   // the group's blocks so far
+          lighter += qb > before;
+          before = qb;
         }
+        for (int x : hit) wrong += x != 1;
+        int spread = 1;
+        for (int x : xcd) spread = __builtin_popcount(x) > spread ? __builtin_popcount(x) : spread;
+        printf("blocks=%d slabs=%d group=%d wrong=%d xcds=%d lighter=%d\n", n_qblk, slabs, group, wrong, spread, lighter);
+        bad += wrong != 0 || lighter != 0 || ((slabs & 7) == 0 && spread != 1);
+      }
   return bad;
 }
 

@@ -223,11 +223,11 @@ def test_decode_workgroups_are_placed_once_and_apart(harness):
 
 
 def test_prefill_workgroups_are_placed_once_heavy_ones_first(harness):
-    """Every (query block, slab, key range) gets one workgroup; with a multiple of eight slabs a slab stays
+    """Every (query block, slab) gets one workgroup; with a multiple of eight slabs a slab stays
     on one XCD and within a group of slabs no query block comes after a lighter one."""
     rc, text = _run(harness, "prefill-place")
     lines = [dict((k, int(v)) for k, v in (kv.split("=") for kv in ln.split())) for ln in text.splitlines()]
-    assert len(lines) == 9 * 4 * 3 * 3
+    assert len(lines) == 9 * 7 * 3
     assert rc == 0, [f for f in lines if f["wrong"] or f["lighter"] or (f["slabs"] % 8 == 0 and f["xcds"] != 1)][:5]
 
 
