@@ -186,6 +186,35 @@ int prefill_cut_up() {
   return bad;
 }
 
+// Prefill launches that are not cut and whose workgroups all start together: every query block of every slab is taken by one
+// workgroup, and with a multiple of eight slabs a slab stays on one XCD.  Beyond 256 of them the unit that has the most
+// work, counted in the blocks' places from the shortest, has no more than the longest and the shortest together.
+int prefill_dealt() {
+  int bad = 0;
+  for (int slabs = 1; slabs <= 512; ++slabs)
+    for (int n_qblk = 1; n_qblk * slabs <= 512; ++n_qblk) {
+      const int n = slabs * n_qblk;
+      const uint32_t inv = rap::prefill_inv(slabs);
+      std::vector<int> hit(n, 0), xcd(slabs, 0), unit(256, 0);
+      int wrong = 0, most = 0, spread = 1;
+      for (int wg = 0; wg < n; ++wg) {
+        int nth, slab;
+        rap::prefill_place_cut(wg, n_qblk, slabs, inv, &nth, &slab);
+        if (nth < 0 || nth >= n_qblk || slab < 0 || slab >= slabs) return 1000000;
+        hit[nth * slabs + slab] += 1;
+        xcd[slab] |= 1 << (wg & 7);
+        unit[wg & 255] += n_qblk - nth;
+      }
+      for (int x : hit) wrong += x != 1;
+      for (int x : xcd) spread = __builtin_popcount(x) > spread ? __builtin_popcount(x) : spread;
+      for (int x : unit) most = x > most ? x : most;
+      const bool uneven = n > 256 && most > n_qblk + 1;
+      printf("slabs=%d blocks=%d wrong=%d xcds=%d most=%d uneven=%d\n", slabs, n_qblk, wrong, spread, most, uneven);
+      bad += wrong != 0 || ((slabs & 7) == 0 && spread != 1) || uneven;
+    }
+  return bad;
+}
+
 int flat(bool one_length) {
   const int cus = 256;
   int bad = 0;
@@ -315,7 +344,7 @@ int pieceplan(bool read_whole) {
 
 int main(int argc, char** argv) {
   if (argc != 2) {
-    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|flat|flat-one-length|prefill-place|prefill-cut\n");
+    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|flat|flat-one-length|prefill-place|prefill-cut|prefill-deal\n");
     return 2;
   }
   if (strcmp(argv[1], "loadplan") == 0) return loadplan(false) == 0 ? 0 : 1;
@@ -324,6 +353,7 @@ int main(int argc, char** argv) {
   if (strcmp(argv[1], "flat-one-length") == 0) return flat(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "prefill-place") == 0) return prefill_placed() == 0 ? 0 : 1;
   if (strcmp(argv[1], "prefill-cut") == 0) return prefill_cut_up() == 0 ? 0 : 1;
+  if (strcmp(argv[1], "prefill-deal") == 0) return prefill_dealt() == 0 ? 0 : 1;
   if (strcmp(argv[1], "place") == 0) return place(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "place-rotated") == 0) return place(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "pieceplan") == 0) return pieceplan(false) == 0 ? 0 : 1;

@@ -241,6 +241,15 @@ def test_prefill_key_ranges_cover_every_block_once(harness):
     assert rc == 0, [f for f in lines if f["wrong"] or f["unordered"] or (f["slabs"] % 8 == 0 and f["xcds"] != 1)][:5]
 
 
+def test_prefill_workgroups_that_start_together_are_dealt_once(harness):
+    """Launches of up to 512 workgroups that are not cut: every (query block, slab) once, a slab on one XCD where they
+    number a multiple of eight, and the longest blocks share a compute unit with the shortest."""
+    rc, text = _run(harness, "prefill-deal")
+    lines = [dict((k, int(v)) for k, v in (kv.split("=") for kv in ln.split())) for ln in text.splitlines()]
+    assert len(lines) > 3000 and any(f["slabs"] * f["blocks"] == 512 for f in lines)
+    assert rc == 0, [f for f in lines if f["wrong"] or f["uneven"] or (f["slabs"] % 8 == 0 and f["xcds"] != 1)][:5]
+
+
 def test_ranges_by_length_cover_and_fill(harness):
     """The row ranges of a batch of unequal lengths, as the decode and the combining kernel find them: every unit of 128
     rows once, inside the partials' room; and lengths within a tenth of each other put no more rows on any compute unit
