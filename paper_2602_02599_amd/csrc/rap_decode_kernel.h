@@ -214,8 +214,15 @@ __device__ __forceinline__ void static_for_pairs(F&& f) {
   static_for_pairs_seq(std::make_integer_sequence<int, N>(), f);
 }
 
-// Wavefronts per SIMD that an instantiation's registers are to leave room for: what its tile and accumulators allow
-// without spilling (fp8, 30 pairs, d_v = 60, 16 x 16384 rows: four 47.1 us, three 53.2).
+// Whether there is a lean loop in front of the loop for all tiles (kLongRanges).  Three score steps with seven or eight
+// channel tiles spill too much for it (33 pairs, d_v = 100: 62.3 us, lean 66.3; paged, two with eight, 66.0 and 69.6).
+constexpr bool decode_lean(int kch, int nt, bool paged, bool q8, int mx4b) {
+  return q8 || mx4b > 0 || !((kch == 3 && nt >= 7) || (kch == 2 && nt == 8 && paged));
+}
+
+// Wavefronts per SIMD that an instantiation's registers are to leave room for: as many as its tile and accumulators allow
+// with few spills or none (fp8, 30 pairs, d_v = 60, 16 x 16384 rows: four 47.1 us, three 53.2).  Three score steps with eight
+// channel tiles spill most, 16 registers, and 39 over paged caches.
 constexpr int decode_waves(int kch, int nt, bool vpair, bool q8, int mx4b, bool lean) {
   if (mx4b > 0) return nt == 4 && kch <= 3 ? 4 : 3;
   if (!lean) return kch <= 3 ? 3 : 2;
@@ -790,12 +797,10 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM !=
   // All tiles but a wavefront's last one or two are lean: loads without a condition need no copies of the registers
   // they go to (60 to 150 instructions of a tile's 390 to 330), and no row masks.  16 x 32768 rows, 4-bit, 89.4 -> 81.9 us;
   // fp8 32 x 16384 126.2 -> 121.9, ragged 40 x 7989 48.2 -> 41.8; bf16 10 x 30925 124.7 -> 119.7, 16 x 8192 61.8
-  // -> 61.2 us.  Three score steps with seven or eight channel tiles spill too much for it (33 pairs, d_v = 100: 62.3
-  // us, lean 66.3; paged, two with eight, 66.0 and 69.6).  Ranges of up to four tiles per wavefront gain nothing, and the
-  // second loop in their way costs them up to 1 us (2 x 6000, 24 pairs, 10.0 us, with it 11.1): they have none.
+  // -> 61.2 us.  Ranges of up to four tiles per wavefront gain nothing, and the second loop in their way costs them up to
+  // 1 us (2 x 6000, 24 pairs, 10.0 us, with it 11.1): they have none.
   int base = first;
-  constexpr bool LEAN_PAYS = FORM != kShortRanges && (Q8 || MX4 || !((KCH == 3 && NT >= 7) || (KCH == 2 && NT == 8 && PAGED)));
-  if constexpr (LEAN_PAYS) {
+  if constexpr (FORM != kShortRanges && decode_lean(KCH, NT, PAGED, Q8, MX4B)) {
     const bool skips = !MX4 && t_skip >= r0 && t_skip < r1;
     if (!skips)
       for (; base + 5 * kTileRows <= r1; base += 4 * kTileRows) tile(base, std::true_type());
@@ -872,9 +877,13 @@ hipError_t launch_form(const DecodeArgs& a, hipStream_t stream) {
 template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL = false, int MX4B = 0>
 hipError_t launch_inst2(const DecodeArgs& a, hipStream_t stream) {
   if (a.flat_wgs > 0) return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kByLength>(a, stream);
-  if constexpr (!Q8 && MX4B == 0)
-    if (a.rows_per_split <= 16 * kTileRows) return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kShortRanges>(a, stream);
-  return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kLongRanges>(a, stream);
+  if constexpr (!decode_lean(KCH, NT, PAGED, Q8, MX4B)) {
+    return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kShortRanges>(a, stream);
+  } else {
+    if constexpr (!Q8 && MX4B == 0)
+      if (a.rows_per_split <= 16 * kTileRows) return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kShortRanges>(a, stream);
+    return launch_form<KCH, NT, VPAIR, PAGED, Q8, AL, MX4B, kLongRanges>(a, stream);
+  }
 }
 
 }  // namespace
