@@ -109,6 +109,7 @@ struct DecodeArgs {
   // matrix instruction; the causal part among the tokens themselves is added by the combining
   // kernel, which always runs.  "Query row" below is then (b * n_tok + token) * H_q + head.
   int32_t n_tok;
+  int32_t flat_wgs;         // see flat_slots; 0: ranges of rows_per_split rows
   int32_t group_inv16;      // ceil(65536 / group): (c * group_inv16) >> 16 == c / group for c < 16
   float* out;          // [B, H_q, d_v]
   float* part_acc;     // [query rows, n_slots, d_v]   un-normalised accumulators
@@ -117,13 +118,15 @@ struct DecodeArgs {
   int32_t max_len, rows_per_split, n_split;
   int32_t n_slots;          // partial slots per query head: n_split, plus one in the decode step
   int32_t lds_wave_bytes;   // matrix-core kernel: LDS slice of one wavefront
+  int64_t cap;
+  float scale_log2e;   // softmax scale * log2(e): exponentials are taken as exp2
   // Ranges by length (flat_wgs > 0, FlatPlan; matrix-core kernel, up to 64 sequences): how many ranges a sequence has is found
   // on the device, from its length and the others': as many as every other where they are about of one length, else so many
   // that the ranges are about as long as each other and no more than flat_wgs per KV head.  Partials are then
   // [H_kv, flat_slots, n_tok * group], sequence by sequence, range by range, the new tokens of a decode step behind.
-  int32_t flat_wgs, flat_slots, flat_full, flat_few;
-  int64_t cap;
-  float scale_log2e;   // softmax scale * log2(e): exponentials are taken as exp2
+  // (At the end, and flat_wgs where there is room: kernels for short ranges with four score steps read 82 scalars back from
+  // vector registers with `cap` behind these numbers and 40 without.  1 x 24831 rows, d = 128, 33.25 and 33.0 us.)
+  int32_t flat_slots, flat_full, flat_few;   // and flat_wgs
 };
 
 constexpr int kMaxOrdered = 128;

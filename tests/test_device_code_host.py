@@ -238,3 +238,23 @@ def test_tile_in_flight_is_not_waited_for(functions):
                     j += 1
     assert n > 150
     assert not bad, "%d, first: %s" % (len(bad), bad[0])
+
+
+def _short_forms(functions):
+    """(score steps, channel tiles, paired, paged) -> (code, its loop over tiles) of the bf16 decode kernels for short ranges."""
+    out = {}
+    for name, code in functions:
+        form = re.search(r"decode_mfma_kernelILi(\d+)ELi(\d+)ELb(\d)ELb(\d)ELb0ELb\dELi0ELi0E", name)
+        loops = [part for part in _loops(code) if any(code[i][0].startswith("v_mfma") for i in part)] if form else []
+        if loops:
+            assert len(loops) == 1, name
+            out[tuple(int(x) for x in form.groups())] = code, loops[0]
+    assert len(out) == 96
+    return out
+
+
+def test_short_ranges_spill_few_scalars(functions):
+    """Scalars that did not fit are read back from vector registers 28 to 45 times in these kernels, and were 82 times where
+    the order of the arguments made the compiler load them in other groups (1 x 24831 rows, d = 128, 33.0 -> 33.25 us)."""
+    reads = {k: sum(op == "v_readlane_b32" for op, _, _ in code) for k, (code, _) in _short_forms(functions).items()}
+    assert max(reads.values()) <= 50, {k: n for k, n in reads.items() if n > 50}
