@@ -258,3 +258,13 @@ def test_short_ranges_spill_few_scalars(functions):
     the order of the arguments made the compiler load them in other groups (1 x 24831 rows, d = 128, 33.0 -> 33.25 us)."""
     reads = {k: sum(op == "v_readlane_b32" for op, _, _ in code) for k, (code, _) in _short_forms(functions).items()}
     assert max(reads.values()) <= 50, {k: n for k, n in reads.items() if n > 50}
+
+
+def test_short_ranges_of_pages_wait_no_more_than_dense_ones(functions):
+    """The loop over tiles of a paged kernel has about as many waits as that of the dense one; it had up to 20 more where reads
+    from LDS were waited for one by one (2 x 3780 rows, d = 106, 11.65 -> 11.9 us).  Three score steps with eight channel
+    tiles spill, and wait for that too."""
+    forms = _short_forms(functions)
+    waits = {k: sum(code[i][0] == "s_waitcnt" for i in loop) for k, (code, loop) in forms.items()}
+    over = {k: (n, waits[k[:3] + (0,)]) for k, n in waits.items() if k[3] and k[:2] != (3, 8) and n > waits[k[:3] + (0,)] + 6}
+    assert not over, over
