@@ -235,6 +235,11 @@ __host__ __device__ __forceinline__ int flat_length(int total, int batch, int mo
   }
   return r;
 }
+// The most ranges one sequence can have, of up to `units` units (a plan with wgs > 0).
+inline int flat_most(const FlatPlan& p, int units) {
+  const int n = (units + kFlatLeast - 1) / kFlatLeast, most = n < p.wgs ? n : p.wgs;
+  return most > p.full ? most : p.full;
+}
 // First unit of piece `nth` of `n` that a sequence of `units` is cut into: the longer ones first.
 __host__ __device__ __forceinline__ int flat_begin(int nth, int n, int units) {
   const int whole = units / n, more = units - whole * n;

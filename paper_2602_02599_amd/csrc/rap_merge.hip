@@ -333,14 +333,29 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(PrefillMergeArgs a) 
 
 namespace {
 
+// Groups of 128 threads per query row: as many as the slots of a row need, eight for each.  FLAT: a long sequence among
+// short ones has more ranges than n_split, up to flat_most; its rows get groups for them while all rows' groups number no
+// more than three per compute unit, beyond which idle groups cost the other rows more than they save.  Attention
+// calls with 1 / 2 / 4 / 8 groups, one sequence long and the others a 32nd: 8 x 65536, 256 rows, 47.4 / 45.6 / 44.9 / 45.2 us, equal
+// lengths 225.2 / 225.6 / 225.4 / 226.2; 8 x 16384 20.3 / 19.2 / 19.1 / 19.6 and 63.9 / 64.0 / 64.3 / 64.8; 4 x 131072, 160 rows, 60.2 /
+// 57.4 / 56.4 / 56.8 and 165.0 / 164.3 / 164.4 / 164.8; 24 x 8192, 768 rows, 15.9 / 16.3 / 17.5 / 20.3 and 91.8 / 92.4 / 93.4 / 96.0; 64 x
+// 16384, 2048 rows, 34.2 / 35.3 / 38.7 / 47.1 and 459 / 461 / 464 / 472.
 template <int MT, bool FLAT>
 void launch_groups(const DecodeArgs& a, hipStream_t stream) {
   dim3 grid(static_cast<unsigned>(a.batch) * a.n_tok * a.n_q);
+  int slots = a.n_split;
+  if constexpr (FLAT) {
+    const FlatPlan p = {a.flat_wgs, a.flat_slots, a.flat_full, a.flat_few};
+    const int most = flat_most(p, (a.max_len + kSplitQuantum - 1) / kSplitQuantum);
+    const int each = 3 * kChipUnits / static_cast<int>(grid.x), groups = each >= 8 ? 8 : each >= 4 ? 4 : each >= 2 ? 2 : 1;
+    const int wanted = most < groups * kMergeSlots ? most : groups * kMergeSlots;
+    if (wanted > slots) slots = wanted;
+  }
   // a launch holds fewer than 2^32 threads: from 4 M query rows on, fewer groups walk the ranges in turn
   auto fits = [&](unsigned threads) { return static_cast<unsigned long long>(grid.x) * threads < (1ull << 32); };
-  if (a.n_split <= kMergeSlots || !fits(256)) hipLaunchKernelGGL((merge_kernel<MT, 1, FLAT>), grid, dim3(128), 0, stream, a);
-  else if (a.n_split <= 2 * kMergeSlots || !fits(512)) hipLaunchKernelGGL((merge_kernel<MT, 2, FLAT>), grid, dim3(256), 0, stream, a);
-  else if (a.n_split <= 4 * kMergeSlots || !fits(1024)) hipLaunchKernelGGL((merge_kernel<MT, 4, FLAT>), grid, dim3(512), 0, stream, a);
+  if (slots <= kMergeSlots || !fits(256)) hipLaunchKernelGGL((merge_kernel<MT, 1, FLAT>), grid, dim3(128), 0, stream, a);
+  else if (slots <= 2 * kMergeSlots || !fits(512)) hipLaunchKernelGGL((merge_kernel<MT, 2, FLAT>), grid, dim3(256), 0, stream, a);
+  else if (slots <= 4 * kMergeSlots || !fits(1024)) hipLaunchKernelGGL((merge_kernel<MT, 4, FLAT>), grid, dim3(512), 0, stream, a);
   else hipLaunchKernelGGL((merge_kernel<MT, 8, FLAT>), grid, dim3(1024), 0, stream, a);
 }
 

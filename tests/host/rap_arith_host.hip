@@ -258,7 +258,7 @@ int flat(bool one_length) {
                     ranges += end > begin;
                     longest_range = end - begin > longest_range ? end - begin : longest_range;
                   }
-                  wrong += from != units[b];
+                  wrong += from != units[b] || (n < units[b] ? n : units[b]) > rap::flat_most(p, most);
                   at += n;
                 }
                 wrong += at > scan_slots || p.slots > batch * (n_split + 1);
