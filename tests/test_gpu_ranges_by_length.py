@@ -1,7 +1,15 @@
-"""Decode attention whose row ranges follow the lengths of the batch, and what the header says of the order of the sums: with
-ranges of a fixed number of rows a sequence's output does not depend on its neighbours."""
+"""Decode attention whose row ranges follow the lengths of the batch, at real widths against the float64 oracle, and what
+the header says of the order of the sums: with ranges of a fixed number of rows a sequence's output does not depend on
+its neighbours.  Bars as in tests/helpers.py."""
+import math
+
+import numpy as np
 import pytest
 import torch
+
+from oracle import rap_oracle as O
+import rap_inputs as I
+from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -52,6 +60,79 @@ class Cache:
                 pools.append(pool)
             dense = pools
         self.k, self.v = dense
+
+    def head(self, h, seqs):
+        """K and V of KV head h of some sequences, for the oracle: [len(seqs), 1, cap, d] bit patterns."""
+        out = []
+        for x in (self.k, self.v):
+            if self.pg is not None:
+                x = x[self.table].view(len(self.lens), -1, *x.shape[1:])[seqs][:, :, h].flatten(1, 2)
+            else:
+                x = x[seqs][:, h]
+            x = x[:, None].contiguous()
+            out.append(x.cpu().numpy() if x.dtype == torch.uint8 else I.bits(x))
+        return out
+
+    def reference(self, q, h, seqs, scale):
+        """q [B, n_tok, H_q, d_k] -> the oracle's rows of KV head h, [len(seqs), n_tok, G, d_v]."""
+        G = q.shape[2] // self.k.shape[1]
+        qb = I.bits(q[seqs][:, :, h * G:(h + 1) * G].contiguous())
+        k, v = self.head(h, seqs)
+        lens = [self.lens[b] for b in seqs]
+        if self.kind == "mx4":
+            ks, vs = (s[seqs][:, h:h + 1].cpu().numpy() for s in self.scales)
+            return O.attn_mx4_ref(qb[:, 0], k, ks, v, vs, lens, scale, 2 * self.P, self.dv)[:, None]
+        if self.kind.startswith("fp8"):
+            ks, vs = (s[h:h + 1].cpu().numpy() for s in self.scales)
+            return O.prefill_attn_q8_ref(qb, k, v, ks, vs, lens, scale)
+        return O.prefill_attn_ref(qb, k, v, lens, scale)
+
+
+# 9 x 9000 rows over 8 KV heads: 512 workgroups of about 1400 rows.  One to four score steps, channel tiles in pairs and
+# not, with a lean loop and without (33 pairs, d_v = 100)
+WIDTHS = [(45, 90), (33, 100), (58, 115), (64, 128), (30, 61)]
+LENS = {"spread": lambda i: 600 + 8400 * i // 8, "alike": lambda i: 9000 - 97 * (i * 5 % 9), "few long": lambda i: 9000 if i in (2, 7) else 300 + i}
+
+
+@pytest.mark.parametrize("kind", ["bf16", "paged", "fp8", "fp8 paged", "mx4"])
+@pytest.mark.parametrize("P,dv", WIDTHS)
+def test_real_widths_against_the_oracle(rap, kind, P, dv):
+    B, Hkv, Hq, cap, ctx = 9, 8, 32, 9088, 9000
+    for n, (name, length) in enumerate(LENS.items()):
+        _say("%s P=%d dv=%d lengths %s" % (kind, P, dv, name))
+        lens = [length((i * 4 + n) % 9) for i in range(B)]
+        c = Cache(rap, kind, P, dv, Hkv, cap, lens, 31 * P + n)
+        shp, scale = rap.shape(B, Hq, Hkv, 128, P, dv, cap, 5e5), (0.2 if kind == "mx4" else 1.0) / math.sqrt(2 * P)
+        sl = torch.tensor(lens, dtype=torch.int32, device=DEV)
+        h = (P + dv + n) % Hkv
+        order = sorted(range(B), key=lambda b: lens[b])
+        seqs = [order[0], order[4], order[8]]
+        for n_tok in (1,) if kind == "mx4" else (1, 3):
+            q = torch.randn((B, n_tok, Hq, 2 * P), generator=c.g, device=DEV, dtype=torch.bfloat16)
+            gw, ws = H.guarded_workspace(rap, shp, ctx, n_tok=n_tok)
+            go, out = H.guarded_out((B, n_tok, Hq, dv), DEV)
+            if kind == "mx4":
+                rap.rap_decode_attn_mx4(shp, q, c.k, c.scales[0], c.v, c.scales[1], sl, ctx, out, scale, ws)
+            else:
+                rap.rap_decode_attn_multi(shp, c.k, c.v, *c.scales, c.pg, n_tok, q, sl, ctx, out, scale, ws)
+            torch.cuda.synchronize()
+            gw.check("workspace")
+            go.check("out")
+            assert bool(torch.isfinite(out).all())
+            H.assert_attn_close(out[seqs][:, :, 4 * h:4 * h + 4].cpu().numpy(), c.reference(q, h, seqs, scale), "%s, %d tokens" % (name, n_tok))
+        if kind == "mx4":
+            continue
+        # the one-call step: its new row replaces the last one
+        rand = lambda *s: torch.randn(s, generator=c.g, device=DEV, dtype=torch.bfloat16)
+        q, kn, vn = rand(B, Hq, 2 * P), rand(B, Hkv, 2 * P), rand(B, Hkv, dv)
+        keep = torch.arange(P, dtype=torch.int32, device=DEV).repeat(Hkv, 1).contiguous()
+        gw, ws = H.guarded_workspace(rap, shp, ctx)
+        go, out = H.guarded_out((B, Hq, dv), DEV)
+        rap.rap_decode_step_ex(shp, c.k, c.v, *c.scales, c.pg, kn, vn, sl - 1, keep, q, True, sl, ctx, out, scale, ws)
+        torch.cuda.synchronize()
+        gw.check("workspace")
+        go.check("out")
+        H.assert_attn_close(out[seqs][:, None, 4 * h:4 * h + 4].cpu().numpy(), c.reference(q[:, None], h, seqs, scale), name + ", one call")
 
 
 @pytest.mark.parametrize("kind", ["bf16", "fp8", "paged"])
