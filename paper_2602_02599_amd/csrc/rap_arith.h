@@ -174,6 +174,20 @@ constexpr int kSplitQuantum = 128;   // rows_per_split granularity
 struct FlatPlan {
   int wgs, slots, full, few;
 };
+// floor(a / b) for 0 <= a < 2^21 and b > 0, from 1 / b to within one unit in the last place: (a + 0.5) / b is 0.5 / b or more
+// away from any whole number, and the product is off by less than 2^-22 of itself.  Five instructions, where the general
+// division of 32-bit numbers takes twenty to thirty in a chain, which workgroups that look for their range wait for.
+constexpr int kFlatDivLimit = 1 << 21;
+__host__ __device__ __forceinline__ float flat_inverse(int b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_rcpf(static_cast<float>(b));
+#else
+  return 1.0f / static_cast<float>(b);
+#endif
+}
+__host__ __device__ __forceinline__ int flat_div(int a, float inv_b) {
+  return static_cast<int>((static_cast<float>(a) + 0.5f) * inv_b);
+}
 // Two workgroups per compute unit where that leaves two and a half or more per sequence; else as many as the chip holds
 // (three per unit up to d_k = 96), else four per sequence.  Fixed ranges and these (lengths spread evenly from max / 16 to
 // max): bf16 4 x 131072, d = 64, 163.2 -> 95.0 us, 7 x 125041, 4 KV heads, 154.5 -> 119.3, 10 x 30925 84.1 -> 70.6, 16 x 8192 42.3
@@ -195,8 +209,9 @@ inline FlatPlan flat_plan(int batch, int n_kv, int d_k, int n_split, int rows_pe
   const int shortest = fused_step || n_tok > 1 ? 1024 : 768;
   FlatPlan p = {0, 0, 0, 0};
   if (n_split < 2 || rows_per_split < shortest || w < 2 * batch || len < 1) return p;
-  p.wgs = w;
   const int units = (len + kSplitQuantum - 1) / kSplitQuantum, r = (units + n_split - 1) / n_split;
+  if (static_cast<long long>(units) * (batch + 1) >= kFlatDivLimit / 2) return p;   // (134 M rows a KV head)
+  p.wgs = w;
   p.full = (units + r - 1) / r;
   p.few = places / (n_kv * batch);
   p.slots = (w > batch * n_split ? w : batch * n_split) + (fused_step ? batch : 0);
@@ -226,7 +241,7 @@ constexpr int kFlatLeast = 4;
 template <class Count>
 __host__ __device__ __forceinline__ int flat_length(int total, int batch, int most, Count count) {
   // a sequence has one range that is not whole at most, so no longer ones than hi are needed
-  int hi = total / (most - batch) + 1, r = (total + most - 1) / most;
+  int hi = flat_div(total, flat_inverse(most - batch)) + 1, r = flat_div(total + most - 1, flat_inverse(most));
   r = r < kFlatLeast ? kFlatLeast : r;
   while (r < hi) {
     const int mid = (r + hi) >> 1;

@@ -294,7 +294,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM !=
   const int n_scan = FLAT ? (a.flat_slots - (a.new_pos != nullptr ? a.batch : 0)) * a.n_kv : a.n_split * a.n_kv * a.batch;
   const int wg = blockIdx.x;
   const int no_range = FLAT ? -1 : a.n_split;
-  int b, h, split = no_range, row0 = 0, row1 = 0;
+  int b, h, split = no_range, row0 = 0, row1 = 0, len = 0;
   if (wg < n_scan) {
     if constexpr (FLAT) {
       FlatRange f = flat_range(a, lane, wg / a.n_kv);
@@ -310,6 +310,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM !=
       }
       row0 = flat_begin(f.nth, f.n, f.units) * kSplitQuantum;
       row1 = flat_begin(f.nth + 1, f.n, f.units) * kSplitQuantum;
+      len = f.len;
     } else {
       decode_place(wg, a.n_split, a.n_kv, a.batch, &b, &split, &h);
     }
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(256, decode_waves(KCH, NT, VPAIR, Q8, MX4B, FORM !=
     h = (wg - n_scan) - b * a.n_kv;
   }
 
-  int len = a.seq_lens[b];
+  if (!FLAT || wg >= n_scan) len = a.seq_lens[b];
   len = len < 0 ? 0 : (len > a.max_len ? a.max_len : len);
   // One-call decode step: the new token's row is not in the cache yet.  As the last row it simply
   // shortens the sequence; anywhere else inside it, the row is masked like the rows beyond the end.

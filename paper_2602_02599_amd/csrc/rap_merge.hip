@@ -36,7 +36,9 @@ template <int MT, int GRP, bool FLAT>
 __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
   constexpr bool MULTI = MT > 0;
   const long long hq = blockIdx.x;                 // query row: (b * n_tok + token) * n_q + query head
-  const int b = static_cast<int>(hq / (static_cast<long long>(a.n_q) * a.n_tok));
+  // (FLAT: 32 bits, because the first slots' addresses wait for what is left over)
+  const uint32_t n_q = a.n_q, in_batch = FLAT ? blockIdx.x / (n_q * a.n_tok) : 0;
+  const int b = FLAT ? in_batch : static_cast<int>(hq / (static_cast<long long>(a.n_q) * a.n_tok));
   const int c = threadIdx.x & 127;
   const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
   const bool live = c < a.d_v;
@@ -44,8 +46,9 @@ __global__ __launch_bounds__(128 * GRP) void merge_kernel(DecodeArgs a) {
   const int stride = FLAT ? a.n_tok * a.group : 1;
   long long row0 = hq * a.n_slots;
   if constexpr (FLAT) {
-    const int qh = static_cast<int>(hq % a.n_q), qt = MULTI ? static_cast<int>((hq / a.n_q) % a.n_tok) : 0;
-    row0 = static_cast<long long>(qh / a.group) * a.flat_slots * stride + qt * a.group + qh % a.group;
+    const uint32_t in_seq = blockIdx.x - in_batch * n_q * a.n_tok, qt = MULTI ? in_seq / n_q : 0, qh = in_seq - qt * n_q;
+    const uint32_t kv = qh / static_cast<uint32_t>(a.group);
+    row0 = static_cast<long long>(kv) * a.flat_slots * stride + qt * a.group + (qh - kv * a.group);
   }
   int slot0 = FLAT ? b * a.flat_full : 0;
   const float* ml = a.part_ml + row0 * 2;

@@ -215,6 +215,20 @@ int prefill_dealt() {
   return bad;
 }
 
+// The division by an inverse that is off by a unit in the last place either way, next to every multiple of the divisor.
+int flat_divided() {
+  int bad = 0;
+  for (int b = 1; b < rap::kFlatDivLimit; b += b < 3000 ? 1 : 1 + b / 977) {
+    const float inv = rap::flat_inverse(b);
+    for (float f : {std::nextafterf(inv, 0.f), inv, std::nextafterf(inv, 2.f)})
+      for (long long m = 0; m <= rap::kFlatDivLimit; m += b * (1 + rap::kFlatDivLimit / b / 700))
+        for (long long a = m - 1; a <= m + 1; ++a)
+          if (a >= 0 && a < rap::kFlatDivLimit) bad += rap::flat_div(static_cast<int>(a), f) != a / b;
+  }
+  printf("division wrong=%d\n", bad);
+  return bad;
+}
+
 int flat(bool one_length) {
   const int cus = 256;
   int bad = 0;
@@ -344,11 +358,12 @@ int pieceplan(bool read_whole) {
 
 int main(int argc, char** argv) {
   if (argc != 2) {
-    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|flat|flat-one-length|prefill-place|prefill-cut|prefill-deal\n");
+    fprintf(stderr, "usage: rap_arith_host bf16|sincos|odd448|mx4|loadplan|loadplan-trim1|pieceplan|pieceplan-whole|place|place-rotated|flat|flat-div|flat-one-length|prefill-place|prefill-cut|prefill-deal\n");
     return 2;
   }
   if (strcmp(argv[1], "loadplan") == 0) return loadplan(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "loadplan-trim1") == 0) return loadplan(true) == 0 ? 0 : 1;
+  if (strcmp(argv[1], "flat-div") == 0) return flat_divided() == 0 ? 0 : 1;
   if (strcmp(argv[1], "flat") == 0) return flat(false) == 0 ? 0 : 1;
   if (strcmp(argv[1], "flat-one-length") == 0) return flat(true) == 0 ? 0 : 1;
   if (strcmp(argv[1], "prefill-place") == 0) return prefill_placed() == 0 ? 0 : 1;

@@ -263,3 +263,9 @@ def test_ranges_by_length_cover_and_fill(harness):
     assert rc == 1
     bad = [ln for ln in text.splitlines() if ln.startswith("sequences=24 heads=8 d_k=90 rows=8192 range=2048 how=0 pattern=1 ")]
     assert len(bad) == 1 and bad[0].endswith("wrong=0 fullest=64 equal=48"), bad
+
+
+def test_division_of_the_range_search_is_exact(harness):
+    """Floor of a quotient from an approximate inverse, over the whole range it is used in."""
+    rc, text = _run(harness, "flat-div")
+    assert rc == 0 and text.strip() == "division wrong=0", text
