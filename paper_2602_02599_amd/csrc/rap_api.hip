@@ -443,7 +443,8 @@ rap_status_t decode_impl(const DecodeRequest& r) {
   }
 
   if (p.flat && combine) {
-    const rap::FlatPlan f = rap::flat_plan(a.batch, a.n_kv, a.d_k, a.n_split, a.rows_per_split, a.max_len, a.n_tok, fused_step, device_cus());
+    const rap::FlatPlan f = rap::flat_plan(a.batch, a.n_kv, a.d_k, a.n_split, a.rows_per_split, a.max_len, a.n_tok, fused_step,
+                                           a.k_scale != nullptr || a.k_scales4 != nullptr, device_cus());
     a.flat_wgs = f.wgs;
     a.flat_slots = f.slots;
     a.flat_full = f.full;

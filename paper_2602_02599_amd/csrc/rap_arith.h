@@ -196,17 +196,22 @@ __host__ __device__ __forceinline__ int flat_div(int a, float inv_b) {
 // 81 / 83 / 83, bf16 64 x 16384 (one per sequence / ) 285 / 264 / 257.  As many as the partials' room holds where
 // that is two or more times as many: 33 x 16384, half of them an eighth as long, 146 -> 140 us, but fp8 24 x 16384 57 -> 62
 // to 70, 12 x 30000 50 -> 59.  Not for ranges of full sequences below 768 rows (1024 where the combining kernel has more to
-// do): looking at the lengths costs both kernels some 0.5 us.
+// do): looking at the lengths costs both kernels some 0.5 us.  Over codes, whose rows are half as long or less, nor for ranges
+// below 2048 rows that do not all start together, where every round of workgroups pays for that look.  Fixed ranges as they
+// were before the lean loop / by length / fixed, fp8: 116/115, 24 x 4096 full 40.9 / 44.0 / 40.1, spread 28.4 / 26.4 / 26.8;
+// d = 60, 40 x 4096 34.1 / 35.6 / 33.8 and 23.3 / 25.3 / 22.6; 48 x 3000 32.0 / 34.0 / 31.8 and 22.6 / 24.7 / 21.9; d = 90, 36 x 6000
+// 64.6 / 66.2 / 64.1 and 42.6 / 39.3 / 40.0.  What starts together gains: d = 90, 24 x 4096 31.7 / 31.1 / 30.0 and 28.5 / 23.6 / 25.5.
 inline FlatPlan flat_plan(int batch, int n_kv, int d_k, int n_split, int rows_per_split, int max_len, int n_tok, bool fused_step,
-                          int cus) {
+                          bool codes, int cus) {
   const int places = cus * (d_k <= 96 ? 3 : 2);
+  const bool one_round = static_cast<long long>(batch) * n_kv * n_split <= places;
   int w = 2 * cus / n_kv;
   if (2 * w < 5 * batch) w = places / n_kv;
   if (2 * w < 5 * batch) w = 4 * batch;
   const int room = batch * (fused_step ? n_split : n_split + 1);
   if (w > room) w = room;
   const int len = max_len - (fused_step ? 1 : n_tok > 1 ? n_tok : 0);
-  const int shortest = fused_step || n_tok > 1 ? 1024 : 768;
+  const int shortest = codes && !one_round ? 2048 : fused_step || n_tok > 1 ? 1024 : 768;
   FlatPlan p = {0, 0, 0, 0};
   if (n_split < 2 || rows_per_split < shortest || w < 2 * batch || len < 1) return p;
   const int units = (len + kSplitQuantum - 1) / kSplitQuantum, r = (units + n_split - 1) / n_split;

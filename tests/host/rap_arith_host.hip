@@ -239,7 +239,11 @@ int flat(bool one_length) {
           for (int rows : {512, 768, 1024, 1408, 2048, 2816, 4096, 8192})
             for (int how = 0; how < 3; ++how) {             // plain, five tokens, the one-call step
               const int n_split = (max_len + rows - 1) / rows, n_tok = how == 1 ? 5 : 1;
-              const rap::FlatPlan p = rap::flat_plan(batch, n_kv, d_k, n_split, rows, max_len, n_tok, how == 2, cus);
+              const rap::FlatPlan p = rap::flat_plan(batch, n_kv, d_k, n_split, rows, max_len, n_tok, how == 2, false, cus);
+              // over codes the same, or ranges of a fixed length where short ones take more than one round
+              const rap::FlatPlan q = rap::flat_plan(batch, n_kv, d_k, n_split, rows, max_len, n_tok, how == 2, true, cus);
+              const bool rounds = batch * n_kv * n_split > cus * (d_k <= 96 ? 3 : 2);
+              bad += q.wgs != (rows < 2048 && rounds ? 0 : p.wgs);
               if (p.wgs == 0) continue;
               const int most = (max_len - (how == 2 ? 1 : how == 1 ? 5 : 0) + rap::kSplitQuantum - 1) / rap::kSplitQuantum;
               const int scan_slots = p.slots - (how == 2 ? batch : 0);
