@@ -135,6 +135,48 @@ def test_real_widths_against_the_oracle(rap, kind, P, dv):
         H.assert_attn_close(out[seqs][:, None, 4 * h:4 * h + 4].cpu().numpy(), c.reference(q[:, None], h, seqs, scale), name + ", one call")
 
 
+@pytest.mark.parametrize("name", list(LENS))
+def test_extreme_scores(rap, name):
+    """One row that outweighs all others (first, last, in the middle of a sequence), rows that all weigh the same at a score far
+    below zero, and a NaN in one row of one KV head, whose rows are zeros while all others keep their bits."""
+    B, Hkv, Hq, P, dv, cap, ctx = 9, 8, 32, 45, 90, 9088, 9000
+    lens = [LENS[name]((i * 4) % 9) for i in range(B)]
+    _say("extreme scores, lengths %s" % name)
+    c = Cache(rap, "bf16", P, dv, Hkv, cap, lens, 77)
+    shp, scale = rap.shape(B, Hq, Hkv, 128, P, dv, cap, 5e5), 1.0 / math.sqrt(2 * P)
+    sl = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    q = torch.randn((B, Hq, 2 * P), generator=c.g, device=DEV, dtype=torch.bfloat16)
+
+    def attend():
+        gw, ws = H.guarded_workspace(rap, shp, ctx)
+        go, out = H.guarded_out((B, Hq, dv), DEV)
+        rap.rap_decode_attn(shp, q, c.k, c.v, sl, ctx, out, scale, ws)
+        torch.cuda.synchronize()
+        gw.check("workspace")
+        go.check("out")
+        return out.clone()
+
+    h = 3
+    for b in range(B):
+        c.k[b, h, [0, lens[b] - 1, lens[b] // 2][b % 3]] = 40.0 * q[b, 4 * h + 1]
+        c.k[b, h + 1, :lens[b]] = -40.0 * q[b, 4 * h + 6]
+    out = attend()
+    assert bool(torch.isfinite(out).all())
+    for b in range(B):
+        row = c.v[b, h, [0, lens[b] - 1, lens[b] // 2][b % 3]].float()
+        # a score some 340 above the others leaves them exp(-340); one probability in head and remainder is exact
+        assert torch.equal(out[b, 4 * h + 1], row)
+        mean = c.v[b, h + 1, :lens[b]].double().mean(0)
+        # fp32 sums of up to 9000 values of order one, over their number: 1e-7 of their root mean square each
+        assert (out[b, 4 * h + 6].double() - mean).abs().max().item() < 1e-6
+    bad = 5
+    c.k[bad, 6, lens[bad] // 3, 7] = float("nan")
+    nan = attend()
+    assert bool((nan[bad, 24:28] == 0).all())
+    nan[bad, 24:28] = out[bad, 24:28]
+    assert torch.equal(nan.view(torch.int32), out.view(torch.int32))
+
+
 @pytest.mark.parametrize("kind", ["bf16", "fp8", "paged"])
 def test_fixed_ranges_do_not_depend_on_neighbours(rap, kind):
     """24 sequences whose ranges would follow their lengths: with rows_per_split set, and with a workspace that only holds the
