@@ -155,7 +155,8 @@ rap_status_t make_plan(const rap_shape_t* s, int64_t max_seq_len, const rap_tuni
   const int64_t k0 = 2 * cus / slabs > 1 ? 2 * cus / slabs : 1;                // ranges per slab, plain rule
   const int64_t halves = round_to_quantum((max_seq_len + k0 - 1) / k0);
   int64_t r = halves < 512 ? 512 : (halves > 4096 ? 4096 : halves);
-  // workgroups the chip holds at once: three per compute unit up to d_k = 96, else two
+  // workgroups the chip holds at once: three per compute unit up to d_k = 96, else two (narrow instantiations leave room for
+  // four, decode_waves; the rule's figures are with three)
   const int64_t places = cus * (2 * s->n_pairs <= 96 ? 3 : 2);
   const int64_t n_wg = slabs * ((max_seq_len + r - 1) / r);
   const bool single_round = n_wg > places && n_wg < 2 * places && halves <= 8192;

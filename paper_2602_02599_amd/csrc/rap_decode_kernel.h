@@ -266,8 +266,10 @@ constexpr int kMaxCols = 16;   // columns of the matrix instruction: query rows 
 // -> 93 us (3.4 -> 4.6 TB/s); 64 wide 87 -> 68, 128 wide 130 -> 102 us.  What bounds it now is the
 // vector ALU, 255 instructions per 32 rows and 60 % busy; row masks and clamped V rows are off the
 // common path for that reason (without that 103 us).
-// FORM: kShortRanges, one loop for all tiles; kLongRanges, a lean loop in front of it (which over codes costs short ranges
-// nothing, so that there is no other form of them).
+// FORM: kShortRanges, one loop for all tiles; kLongRanges, a lean loop in front of it.  Over codes that is as fast or faster for
+// short ranges too, and there is no other form of them (one loop / with the lean one: fp8 1 x 2048 rows 9.0 / 8.9 us, 1 x
+// 8192 10.75 / 10.4, 1 x 32768 18.3 / 17.6, 4 x 8192 16.3 / 15.6; groups of eight 9.4 / 9.3, 11.4 / 11.2, 18.6 / 17.8, 17.1 /
+// 16.5; 4-bit 8.8 / 8.75, 10.75 / 10.7, 16.25 / 16.1, 15.3 / 14.9).
 // kByLength: the lean loop, and ranges by length (DecodeArgs).
 enum { kShortRanges = 0, kLongRanges = 1, kByLength = 2 };
 template <int KCH, int NT, bool VPAIR, bool PAGED, bool Q8, bool AL, int MX4B, int FORM>
