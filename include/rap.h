@@ -158,10 +158,10 @@ size_t rap_decode_attn_workspace_bytes(const rap_shape_t* shape, int64_t max_seq
  *              The cut, and with it the order of the fp32 sums and which rows fall into one range,
  *              depends on shape, max_seq_len, tuning, device, on whether the workspace holds the
  *              queried size and, where that leaves the choice to the call (rows_per_split 0, a
- *              workspace of the queried size, more than one sequence), on seq_lens: the ranges of a
- *              sequence then follow the lengths of all sequences of the batch, so that its output can
- *              differ in the last bits with the lengths of its neighbours.  It depends on nothing
- *              else.  With rows_per_split set, or with the smaller workspace, every sequence is cut at
+ *              workspace of the queried size, more than one sequence), on seq_lens and, in the
+ *              one-call step, on pos: the ranges of a sequence then follow the lengths of all sequences
+ *              of the batch, so that its output can differ in the last bits with the lengths of its
+ *              neighbours.  It depends on nothing else.  With rows_per_split set, or with the smaller workspace, every sequence is cut at
  *              multiples of one number of rows that seq_lens has no part in, and an output row has the
  *              same bits whatever the lengths of the other sequences are.  This holds for all decode
  *              attention calls below (rotating, one-call step, fp8, 4-bit, paged, several tokens).
